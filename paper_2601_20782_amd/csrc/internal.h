@@ -70,10 +70,12 @@ struct CnnDev {
     int64_t w0 = 0, b0 = 0, gf = 0, bef = 0;
     int64_t g[NQS_MAX_LAYERS] = {0}, be[NQS_MAX_LAYERS] = {0}, w1[NQS_MAX_LAYERS] = {0}, b1[NQS_MAX_LAYERS] = {0},
             w2[NQS_MAX_LAYERS] = {0}, b2[NQS_MAX_LAYERS] = {0};
-    // matrix-core operands: block r's conv1 (j = 0) and conv2 (j = 1) weights at
-    // wmc + (2 r + j) 9 F^2 elements, laid out [offset][out channel][in channel];
-    // raw BF16/FP16 codes for those copies, FP32 values for the FP32 copy
+    // matrix-core operands: block r's conv1 (j = 0) and conv2 (j = 1) weights at (2 r + j) 9 F^2 elements;
+    // wmf: FP32 values, [offset][out channel][in channel c at (c % 4) F / 4 + c / 4], written for F a multiple
+    // of 4; wmc: raw BF16/FP16 codes, [offset][out channel][in channel], wmf itself for the FP32 copy
+    float *wmf = nullptr;
     void *wmc = nullptr;
+    uint16_t *nbr = nullptr;  // [site][16] neighbours of the 3 x 3 window: 0, 2, 4, 6, 8, pads, 1, 3, 5, 7, pads
 };
 
 // Complex-parameter RBM copy: FP32 (real, imaginary) pairs of the rounded
