@@ -90,6 +90,62 @@ void *workspace_slot(int slot, size_t bytes, hipStream_t stream)
 
 void *workspace(size_t bytes, hipStream_t stream) { return workspace_slot(0, bytes, stream); }
 
+// ---- scratch of one call (ScratchLease) ----
+struct LeaseSlot {
+    std::mutex mu;
+    void *ptr = nullptr;
+    size_t bytes = 0;
+    hipEvent_t done = nullptr;
+    bool used = false;
+};
+constexpr int kLeaseDevices = 64;
+static LeaseSlot g_lease[kLeaseDevices];
+
+ScratchLease::ScratchLease(size_t bytes, hipStream_t stream) : stream_(stream)
+{
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kLeaseDevices) return;
+    LeaseSlot &l = g_lease[dev];
+    l.mu.lock();
+    dev_ = dev;
+    if (!l.done && hipEventCreateWithFlags(&l.done, hipEventDisableTiming) != hipSuccess) {
+        l.done = nullptr;
+        return;
+    }
+    if (l.bytes < bytes) {
+        if (l.used && hipEventSynchronize(l.done) != hipSuccess) return;
+        l.used = false;
+        if (l.ptr) (void)hipFree(l.ptr);
+        l.ptr = nullptr;
+        l.bytes = 0;
+        const size_t want = std::max<size_t>(bytes, (size_t)1 << 20);
+        if (hipMalloc(&l.ptr, want) != hipSuccess) {
+            l.ptr = nullptr;
+            return;
+        }
+        l.bytes = want;
+    }
+    if (l.used && hipStreamWaitEvent(stream, l.done, 0) != hipSuccess) return;
+    ptr_ = l.ptr;
+}
+
+ScratchLease::~ScratchLease()
+{
+    if (dev_ < 0) return;
+    LeaseSlot &l = g_lease[dev_];
+    if (ptr_) {
+        l.used = hipEventRecord(l.done, stream_) == hipSuccess;
+        if (!l.used) (void)hipStreamSynchronize(stream_);
+    }
+    l.mu.unlock();
+}
+
+bool stream_capturing(hipStream_t stream)
+{
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    return hipStreamIsCapturing(stream, &st) == hipSuccess && st != hipStreamCaptureStatusNone;
+}
+
 int64_t model_num_params(const nqs_model_desc &d)
 {
     const int64_t N = d.n_visible;

@@ -854,7 +854,7 @@ __global__ void __launch_bounds__(kMcThreads, 4) cnn_sample_mc_kernel(CnnSampleA
 // The n (S + 1) configurations (each sample, then its S flips) are numbered through and a workgroup takes B at a
 // time, so that the grid is full whatever n is; their log psi go to f[n][S + 1] and one wave per sample sums the
 // ratios.  FP32 products on the matrix cores for every format (activations rounded to it), each sum a chain of
-// fmaf that starts at the bias, so the values are the one-configuration kernel's bit for bit.
+// fmaf that starts at the bias, so the log psi are the one-configuration kernel's bit for bit.
 template <int F>
 __global__ void __launch_bounds__(kMcThreads, 4) cnn_eloc_logpsi_kernel(CnnDev net, const int8_t *__restrict__ samples,
                                                                         int64_t n, int B, float *__restrict__ f)
@@ -874,15 +874,14 @@ __global__ void __launch_bounds__(kMcThreads, 4) cnn_eloc_logpsi_kernel(CnnDev n
         }
         __syncthreads();
         cnn_mc_forward<kF32, F, true>(net, net.wmf, l, rows, net.dtype);
-        // log psi in the one-configuration kernel's order: threads s, s + 256, ... of its 256, a wave's threads
-        // by a butterfly, then the four waves
+        // log psi in the one-configuration kernel's order: a site per thread, a wave's threads by a butterfly,
+        // then the four waves
         const int lane = tid & 63;
         for (int b = tid >> 6; b < B; b += kMcWaves) {
             float a = 0.0f;
             for (int w = 0; w < kCnnThreads / 64; ++w) {
-                float part = 0.0f;
-                for (int s = w * 64 + lane; s < S; s += kCnnThreads) part += rsum[(size_t)(b * S + s) * F];
-                a += group_sum<64>(part);
+                const int s = w * 64 + lane;
+                a += group_sum<64>(s < S ? rsum[(size_t)(b * S + s) * F] : 0.0f);
             }
             if (lane == 0 && q0 + b < total) f[q0 + b] = a;
         }
@@ -1050,12 +1049,16 @@ nqs_status cnn_local_energy(nqs_model *m, const nqs_ham_desc &ham, const int8_t 
     const CnnDev &net = m->copies[dtype].cnn;
     if ((st = cnn_check(net)) != NQS_OK) return st;
     const int L = net.L, S = L * L, F = net.F;
-    // 16 and 32 channels whose batch fits LDS: the batched forward pass (the values are the same bit for bit)
-    if ((F == 16 || F == 32) && S <= 65536 / 2 && L <= 255 && cnn_mc_lds_bytes(1, S, F, 4) <= 160 * 1024) {
-        const int64_t total_max = (int64_t)16 << 20;   // log psi values kept at a time: 64 MB of workspace
-        const int64_t chunk = std::max<int64_t>(1, std::min<int64_t>(n, total_max / (S + 1)));
-        float *f = (float *)workspace(sizeof(float) * (size_t)chunk * (S + 1), stream);
-        if (!f) return set_error(NQS_ENOMEM, "workspace allocation failed");
+    // 16 and 32 channels on up to 256 sites whose batch fits LDS: the batched forward pass, whose log psi are the
+    // one-configuration kernel's bit for bit (beyond 256 sites a thread of that kernel sums two sites' channels as one
+    // chain).  A captured call takes the one-configuration kernel, which needs no scratch.
+    if ((F == 16 || F == 32) && S <= kCnnThreads && cnn_mc_lds_bytes(1, S, F, 4) <= 160 * 1024 &&
+        !stream_capturing(stream)) {
+        // log psi values kept at a time: 64 MB of scratch
+        const int64_t chunk = std::max<int64_t>(1, std::min<int64_t>(n, ((int64_t)16 << 20) / (S + 1)));
+        const ScratchLease lease(sizeof(float) * (size_t)chunk * (S + 1), stream);
+        float *f = (float *)lease.ptr();
+        if (!f) return set_error(NQS_ENOMEM, "scratch allocation failed");
         for (int64_t k0 = 0; k0 < n; k0 += chunk) {
             const int64_t kn = std::min(chunk, n - k0), count = kn * (S + 1);
             const int B = cnn_mc_batch(S, F, 4, count);

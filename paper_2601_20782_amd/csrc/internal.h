@@ -144,6 +144,27 @@ void *workspace(size_t bytes, hipStream_t stream);
 // (which use slot 0).
 constexpr int kWorkspaceSlots = 3;
 void *workspace_slot(int slot, size_t bytes, hipStream_t stream);
+
+// Scratch of one call, for entry points that any thread and stream may use at the same time: one buffer per
+// device, grown on demand, that a call holds while it enqueues its kernels.  The holder's stream first waits for
+// the event that the previous holder recorded behind its last kernel, so calls on different streams take turns
+// on the device; a mutex keeps the launches of two threads from interleaving.  Callers ask for at most
+// kLeaseBytes (larger problems are cut into chunks) and not from a stream that is being captured (a captured
+// graph would keep the address of a buffer that may grow, hence move, before a replay).
+constexpr size_t kLeaseBytes = (size_t)256 << 20;
+class ScratchLease {
+public:
+    ScratchLease(size_t bytes, hipStream_t stream);
+    ~ScratchLease();
+    ScratchLease(const ScratchLease &) = delete;
+    ScratchLease &operator=(const ScratchLease &) = delete;
+    void *ptr() const { return ptr_; }   // nullptr: the allocation failed
+private:
+    void *ptr_ = nullptr;
+    int dev_ = -1;
+    hipStream_t stream_;
+};
+bool stream_capturing(hipStream_t stream);
 // low-precision Cholesky factor of T + shift and its inverse (srmix.hip)
 size_t mix_workspace_bytes(int64_t n);
 nqs_status mix_factor(const float *T, int64_t n, double shift, int fmt, void *ws, float **Lin, float **LinT,
