@@ -323,8 +323,6 @@ struct GradArgs {
     float *O;         // columns [p0, p1) of O, row stride p1 - p0
     int64_t P;
     int64_t p0, p1;
-    float *acts;      // factor kernel: [n][sum of layer inputs] inputs a_{l-1} of every layer, post-ReLU
-    float *dels;      // factor kernel: [n][sum of layer outputs] backpropagated deltas
     int lds_stride;   // floats reserved per layer activation vector
 };
 
@@ -437,106 +435,282 @@ nqs_status launch_vjp_chunk(const float *O, const float *g, int64_t n, int64_t P
     return NQS_OK;
 }
 
-// Factors of O for B samples per block: the layer inputs a_{l-1} (post-ReLU) and
-// the deltas of every layer.  Each weight read from memory serves B samples;
-// per sample the arithmetic (and its order) is that of ffnn_grad_kernel, so
-// delta_l[r] * a_{l-1}[c] reproduces its O bit for bit.
-template <int B>
-__global__ void __launch_bounds__(256) ffnn_factor_kernel(GradArgs A)
+// ---------------------------------------------------------------------------
+// Factors of O for many samples: the layer inputs a_{l-1} and the deltas of every layer, whose outer products are
+// the blocks of O.  Forward and backward pass are products of the samples' rows with the layer's weights on the
+// FP32 matrix cores:
+//   z_l = a_{l-1} W_l^T + b_l (k in order, starting at the bias),  delta_{l-1} = (delta_l W_l) * [a_{l-1} > 0].
+// v_mfma_f32_16x16x4_f32 adds its four products one after another with one rounding each, so every sum is the
+// chain of fmaf of ffnn_grad_kernel (one block per sample) and the factors reproduce its O bit for bit.  No split of
+// the contraction: it would change the chain.
+//
+// 64 samples x 64 outputs per block of four waves (2 x 2 tiles of 16 x 16 each), 32 contraction steps per barrier,
+// the next ones loaded into registers meanwhile; row strides of 36 and 80 floats spread a fragment read over all 64
+// banks.  log psi of 4096 samples of the 100-400-200 network: 48 us (five
+// launches; the products take half of it) against 175 us with one block per sample, whose sums wait for L2.
+// ---------------------------------------------------------------------------
+constexpr int kGmTile = 64, kGmStep = 32, kGmLdx = 36, kGmLdb = 80;
+typedef float gm_f32x4 __attribute__((ext_vector_type(4)));
+
+struct FactorGemmArgs {
+    const float *X;      // [n][ldx], K columns
+    const float *B;      // [K][N]
+    const float *bias;   // [N] start of the sums, or NULL (0)
+    const float *mask;   // [n][ldm]: outputs where it is not positive are 0; or NULL
+    float *out;          // [n][ldo], N columns
+    int64_t n, ldx, ldm, ldo;
+    int K, N, relu;
+};
+
+__global__ void __launch_bounds__(256) ffnn_factor_gemm_kernel(FactorGemmArgs A)
 {
-    extern __shared__ float smem[];
-    const FfnnDev &net = A.net;
+    __shared__ float Xs[2][kGmTile * kGmLdx], Bs[2][kGmStep * kGmLdb];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, la = lane & 15, lk = lane >> 4;
+    const int64_t m0 = blockIdx.y * (int64_t)kGmTile;
+    const int n0 = blockIdx.x * kGmTile, wm = (wave >> 1) * 32, wn = (wave & 1) * 32;
+    // staging: rows xr + 8 i of X at step xk; steps br + 4 i of B at column bc
+    const int xk = tid & 31, xr = tid >> 5, bc = tid & 63, br = tid >> 6;
+    float xv[8], bv[8];
+    auto load = [&](int k0) {
+        const int k = k0 + xk;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            const int64_t row = m0 + xr + 8 * i;
+            xv[i] = row < A.n && k < A.K ? A.X[row * A.ldx + k] : 0.0f;
+            const int kb = k0 + br + 4 * i, col = n0 + bc;
+            bv[i] = kb < A.K && col < A.N ? A.B[(size_t)kb * A.N + col] : 0.0f;
+        }
+    };
+    auto store = [&](int buf) {
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            Xs[buf][(xr + 8 * i) * kGmLdx + xk] = xv[i];
+            Bs[buf][(br + 4 * i) * kGmLdb + bc] = bv[i];
+        }
+    };
+    gm_f32x4 acc[2][2];
+#pragma unroll
+    for (int b = 0; b < 2; ++b) {
+        const int col = n0 + wn + 16 * b + la;
+        const float v = A.bias && col < A.N ? A.bias[col] : 0.0f;
+#pragma unroll
+        for (int a = 0; a < 2; ++a) acc[a][b] = gm_f32x4{v, v, v, v};
+    }
+    load(0);
+    store(0);
+    int buf = 0;
+    for (int k0 = 0; k0 < A.K; k0 += kGmStep) {
+        __syncthreads();
+        const bool more = k0 + kGmStep < A.K;
+        if (more) load(k0 + kGmStep);
+#pragma unroll
+        for (int s = 0; s < kGmStep / 4; ++s) {
+            float a[2], b[2];
+#pragma unroll
+            for (int q = 0; q < 2; ++q) {
+                a[q] = Xs[buf][(wm + 16 * q + la) * kGmLdx + 4 * s + lk];
+                b[q] = Bs[buf][(4 * s + lk) * kGmLdb + wn + 16 * q + la];
+            }
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
+#pragma unroll
+                for (int j = 0; j < 2; ++j)
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i], b[j], acc[i][j], 0, 0, 0);
+        }
+        if (more) store(buf ^ 1);
+        buf ^= 1;
+    }
+    // D[i][j] of a 16 x 16 block: j = lane % 16 (output), i = 4 (lane / 16) + register (sample)
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int64_t row = m0 + wm + 16 * i + 4 * lk + r;
+                const int col = n0 + wn + 16 * j + la;
+                if (row >= A.n || col >= A.N) continue;
+                float v = acc[i][j][r];
+                if (A.relu) v = fmaxf(v, 0.0f);
+                if (A.mask) v = A.mask[row * A.ldm + col] > 0.0f ? v : 0.0f;
+                A.out[row * A.ldo + col] = v;
+            }
+}
+
+// spins as the first layer's inputs (row stride sa)
+__global__ void ffnn_factor_spins_kernel(const int8_t *__restrict__ samples, int64_t n, int N, int64_t sa,
+                                         float *__restrict__ acts)
+{
+    const int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+    if (e >= n * N) return;
+    const int64_t k = e / N;
+    acts[k * sa + (e - k * N)] = (float)samples[e];
+}
+
+// The head of one sample per block: log psi = sum log cosh z in ffnn_grad_kernel's order, and z -> tanh z in place.
+__global__ void __launch_bounds__(256) ffnn_factor_head_kernel(float *z, int64_t n, int64_t ld, int w,
+                                                               float *__restrict__ logpsi)
+{
+    __shared__ float red[4];
+    for (int64_t k = blockIdx.x; k < n; k += gridDim.x) {
+        float *zk = z + k * ld;
+        float part = 0.0f;
+        for (int r = threadIdx.x; r < w; r += 256) {
+            const float v = zk[r];
+            if (logpsi) part += logcosh_f32(v);
+            zk[r] = tanhf(v);
+        }
+        if (!logpsi) continue;
+        part = group_sum<64>(part);
+        if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = part;
+        __syncthreads();
+        if (threadIdx.x == 0) logpsi[k] = red[0] + red[1] + red[2] + red[3];
+        __syncthreads();
+    }
+}
+
+// acts [n][sum of the layers' inputs], dels [n][sum of their outputs]; logpsi may be NULL.  Without `backward` only
+// the last layer's deltas are formed.
+static nqs_status factors_from(const FfnnDev &net, const int8_t *samples, int64_t n, float *acts, float *dels,
+                               float *logpsi, bool backward, hipStream_t stream)
+{
     const int L = net.n_layers, N = net.widths[0];
-    // per sample, packed: spins [N], pre-activations of every layer, two delta vectors of S floats
-    const int S = A.lds_stride;
-    const int tid = threadIdx.x, nt = blockDim.x;
-    int64_t sa = 0, sd = 0;
-    int zoff[NQS_MAX_LAYERS];
-    int R = (N + 3) & ~3;
+    int64_t sa = 0, sd = 0, oa[NQS_MAX_LAYERS], od[NQS_MAX_LAYERS];
     for (int l = 0; l < L; ++l) {
+        oa[l] = sa;
+        od[l] = sd;
         sa += net.widths[l];
         sd += net.widths[l + 1];
-        zoff[l] = R;
-        R += (net.widths[l + 1] + 3) & ~3;
     }
-    const int doff = R;
-    R += 2 * S;
-    auto in0 = [&](int b) { return smem + (size_t)b * R; };
-    auto zl = [&](int b, int l) { return smem + (size_t)b * R + zoff[l]; };
-    auto dlb = [&](int b, int h) { return smem + (size_t)b * R + doff + (size_t)h * S; };
-    for (int64_t s0 = (int64_t)blockIdx.x * B; s0 < A.n; s0 += (int64_t)gridDim.x * B) {
-        const int nb = (int)min((int64_t)B, A.n - s0);
-        for (int e = tid; e < B * N; e += nt) {
-            const int b = e / N, i = e - b * N;
-            in0(b)[i] = b < nb ? (float)A.samples[(s0 + b) * N + i] : 0.0f;
-        }
-        __syncthreads();
-        for (int l = 0; l < L; ++l) {
-            const int out = net.widths[l + 1], in = net.widths[l];
-            const float *Wt = net.Wt[l];
-            for (int r = tid; r < out; r += nt) {
-                float acc[B];
-#pragma unroll
-                for (int b = 0; b < B; ++b) acc[b] = net.b[l][r];
-#pragma unroll 4
-                for (int k = 0; k < in; ++k) {
-                    const float w = Wt[(size_t)k * out + r];
-#pragma unroll
-                    for (int b = 0; b < B; ++b) {
-                        const float x = l == 0 ? in0(b)[k] : fmaxf(zl(b, l - 1)[k], 0.0f);
-                        acc[b] = fmaf(w, x, acc[b]);
-                    }
-                }
-#pragma unroll
-                for (int b = 0; b < B; ++b) zl(b, l)[r] = acc[b];
-            }
-            __syncthreads();
-        }
-        // layer inputs
-        for (int b = 0; b < nb; ++b) {
-            float *ar = A.acts + (s0 + b) * sa;
-            int64_t oa = 0;
-            for (int l = 0; l < L; ++l) {
-                const int in = net.widths[l];
-                for (int k = tid; k < in; k += nt) ar[oa + k] = l == 0 ? in0(b)[k] : fmaxf(zl(b, l - 1)[k], 0.0f);
-                oa += in;
-            }
-        }
-        const int wl = net.widths[L];
-        for (int e = tid; e < B * wl; e += nt) {
-            const int b = e / wl, r = e - b * wl;
-            dlb(b, 0)[r] = tanhf(zl(b, L - 1)[r]);
-        }
-        __syncthreads();
-        int h = 0;
-        int64_t od = sd;
-        for (int l = L - 1; l >= 0; --l) {
-            const int out = net.widths[l + 1], in = net.widths[l];
-            od -= out;
-            for (int b = 0; b < nb; ++b) {
-                float *dr = A.dels + (s0 + b) * sd + od;
-                for (int r = tid; r < out; r += nt) dr[r] = dlb(b, h)[r];
-            }
-            if (l == 0) break;
-            const float *W = net.W[l];
-            for (int k = tid; k < in; k += nt) {
-                float g[B];
-#pragma unroll
-                for (int b = 0; b < B; ++b) g[b] = 0.0f;
-#pragma unroll 4
-                for (int r = 0; r < out; ++r) {
-                    const float w = W[(size_t)r * in + k];
-#pragma unroll
-                    for (int b = 0; b < B; ++b) g[b] = fmaf(w, dlb(b, h)[r], g[b]);
-                }
-#pragma unroll
-                for (int b = 0; b < B; ++b) dlb(b, h ^ 1)[k] = zl(b, l - 1)[k] > 0.0f ? g[b] : 0.0f;
-            }
-            __syncthreads();
-            h ^= 1;
-        }
-        __syncthreads();
+    const int64_t sb = (n * N + 255) / 256, my = (n + kGmTile - 1) / kGmTile;
+    if (sb > INT32_MAX || my > 65535) return set_error(NQS_EINVAL, "too many samples");
+    hipLaunchKernelGGL(ffnn_factor_spins_kernel, dim3((unsigned)sb), dim3(256), 0, stream, samples, n, N, sa, acts);
+    auto gemm = [&](const FactorGemmArgs &G) {
+        hipLaunchKernelGGL(ffnn_factor_gemm_kernel, dim3((unsigned)((G.N + kGmTile - 1) / kGmTile), (unsigned)my),
+                           dim3(256), 0, stream, G);
+    };
+    for (int l = 0; l < L; ++l) {
+        const bool last = l + 1 == L;
+        gemm(FactorGemmArgs{acts + oa[l], net.Wt[l], net.b[l], nullptr, last ? dels + od[l] : acts + oa[l + 1], n, sa, 0,
+                            last ? sd : sa, net.widths[l], net.widths[l + 1], last ? 0 : 1});
     }
+    hipLaunchKernelGGL(ffnn_factor_head_kernel, dim3((unsigned)std::min<int64_t>(n, 65536)), dim3(256), 0, stream,
+                       dels + od[L - 1], n, sd, net.widths[L], logpsi);
+    for (int l = L - 1; backward && l >= 1; --l)
+        gemm(FactorGemmArgs{dels + od[l], net.W[l], nullptr, acts + oa[l], dels + od[l - 1], n, sd, sa, sd,
+                            net.widths[l + 1], net.widths[l], 0});
+    NQS_HIP_TRY(hipGetLastError());
+    return NQS_OK;
+}
+
+// O [n][p1 - p0] from the factors: one multiply per value, bound by the writes.  A block writes kExpandSpan
+// consecutive parameters of one sample, so its stores run through memory in order, from the sample's factors in LDS;
+// 16 bytes a store where every layer's rows and O's are multiples of 16 bytes.  4096 samples of the 100-400-200
+// network (1.98 GB): 482 us with the factors, 4.5 TB/s for this kernel (a copy reaches 5.2, read and written);
+// 905 us when a block wrote 4 KB of each of 16 samples, 1762 us with one block per sample for everything.
+struct ExpandArgs {
+    const float *acts, *dels;
+    float *O;                     // [n][p1 - p0]
+    int64_t n, p0, p1, sa, sd;    // sa, sd: row lengths of acts and dels
+    int L;
+    int64_t offW[NQS_MAX_LAYERS + 1];   // first parameter of layer l; offW[L] = P
+    int in[NQS_MAX_LAYERS], out[NQS_MAX_LAYERS];
+    int64_t offA[NQS_MAX_LAYERS], offD[NQS_MAX_LAYERS];
+};
+
+constexpr int kExpandSpan = 16384;
+
+// V consecutive parameters per thread and store (1, or 4 where every row is a multiple of 4 floats)
+template <int V>
+__global__ void __launch_bounds__(256) ffnn_expand_kernel(ExpandArgs E, int spans)
+{
+    extern __shared__ __align__(16) float fac[];   // the sample's deltas [sd], then its layer inputs [sa]
+    const int64_t k = blockIdx.x / spans;
+    const int tid = threadIdx.x;
+    const int64_t b0 = E.p0 + (int64_t)(blockIdx.x - k * spans) * kExpandSpan, b1 = min(E.p1, b0 + kExpandSpan);
+    float *ds = fac, *as = fac + ((E.sd + 3) & ~(int64_t)3);
+    // only the layers that the span meets
+    for (int l = 0; l < E.L; ++l) {
+        if (E.offW[l + 1] <= b0 || E.offW[l] >= b1) continue;
+        for (int i = tid; i < E.out[l]; i += 256) ds[E.offD[l] + i] = E.dels[k * E.sd + E.offD[l] + i];
+        for (int i = tid; i < E.in[l]; i += 256) as[E.offA[l] + i] = E.acts[k * E.sa + E.offA[l] + i];
+    }
+    __syncthreads();
+    float *O = E.O + k * (E.p1 - E.p0) - E.p0;
+    for (int l = 0; l < E.L; ++l) {
+        const int in = E.in[l];
+        const int64_t w0 = E.offW[l], w1 = w0 + (int64_t)E.out[l] * in;
+        const float *d = ds + E.offD[l], *a = as + E.offA[l];
+        // weights: position q = r in + c, advanced by 256 V with (r, c) carried
+        const int64_t s0 = max(b0, w0), s1 = min(b1, w1);
+        if (s0 < s1) {
+            const int64_t q0 = s0 - w0 + tid * V;
+            int r = (int)(q0 / in), c = (int)(q0 - (int64_t)r * in);
+            const int dr = 256 * V / in, dc = 256 * V - dr * in;
+            for (int64_t p = s0 + tid * V; p < s1; p += 256 * V) {
+                const float dv = d[r];
+                if constexpr (V == 4) {
+                    const float4 av = *reinterpret_cast<const float4 *>(a + c);
+                    *reinterpret_cast<float4 *>(O + p) = make_float4(dv * av.x, dv * av.y, dv * av.z, dv * av.w);
+                } else {
+                    O[p] = dv * a[c];
+                }
+                r += dr;
+                c += dc;
+                if (c >= in) {
+                    c -= in;
+                    ++r;
+                }
+            }
+        }
+        for (int64_t p = max(b0, w1) + tid; p < min(b1, E.offW[l + 1]); p += 256) O[p] = d[p - w1];
+    }
+}
+
+static ExpandArgs expand_args(const FfnnDev &net)
+{
+    ExpandArgs E{};
+    E.L = net.n_layers;
+    int64_t off = 0;
+    for (int l = 0; l < E.L; ++l) {
+        E.in[l] = net.widths[l];
+        E.out[l] = net.widths[l + 1];
+        E.offW[l] = off;
+        E.offA[l] = E.sa;
+        E.offD[l] = E.sd;
+        off += (int64_t)E.out[l] * E.in[l] + E.out[l];
+        E.sa += E.in[l];
+        E.sd += E.out[l];
+    }
+    E.offW[E.L] = off;
+    return E;
+}
+
+// columns [p0, p1) of O of the n samples whose factors E holds
+static nqs_status expand_columns(ExpandArgs E, int64_t n, int64_t p0, int64_t p1, float *O, hipStream_t stream)
+{
+    E.n = n;
+    E.p0 = p0;
+    E.p1 = p1;
+    bool vec = (p1 - p0) % 4 == 0 && p0 % 4 == 0 && (uintptr_t)O % 16 == 0;
+    for (int l = 0; l < E.L; ++l) vec = vec && E.in[l] % 4 == 0 && E.out[l] % 4 == 0;
+    const int64_t spans = (p1 - p0 + kExpandSpan - 1) / kExpandSpan, most = INT32_MAX / spans;   // samples per launch
+    const size_t lds = sizeof(float) * (size_t)(((E.sd + 3) & ~(int64_t)3) + E.sa);
+    for (int64_t k0 = 0; k0 < n; k0 += most) {
+        ExpandArgs C = E;
+        C.n = std::min(most, n - k0);
+        C.acts += k0 * E.sa;
+        C.dels += k0 * E.sd;
+        C.O = O + k0 * (p1 - p0);
+        auto launch = [&](auto kernel) {
+            allow_lds(kernel, lds);
+            hipLaunchKernelGGL(kernel, dim3((unsigned)(C.n * spans)), dim3(256), lds, stream, C, (int)spans);
+        };
+        if (vec) launch(ffnn_expand_kernel<4>);
+        else launch(ffnn_expand_kernel<1>);
+    }
+    NQS_HIP_TRY(hipGetLastError());
+    return NQS_OK;
 }
 
 nqs_status ffnn_logpsi_grad(nqs_model *m, const int8_t *samples, int64_t n, float *logpsi, float *O,
@@ -552,20 +726,40 @@ nqs_status ffnn_logpsi_grad(nqs_model *m, const int8_t *samples, int64_t n, floa
     A.P = m->P;
     A.p0 = p0;
     A.p1 = p1;
-    A.acts = nullptr;
-    A.dels = nullptr;
     A.lds_stride = (maxw + 3) & ~3;
     const size_t lds = sizeof(float) * (size_t)A.lds_stride * (1 + net.n_layers + 2);
     if (lds > 160 * 1024) return set_error(NQS_EUNSUPPORTED, "network too wide for the gradient kernel");
     allow_lds(ffnn_grad_kernel, lds);
-    const int blocks = (int)std::min<int64_t>(n, 4096);
-    if (logpsi || O) {
+    // Small calls, and calls under capture (no scratch), take one block per sample; the others form the factors
+    // and expand them, chunk by chunk.  The values are the same bit for bit.  The line: 16-64-32, 512 samples 36 us as one
+    // block per sample (its chains' latency; 126 us at 4096 samples against 43), 36-144-72, 64 samples 68 against 39;
+    // log psi alone 36-144-72, 1024 samples 21 against 28 (five launches), 64-256-128 34 against 29.
+    const double P = (double)m->P, nP = (double)n * P;
+    const bool small = O ? P < 1.2e4 && nP < 2.5e6 : P < 3.0e4 && nP < 3.0e7;
+    if ((logpsi || O) && (small || stream_capturing(stream))) {
         A.samples = samples;
         A.n = n;
         A.logpsi = logpsi;
         A.O = O;
-        hipLaunchKernelGGL(ffnn_grad_kernel, dim3(blocks), dim3(256), lds, stream, A);
+        hipLaunchKernelGGL(ffnn_grad_kernel, dim3((unsigned)std::min<int64_t>(n, 4096)), dim3(256), lds, stream, A);
         NQS_HIP_TRY(hipGetLastError());
+    } else if (logpsi || O) {
+        ExpandArgs E = expand_args(net);
+        const int64_t per = E.sa + E.sd;
+        const int64_t chunk = std::max<int64_t>(1, std::min<int64_t>({n, (int64_t)(kLeaseBytes / sizeof(float)) / per,
+                                                                           (int64_t)4 << 20}));
+        const ScratchLease lease(sizeof(float) * (size_t)(chunk * per), stream);
+        if (!lease.ptr()) return set_error(NQS_ENOMEM, "scratch allocation failed");
+        float *acts = (float *)lease.ptr(), *dels = acts + chunk * E.sa;
+        E.acts = acts;
+        E.dels = dels;
+        for (int64_t k0 = 0; k0 < n; k0 += chunk) {
+            const int64_t kn = std::min(chunk, n - k0);
+            st = factors_from(net, samples + k0 * net.widths[0], kn, acts, dels, logpsi ? logpsi + k0 : nullptr,
+                              O != nullptr, stream);
+            if (st == NQS_OK && O) st = expand_columns(E, kn, p0, p1, O + k0 * (p1 - p0), stream);
+            if (st != NQS_OK) return st;
+        }
     }
     if (vjp_in) {
         // chunks of samples through a workspace O block
@@ -779,80 +973,20 @@ nqs_status ffnn_local_energy(nqs_model *m, const nqs_ham_desc &ham, const int8_t
 // sample) are computed once; each column block of O is then expanded from them
 // (a write-bound pass) instead of rerunning the forward and backward passes.
 
-struct ExpandArgs {
-    const float *acts, *dels;
-    float *O;                     // [n][p1 - p0]
-    int64_t n, p0, p1, sa, sd;    // sa, sd: row lengths of acts and dels
-    int L;
-    int64_t offW[NQS_MAX_LAYERS + 1];   // first parameter of layer l; offW[L] = P
-    int in[NQS_MAX_LAYERS], out[NQS_MAX_LAYERS];
-    int64_t offA[NQS_MAX_LAYERS], offD[NQS_MAX_LAYERS];
-};
-
-constexpr int kExpandRows = 16;
-
-__global__ void __launch_bounds__(256) ffnn_expand_kernel(ExpandArgs E)
-{
-    const int64_t p = E.p0 + blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (p >= E.p1) return;
-    int l = 0;
-    while (l + 1 < E.L && p >= E.offW[l + 1]) ++l;
-    const int64_t q = p - E.offW[l], nw = (int64_t)E.out[l] * E.in[l];
-    int64_t ai, di;
-    if (q < nw) {
-        const int64_t r = q / E.in[l];
-        ai = E.offA[l] + (q - r * E.in[l]);
-        di = E.offD[l] + r;
-    } else {
-        ai = -1;
-        di = E.offD[l] + (q - nw);
-    }
-    const int64_t ldo = E.p1 - E.p0;
-    const int64_t k0 = blockIdx.y * (int64_t)kExpandRows, k1 = min(E.n, k0 + kExpandRows);
-    for (int64_t k = k0; k < k1; ++k) {
-        const float d = E.dels[k * E.sd + di];
-        E.O[k * ldo + (p - E.p0)] = ai >= 0 ? d * E.acts[k * E.sa + ai] : d;
-    }
-}
-
 nqs_status ffnn_factors(nqs_model *m, const int8_t *samples, int64_t n, float *acts, float *dels, hipStream_t stream)
 {
     nqs_status st = ensure_copy(m, NQS_F32, stream);
     if (st != NQS_OK) return st;
     const FfnnDev &net = m->copies[NQS_F32].ffnn;
-    const int L = net.n_layers;
-    int maxw = net.widths[0];
-    for (int l = 1; l <= L; ++l) maxw = std::max(maxw, net.widths[l]);
-    GradArgs A;
-    A.net = net;
-    A.samples = samples;
-    A.n = n;
-    A.logpsi = nullptr;
-    A.O = nullptr;
-    A.P = m->P;
-    A.p0 = 0;
-    A.p1 = m->P;
-    A.acts = acts;
-    A.dels = dels;
-    A.lds_stride = (maxw + 3) & ~3;
-    size_t per = (size_t)((net.widths[0] + 3) & ~3) + 2 * (size_t)A.lds_stride;   // LDS floats per sample
-    for (int l = 1; l <= L; ++l) per += (size_t)((net.widths[l] + 3) & ~3);
-    per *= sizeof(float);
-    const int64_t blocks_cap = (int64_t)device_cus() * 16;
-    auto launch = [&](auto kernel, int B) {
-        allow_lds(kernel, per * B);
-        const int64_t blocks = std::min<int64_t>((n + B - 1) / B, blocks_cap);
-        hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(256), per * B, stream, A);
-    };
-    // samples per block: each weight read serves B samples, while at least two
-    // blocks (eight waves) fit a compute unit's 160 KB of LDS to hide load latency
-    if (per * 8 <= 80 * 1024) launch(ffnn_factor_kernel<8>, 8);
-    else if (per * 4 <= 80 * 1024) launch(ffnn_factor_kernel<4>, 4);
-    else if (per * 2 <= 80 * 1024) launch(ffnn_factor_kernel<2>, 2);
-    else if (per <= 160 * 1024) launch(ffnn_factor_kernel<1>, 1);
-    else return set_error(NQS_EUNSUPPORTED, "network too wide for the gradient kernel");
-    NQS_HIP_TRY(hipGetLastError());
-    return NQS_OK;
+    // networks that the gradient kernel does not take are refused here too
+    size_t per = (size_t)((net.widths[0] + 3) & ~3), maxw = net.widths[0];
+    for (int l = 1; l <= net.n_layers; ++l) {
+        per += (size_t)((net.widths[l] + 3) & ~3);
+        maxw = std::max(maxw, (size_t)net.widths[l]);
+    }
+    if (sizeof(float) * (per + 2 * ((maxw + 3) & ~(size_t)3)) > 160 * 1024)
+        return set_error(NQS_EUNSUPPORTED, "network too wide for the gradient kernel");
+    return factors_from(net, samples, n, acts, dels, nullptr, true, stream);
 }
 
 nqs_status ffnn_sample_gram(nqs_model *m, const int8_t *samples, int64_t n, int64_t chunk, float *T,
@@ -861,28 +995,8 @@ nqs_status ffnn_sample_gram(nqs_model *m, const int8_t *samples, int64_t n, int6
     nqs_status st = ensure_copy(m, NQS_F32, stream);
     if (st != NQS_OK) return st;
     const FfnnDev &net = m->copies[NQS_F32].ffnn;
-    const int L = net.n_layers;
-    int maxw = net.widths[0];
-    for (int l = 1; l <= L; ++l) maxw = std::max(maxw, net.widths[l]);
-    ExpandArgs E;
-    E.L = L;
-    E.n = n;
-    int64_t off = 0, sa = 0, sd = 0;
-    for (int l = 0; l < L; ++l) {
-        E.in[l] = net.widths[l];
-        E.out[l] = net.widths[l + 1];
-        E.offW[l] = off;
-        off += (int64_t)E.out[l] * E.in[l] + E.out[l];
-        E.offA[l] = sa;
-        sa += E.in[l];
-    }
-    E.offW[L] = off;
-    for (int l = 0; l < L; ++l) {   // delta_l sits after the deltas of the layers below it
-        E.offD[l] = sd;
-        sd += E.out[l];
-    }
-    E.sa = sa;
-    E.sd = sd;
+    ExpandArgs E = expand_args(net);
+    const int64_t sa = E.sa, sd = E.sd;
     const int64_t P = m->P;
     const size_t fa = (sizeof(float) * (size_t)n * sa + 255) & ~(size_t)255;
     const size_t fd = (sizeof(float) * (size_t)n * sd + 255) & ~(size_t)255;
@@ -897,16 +1011,11 @@ nqs_status ffnn_sample_gram(nqs_model *m, const int8_t *samples, int64_t n, int6
     st = ffnn_factors(m, samples, n, acts, dels, stream);
     if (st != NQS_OK) return st;
 
-    const int64_t ry = (n + kExpandRows - 1) / kExpandRows;
-    if (ry > 65535) return set_error(NQS_EINVAL, "too many samples for the expansion grid");
+    if ((n + 15) / 16 > 65535) return set_error(NQS_EINVAL, "too many samples for the expansion grid");
     for (int64_t p0 = 0; p0 < P; p0 += chunk) {
         const int64_t p1 = std::min(P, p0 + chunk);
-        E.O = Oc;
-        E.p0 = p0;
-        E.p1 = p1;
-        hipLaunchKernelGGL(ffnn_expand_kernel, dim3((unsigned)((p1 - p0 + 255) / 256), (unsigned)ry), dim3(256), 0,
-                           stream, E);
-        NQS_HIP_TRY(hipGetLastError());
+        st = expand_columns(E, n, p0, p1, Oc, stream);
+        if (st != NQS_OK) return st;
         st = launch_gram_ws(Oc, n, p1 - p0, p0 == 0 ? 1 : 2, T, ws + fa + fd + oc, stream);
         if (st != NQS_OK) return st;
     }
