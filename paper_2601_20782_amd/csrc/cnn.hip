@@ -1314,6 +1314,26 @@ __global__ void __launch_bounds__(kCnnThreads) cnn_grad_kernel(CnnDev net, const
     }
 }
 
+// vjp_out[p] += sum_k g[k] O[k][p] over a chunk of samples (FP64 accumulation per chunk)
+__global__ void vjp_chunk_kernel(const float *__restrict__ O, const float *__restrict__ g, int64_t n, int64_t P,
+                                 float *__restrict__ out, int first)
+{
+    const int64_t p = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+    if (p >= P) return;
+    double acc = first ? 0.0 : (double)out[p];
+    for (int64_t k = 0; k < n; ++k) acc += (double)g[k] * (double)O[k * P + p];
+    out[p] = (float)acc;
+}
+
+static nqs_status launch_vjp_chunk(const float *O, const float *g, int64_t n, int64_t P, float *out, bool first,
+                            hipStream_t stream)
+{
+    hipLaunchKernelGGL(vjp_chunk_kernel, dim3((unsigned)((P + 255) / 256)), dim3(256), 0, stream, O, g, n, P, out,
+                       first ? 1 : 0);
+    NQS_HIP_TRY(hipGetLastError());
+    return NQS_OK;
+}
+
 nqs_status cnn_logpsi_grad(nqs_model *m, const int8_t *samples, int64_t n, float *logpsi, float *O,
                            const float *vjp_in, float *vjp_out, hipStream_t stream)
 {

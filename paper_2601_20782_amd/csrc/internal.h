@@ -271,9 +271,6 @@ nqs_status cnn_local_energy(nqs_model *m, const nqs_ham_desc &ham, const int8_t 
 nqs_status cnn_logpsi(nqs_model *m, const int8_t *samples, int64_t n, float *logpsi, hipStream_t stream);
 nqs_status cnn_logpsi_grad(nqs_model *m, const int8_t *samples, int64_t n, float *logpsi, float *O,
                            const float *vjp_in, float *vjp_out, hipStream_t stream);
-// vjp_out[p] (+)= sum_k g[k] O[k][p] over a block of rows of O (first: overwrite)
-nqs_status launch_vjp_chunk(const float *O, const float *g, int64_t n, int64_t P, float *out, bool first,
-                            hipStream_t stream);
 nqs_status ffnn_sample(nqs_model *m, const nqs_sample_cfg &cfg, int8_t *chain_state, int8_t *samples,
                        float *logpsi, uint64_t *n_accepted, const nqs_trace *trace, hipStream_t stream);
 nqs_status ffnn_local_energy(nqs_model *m, const nqs_ham_desc &ham, const int8_t *samples, int64_t n, int dtype,
@@ -299,9 +296,16 @@ struct FacLayerDesc {
     const float *U, *V;
     int64_t ldu, ldv;
     int du, dv, c;
+    const int8_t *S = nullptr;   // V as spins, when V is NULL (the vector-Jacobian product only)
 };
 size_t fac_workspace_bytes(const FacLayerDesc *lay, int L, int64_t n);
 nqs_status launch_fac_gram(const FacLayerDesc *lay, int L, int64_t n, float *T, void *ws, hipStream_t stream);
+// vjp_out = sum_k g_k O_k in parameter order, from the factors of n samples.  Samples may come in chunks: `add`
+// adds to the sums of the chunks before, vjp_out (NULL except for the last chunk) takes the result; n_first is the
+// first (largest) chunk's n, which sizes the workspace.
+size_t fac_vjp_bytes(const FacLayerDesc *lay, int L, int64_t n_first);
+nqs_status launch_fac_vjp(const FacLayerDesc *lay, int L, int64_t n, int64_t n_first, const float *g, bool add,
+                          float *vjp_out, void *ws, hipStream_t stream);
 void launch_spins_to_f32(const int8_t *s, int64_t count, float *out, hipStream_t stream);
 // factors of an RBM: t = tanh(theta) [n][M]
 nqs_status rbm_tanh_theta(nqs_model *m, const int8_t *samples, int64_t n, float *t, hipStream_t stream);

@@ -15,10 +15,13 @@
 // (masked to the blocks that exist).  Means, v and K are FP64 throughout
 // (products of FP32 factors are exact in FP64); T is rounded to FP32 once.
 //
-// Kernels: fac_mean (tiled FP64, one block per 64 x 64 tile of a layer's mean
-// matrix and range of samples; the ranges summed in order by fac_mean_reduce), fac_v (tiled FP64, per-sample bilinear forms, partials per row
-// tile summed in fixed order), fac_gram (FP64 matrix cores,
-// v_mfma_f64_16x16x4f64, one block per 64 x 64 tile of T's upper triangle).
+// The vector-Jacobian product O^T g is the same kind of sum, sum_k g_k [U_k,1] (x) [V_k,1] per layer, so it comes
+// from the same kernel as the means.
+//
+// Kernels, all on the FP64 matrix cores (v_mfma_f64_16x16x4f64): fac_outer (one block per 64 x 64 tile of a layer's
+// mean matrix and range of samples; the ranges summed in order by fac_mean_reduce or, into parameter order, by
+// fac_vjp_reduce), fac_v (per-sample bilinear forms, partials per row tile summed in fixed order), fac_gram (one
+// block per 64 x 64 tile of T's upper triangle).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -32,7 +35,8 @@ typedef double f64x4 __attribute__((ext_vector_type(4)));
 
 struct FacLayer {
     const float *U;   // [n][ldu], first du columns used
-    const float *V;   // [n][ldv], first dv columns used
+    const float *V;   // [n][ldv], first dv columns used; NULL: the spins S
+    const int8_t *S;
     int64_t ldu, ldv;
     int du, dv;
     int c;            // 1: V is also a block of O by itself
@@ -77,48 +81,120 @@ __device__ inline double fac_aug(const float *F, int64_t ld, int d, int64_t n, i
     return j == d ? 1.0 : (double)F[k * ld + j];
 }
 
-// Sums of [U,1]^T [V,1] over the samples of one split (blockIdx.y), one 64 x 64
-// tile of one layer per block (blockIdx.x), to mpart.
-__global__ void __launch_bounds__(256) fac_mean_kernel(FacArgs A)
+// Sums of g_k [U_k,1] (x) [V_k,1] (g = 1 without `g`) over the samples of one split (blockIdx.y), one 64 x 64 tile
+// of one layer per block (blockIdx.x), to mpart, or added to it (`add`).  The products of two FP32 factors and of
+// g with one are exact in FP64.  Both operands are read along the samples, 32 of them per barrier with the next 32
+// already in registers (the row stride of 80 floats spreads a fragment read over all banks): a block's four waves
+// then wait for the matrix cores, 2048 cycles per 32 samples, and not for memory.  Mean matrices of the 100-400-200
+// network, 6000 samples: 118 us on the vector units, 90 us (1.45 GFLOP; 64-bit vector and matrix rates are alike,
+// the vector form waited for its LDS reads).
+constexpr int kOutLd = 80;
+__global__ void __launch_bounds__(256) fac_outer_kernel(FacArgs A, const float *__restrict__ g, int add)
 {
-    __shared__ double Us[kFK][kFT], Vs[kFK][kFT];
+    __shared__ float Us[2][kFK * kOutLd], Vs[2][kFK * kOutLd], gs[2][kFK];
     const int l = fac_layer_of(A, blockIdx.x, false);
     const FacLayer &y = A.lay[l];
     const int64_t t = blockIdx.x - y.mt0;
     const int ctiles = (y.dv + 1 + kFT - 1) / kFT;
     const int r0 = (int)(t / ctiles) * kFT, c0 = (int)(t % ctiles) * kFT;
-    const int tid = threadIdx.x, ty = tid >> 4, tx = tid & 15;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, la = lane & 15, lk = lane >> 4;
+    const int wm = (wave >> 1) * 32, wn = (wave & 1) * 32;
     const int64_t kb = blockIdx.y * A.n / A.splits, ke = (blockIdx.y + 1) * A.n / A.splits;
-    double acc[4][4] = {};
+    const int j = lane, s0 = wave;   // staging: column j of the samples s0, s0 + 4, ...
+    float uv[kFK / 4], vv[kFK / 4], gv = 0.0f;
+    auto load = [&](int64_t k0) {
+#pragma unroll
+        for (int i = 0; i < kFK / 4; ++i) {
+            const int64_t k = k0 + s0 + 4 * i;
+            const int r = r0 + j, c = c0 + j;
+            uv[i] = k >= ke || r > y.du ? 0.0f : r == y.du ? 1.0f : y.U[k * y.ldu + r];
+            vv[i] = k >= ke || c > y.dv ? 0.0f : c == y.dv ? 1.0f : y.V ? y.V[k * y.ldv + c] : (float)y.S[k * y.ldv + c];
+        }
+        if (tid < kFK) gv = k0 + tid >= ke ? 0.0f : g ? g[k0 + tid] : 1.0f;
+    };
+    auto store = [&](int buf) {
+#pragma unroll
+        for (int i = 0; i < kFK / 4; ++i) {
+            Us[buf][(s0 + 4 * i) * kOutLd + j] = uv[i];
+            Vs[buf][(s0 + 4 * i) * kOutLd + j] = vv[i];
+        }
+        if (tid < kFK) gs[buf][tid] = gv;
+    };
+    f64x4 acc[2][2];
+#pragma unroll
+    for (int a = 0; a < 2; ++a)
+#pragma unroll
+        for (int b = 0; b < 2; ++b) acc[a][b] = f64x4{0.0, 0.0, 0.0, 0.0};
+    load(kb);
+    store(0);
+    int buf = 0;
     for (int64_t k0 = kb; k0 < ke; k0 += kFK) {
-        for (int e = tid; e < kFK * kFT; e += 256) {
-            const int kk = e / kFT, j = e % kFT;
-            const int64_t k = k0 + kk < ke ? k0 + kk : A.n;   // A.n reads as zero
-            Us[kk][j] = fac_aug(y.U, y.ldu, y.du, A.n, k, r0 + j);
-            Vs[kk][j] = fac_aug(y.V, y.ldv, y.dv, A.n, k, c0 + j);
-        }
         __syncthreads();
-        for (int kk = 0; kk < kFK; ++kk) {
-            double u[4], v[4];
+        const bool more = k0 + kFK < ke;
+        if (more) load(k0 + kFK);
 #pragma unroll
-            for (int i = 0; i < 4; ++i) u[i] = Us[kk][ty * 4 + i];
+        for (int s = 0; s < kFK / 4; ++s) {
+            const int kk = 4 * s + lk;
+            const double w = (double)gs[buf][kk];
+            double u[2], v[2];
 #pragma unroll
-            for (int i = 0; i < 4; ++i) v[i] = Vs[kk][tx * 4 + i];
+            for (int q = 0; q < 2; ++q) {
+                u[q] = w * (double)Us[buf][kk * kOutLd + wm + 16 * q + la];
+                v[q] = (double)Vs[buf][kk * kOutLd + wn + 16 * q + la];
+            }
 #pragma unroll
-            for (int i = 0; i < 4; ++i)
+            for (int a = 0; a < 2; ++a)
 #pragma unroll
-                for (int j = 0; j < 4; ++j) acc[i][j] = fma(u[i], v[j], acc[i][j]);
+                for (int b = 0; b < 2; ++b)
+                    acc[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(u[a], v[b], acc[a][b], 0, 0, 0);
         }
-        __syncthreads();
+        if (more) store(buf ^ 1);
+        buf ^= 1;
     }
+    // D[i][j] of a 16 x 16 FP64 block: j = lane % 16, i = lane / 16 + 4 * register
     double *out = A.mpart + (int64_t)blockIdx.y * A.mtot + y.moff;
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int a = 0; a < 2; ++a)
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int r = r0 + ty * 4 + i, c = c0 + tx * 4 + j;
-            if (r <= y.du && c <= y.dv) out[(int64_t)r * (y.dv + 1) + c] = acc[i][j];
-        }
+        for (int b = 0; b < 2; ++b)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int r = r0 + wm + 16 * a + lk + 4 * q, c = c0 + wn + 16 * b + la;
+                if (r > y.du || c > y.dv) continue;
+                double *o = out + (int64_t)r * (y.dv + 1) + c;
+                *o = add ? *o + acc[a][b][q] : acc[a][b][q];
+            }
+}
+
+// Entry e of the layers' sums, the splits added in order (eight loads in flight).
+__device__ __forceinline__ double fac_split_sum(const FacArgs &A, int64_t e)
+{
+    double s = 0.0;
+#pragma unroll 8
+    for (int sp = 0; sp < A.splits; ++sp) s += A.mpart[(int64_t)sp * A.mtot + e];
+    return s;
+}
+
+// The sums of fac_outer_kernel as the gradient in parameter order: with c = 1 (RBM) [row du, column dv, inner
+// block], else [inner block, column dv] of each layer in turn.
+__global__ void __launch_bounds__(256) fac_vjp_reduce_kernel(FacArgs A, float *__restrict__ out)
+{
+    const int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+    if (e >= A.mtot) return;
+    int l = 0;
+    int64_t off = 0;
+    while (l + 1 < A.L && e >= A.lay[l + 1].moff) {
+        off += (int64_t)A.lay[l].du * (A.lay[l].dv + 1) + (A.lay[l].c ? A.lay[l].dv : 0);
+        ++l;
+    }
+    const FacLayer &y = A.lay[l];
+    const int64_t q = e - y.moff, nw = (int64_t)y.du * y.dv;
+    const int r = (int)(q / (y.dv + 1)), c = (int)(q - (int64_t)r * (y.dv + 1));
+    int64_t p;
+    if (r < y.du) p = c < y.dv ? (y.c ? y.dv + y.du : 0) + (int64_t)r * y.dv + c : (y.c ? y.dv : nw) + r;
+    else if (c < y.dv && y.c) p = c;
+    else return;
+    out[off + p] = (float)fac_split_sum(A, e);
 }
 
 // M_l = (1/n) (sum of the splits in order), masked: the (du, dv) corner is 0 and
@@ -135,9 +211,7 @@ __global__ void __launch_bounds__(256) fac_mean_reduce_kernel(FacArgs A)
         const FacLayer &y = A.lay[l];
         const int64_t q = e - y.moff;
         const int r = (int)(q / (y.dv + 1)), c = (int)(q - (int64_t)r * (y.dv + 1));
-        double s = 0.0;
-        for (int sp = 0; sp < A.splits; ++sp) s += A.mpart[(int64_t)sp * A.mtot + e];
-        m = s / (double)A.n;
+        m = fac_split_sum(A, e) / (double)A.n;
         if (r == y.du && (c == y.dv || !y.c)) m = 0.0;
         A.Mall[e] = m;
     }
@@ -346,8 +420,9 @@ static FacPlan fac_plan(const FacLayerDesc *lay, int L, int64_t n)
         p.mtot += (int64_t)(lay[l].du + 1) * (lay[l].dv + 1);
         p.vs += rt;
     }
-    // enough sample splits for about eight blocks per compute unit, at least 64 samples each
-    const int64_t want = ((int64_t)device_cus() * 8 + p.mt - 1) / p.mt;
+    // sample splits for about two blocks per compute unit, at least 64 samples each (more splits only cost their sum:
+    // 10 x 10 RBM, 4096 samples: 64 splits 27 us and 19 us for their sum, 32 splits 18 us and 6 us)
+    const int64_t want = ((int64_t)device_cus() * 2 + p.mt - 1) / p.mt;
     p.splits = (int)std::max<int64_t>(1, std::min<int64_t>({want, n / 64, 1024}));
     p.m2blocks = (int)((p.mtot + 255) / 256);
     return p;
@@ -363,16 +438,68 @@ size_t fac_workspace_bytes(const FacLayerDesc *lay, int L, int64_t n)
            round256(sizeof(double) * (size_t)n) + 256;
 }
 
+// the layers and their places in the mean matrices and slots
+static FacArgs fac_args(const FacLayerDesc *lay, int L, int64_t n, const FacPlan &p, double *Mall)
+{
+    FacArgs A{};
+    A.L = L;
+    A.n = n;
+    A.mtot = p.mtot;
+    A.splits = p.splits;
+    A.m2blocks = p.m2blocks;
+    A.slots = p.vs;
+    A.Mall = Mall;
+    int64_t mt = 0, vs = 0, moff = 0;
+    for (int l = 0; l < L; ++l) {
+        FacLayer &y = A.lay[l];
+        y.U = lay[l].U;
+        y.V = lay[l].V;
+        y.S = lay[l].S;
+        y.ldu = lay[l].ldu;
+        y.ldv = lay[l].ldv;
+        y.du = lay[l].du;
+        y.dv = lay[l].dv;
+        y.c = lay[l].c;
+        y.moff = moff;
+        y.M = Mall + moff;
+        moff += (int64_t)(y.du + 1) * (y.dv + 1);
+        y.mt0 = mt;
+        mt += (int64_t)((y.du + 1 + kFT - 1) / kFT) * ((y.dv + 1 + kFT - 1) / kFT);
+        y.vs0 = vs;
+        vs += (y.du + 1 + kFT - 1) / kFT;
+    }
+    return A;
+}
+
+size_t fac_vjp_bytes(const FacLayerDesc *lay, int L, int64_t n)
+{
+    const FacPlan p = fac_plan(lay, L, n);
+    return round256(sizeof(double) * (size_t)p.splits * p.mtot);
+}
+
+nqs_status launch_fac_vjp(const FacLayerDesc *lay, int L, int64_t n, int64_t n_first, const float *g, bool add,
+                          float *vjp_out, void *wsp, hipStream_t stream)
+{
+    if (L < 1 || L > NQS_MAX_LAYERS + 1) return set_error(NQS_EINVAL, "bad factor layer count");
+    const FacPlan p = fac_plan(lay, L, n_first);   // every chunk fills the first one's splits
+    FacArgs A = fac_args(lay, L, n, p, nullptr);
+    A.mpart = (double *)wsp;
+    if (p.mt > INT32_MAX || (p.mtot + 255) / 256 > INT32_MAX) return set_error(NQS_EINVAL, "network too large");
+    hipLaunchKernelGGL(fac_outer_kernel, dim3((unsigned)p.mt, (unsigned)p.splits), dim3(256), 0, stream, A, g, add ? 1 : 0);
+    if (vjp_out)
+        hipLaunchKernelGGL(fac_vjp_reduce_kernel, dim3((unsigned)((p.mtot + 255) / 256)), dim3(256), 0, stream, A,
+                           vjp_out);
+    NQS_HIP_TRY(hipGetLastError());
+    return NQS_OK;
+}
+
 nqs_status launch_fac_gram(const FacLayerDesc *lay, int L, int64_t n, float *T, void *wsp, hipStream_t stream)
 {
     if (L < 1 || L > NQS_MAX_LAYERS + 1) return set_error(NQS_EINVAL, "bad factor layer count");
     const FacPlan p = fac_plan(lay, L, n);
-    FacArgs A;
-    A.L = L;
-    A.n = n;
+    FacArgs A = fac_args(lay, L, n, p, (double *)wsp);
     A.T = T;
     char *ws = (char *)wsp;
-    A.Mall = (double *)ws;
     ws += round256(sizeof(double) * (size_t)p.mtot);
     A.mpart = (double *)ws;
     ws += round256(sizeof(double) * (size_t)p.splits * p.mtot);
@@ -383,37 +510,16 @@ nqs_status launch_fac_gram(const FacLayerDesc *lay, int L, int64_t n, float *T, 
     A.v = (double *)ws;
     ws += round256(sizeof(double) * (size_t)n);
     A.m2 = (double *)ws;
-    A.mtot = p.mtot;
-    A.splits = p.splits;
-    A.m2blocks = p.m2blocks;
-    A.slots = p.vs;
-    int64_t mt = 0, vs = 0, moff = 0;
-    for (int l = 0; l < L; ++l) {
-        FacLayer &y = A.lay[l];
-        y.U = lay[l].U;
-        y.V = lay[l].V;
-        y.ldu = lay[l].ldu;
-        y.ldv = lay[l].ldv;
-        y.du = lay[l].du;
-        y.dv = lay[l].dv;
-        y.c = lay[l].c;
-        y.moff = moff;
-        y.M = A.Mall + moff;
-        moff += (int64_t)(y.du + 1) * (y.dv + 1);
-        y.mt0 = mt;
-        mt += (int64_t)((y.du + 1 + kFT - 1) / kFT) * ((y.dv + 1 + kFT - 1) / kFT);
-        y.vs0 = vs;
-        vs += (y.du + 1 + kFT - 1) / kFT;
-    }
     A.nt = (n + kFT - 1) / kFT;
     const int64_t tiles = A.nt * (A.nt + 1) / 2;
     const int64_t ktiles = (n + kFT - 1) / kFT;
-    if (tiles > INT32_MAX || mt > INT32_MAX || ktiles > INT32_MAX || vs > 65535 || p.m2blocks > INT32_MAX / 2)
+    if (tiles > INT32_MAX || p.mt > INT32_MAX || ktiles > INT32_MAX || p.vs > 65535 || p.m2blocks > INT32_MAX / 2)
         return set_error(NQS_EINVAL, "sample-space Gram matrix too large");
 
-    hipLaunchKernelGGL(fac_mean_kernel, dim3((unsigned)mt, (unsigned)p.splits), dim3(256), 0, stream, A);
+    hipLaunchKernelGGL(fac_outer_kernel, dim3((unsigned)p.mt, (unsigned)p.splits), dim3(256), 0, stream, A,
+                       (const float *)nullptr, 0);
     hipLaunchKernelGGL(fac_mean_reduce_kernel, dim3((unsigned)p.m2blocks), dim3(256), 0, stream, A);
-    hipLaunchKernelGGL(fac_v_kernel, dim3((unsigned)ktiles, (unsigned)vs), dim3(256), 0, stream, A);
+    hipLaunchKernelGGL(fac_v_kernel, dim3((unsigned)ktiles, (unsigned)p.vs), dim3(256), 0, stream, A);
     hipLaunchKernelGGL(fac_vsum_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, stream, A);
     hipLaunchKernelGGL(fac_gram_kernel, dim3((unsigned)tiles), dim3(256), 0, stream, A);
     NQS_HIP_TRY(hipGetLastError());
