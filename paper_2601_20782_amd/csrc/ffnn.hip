@@ -452,13 +452,16 @@ __global__ void __launch_bounds__(256) ffnn_factor_gemm_kernel(FactorGemmArgs A)
     const int xk = tid & 31, xr = tid >> 5, bc = tid & 63, br = tid >> 6;
     float xv[8], bv[8];
     auto load = [&](int k0) {
+        // every load is made, from a valid place (a branch around a load waits for all loads in flight); rows and
+        // columns past the last feed outputs that are not stored
         const int k = k0 + xk;
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
-            const int64_t row = m0 + xr + 8 * i;
-            xv[i] = row < A.n && k < A.K ? A.X[row * A.ldx + k] : 0.0f;
-            const int kb = k0 + br + 4 * i, col = n0 + bc;
-            bv[i] = kb < A.K && col < A.N ? A.B[(size_t)kb * A.N + col] : 0.0f;
+            const float x = A.X[min(m0 + xr + 8 * i, A.n - 1) * A.ldx + min(k, A.K - 1)];
+            const int kb = k0 + br + 4 * i;
+            const float b = A.B[(size_t)min(kb, A.K - 1) * A.N + min(n0 + bc, A.N - 1)];
+            xv[i] = k < A.K ? x : 0.0f;
+            bv[i] = kb < A.K ? b : 0.0f;
         }
     };
     auto store = [&](int buf) {

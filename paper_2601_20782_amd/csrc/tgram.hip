@@ -102,13 +102,15 @@ __global__ void __launch_bounds__(256) fac_outer_kernel(FacArgs A, const float *
     const int64_t kb = blockIdx.y * A.n / A.splits, ke = (blockIdx.y + 1) * A.n / A.splits;
     const int j = lane, s0 = wave;   // staging: column j of the samples s0, s0 + 4, ...
     float uv[kFK / 4], vv[kFK / 4], gv = 0.0f;
+    // every load is made, from a valid place; columns past the last feed sums that are not stored
+    const int r = r0 + j, c = c0 + j, rc = min(r, y.du - 1), cc = min(c, y.dv - 1);
     auto load = [&](int64_t k0) {
 #pragma unroll
         for (int i = 0; i < kFK / 4; ++i) {
-            const int64_t k = k0 + s0 + 4 * i;
-            const int r = r0 + j, c = c0 + j;
-            uv[i] = k >= ke || r > y.du ? 0.0f : r == y.du ? 1.0f : y.U[k * y.ldu + r];
-            vv[i] = k >= ke || c > y.dv ? 0.0f : c == y.dv ? 1.0f : y.V ? y.V[k * y.ldv + c] : (float)y.S[k * y.ldv + c];
+            const int64_t k = k0 + s0 + 4 * i, kc = min(k, A.n - 1);
+            const float u = y.U[kc * y.ldu + rc], v = y.V ? y.V[kc * y.ldv + cc] : (float)y.S[kc * y.ldv + cc];
+            uv[i] = k >= ke ? 0.0f : r == y.du ? 1.0f : u;
+            vv[i] = k >= ke ? 0.0f : c == y.dv ? 1.0f : v;
         }
         if (tid < kFK) gv = k0 + tid >= ke ? 0.0f : g ? g[k0 + tid] : 1.0f;
     };
@@ -224,49 +226,85 @@ __global__ void __launch_bounds__(256) fac_mean_reduce_kernel(FacArgs A)
     if (threadIdx.x == 0) A.m2part[blockIdx.x] = red[0];
 }
 
-// vpart[slot][k] = sum over the slot's 64 rows r of [U_k,1]_r (M [V_k,1])_r
+// vpart[slot][k] = sum over the slot's 64 rows r of [U_k,1]_r (M [V_k,1])_r: a 64 samples x 64 rows tile of
+// [V,1] M^T on the FP64 matrix cores, then the products with [U,1] summed over the rows.  32 columns per barrier,
+// the next ones in registers meanwhile; row strides of 36 words (of either size) spread a fragment read over the
+// banks.  100-400-200, 6000 samples: 157 us on the vector units (eight LDS reads per 16 multiply-adds), 74 us.
+constexpr int kVLd = 36;
 __global__ void __launch_bounds__(256) fac_v_kernel(FacArgs A)
 {
-    __shared__ double Vs[kFK][kFT + 1], Ms[kFK][kFT + 1];
+    __shared__ float Vs[kFT * kVLd];
+    __shared__ double Ms[kFT * kVLd];
+    __shared__ double part[2][kFT];
     const int l = fac_layer_of(A, blockIdx.y, true);
     const FacLayer &y = A.lay[l];
     const int r0 = (int)(blockIdx.y - y.vs0) * kFT;
     const int64_t k0 = (int64_t)blockIdx.x * kFT;
-    const int tid = threadIdx.x, ty = tid >> 4, tx = tid & 15;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, la = lane & 15, lk = lane >> 4;
+    const int wm = (wave >> 1) * 32, wn = (wave & 1) * 32;
     const int ldm = y.dv + 1;
-    double acc[4][4] = {};   // [sample ty*4+i][row tx*4+j]
+    const int sc = tid & 31, sr = tid >> 5;   // staging: column sc of the rows sr, sr + 8, ...
+    float vv[8];
+    double mv[8];
+    auto load = [&](int c0) {
+        const int c = c0 + sc;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            const int64_t k = k0 + sr + 8 * i;
+            const int r = r0 + sr + 8 * i;
+            const float v = y.V[min(k, A.n - 1) * y.ldv + min(c, y.dv - 1)];
+            const double m = y.M[(int64_t)min(r, y.du) * ldm + min(c, y.dv)];
+            vv[i] = c > y.dv ? 0.0f : c == y.dv ? 1.0f : v;
+            mv[i] = c > y.dv ? 0.0 : m;
+        }
+    };
+    f64x4 acc[2][2];   // [sample block][row block]
+#pragma unroll
+    for (int a = 0; a < 2; ++a)
+#pragma unroll
+        for (int b = 0; b < 2; ++b) acc[a][b] = f64x4{0.0, 0.0, 0.0, 0.0};
+    load(0);
     for (int c0 = 0; c0 <= y.dv; c0 += kFK) {
-        for (int e = tid; e < kFK * kFT; e += 256) {
-            const int kk = e % kFK, j = e / kFK;   // consecutive threads along the contraction
-            Vs[kk][j] = fac_aug(y.V, y.ldv, y.dv, A.n, k0 + j, c0 + kk);
-            const int r = r0 + j, c = c0 + kk;
-            Ms[kk][j] = (r <= y.du && c <= y.dv) ? y.M[(int64_t)r * ldm + c] : 0.0;
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            Vs[(sr + 8 * i) * kVLd + sc] = vv[i];
+            Ms[(sr + 8 * i) * kVLd + sc] = mv[i];
         }
         __syncthreads();
-        for (int kk = 0; kk < kFK; ++kk) {
-            double a[4], b[4];
+        if (c0 + kFK <= y.dv) load(c0 + kFK);
 #pragma unroll
-            for (int i = 0; i < 4; ++i) a[i] = Vs[kk][ty * 4 + i];
+        for (int s = 0; s < kFK / 4; ++s) {
+            double v[2], m[2];
 #pragma unroll
-            for (int i = 0; i < 4; ++i) b[i] = Ms[kk][tx * 4 + i];
+            for (int q = 0; q < 2; ++q) {
+                v[q] = (double)Vs[(wm + 16 * q + la) * kVLd + 4 * s + lk];
+                m[q] = Ms[(wn + 16 * q + la) * kVLd + 4 * s + lk];
+            }
 #pragma unroll
-            for (int i = 0; i < 4; ++i)
+            for (int a = 0; a < 2; ++a)
 #pragma unroll
-                for (int j = 0; j < 4; ++j) acc[i][j] = fma(a[i], b[j], acc[i][j]);
+                for (int b = 0; b < 2; ++b)
+                    acc[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(v[a], m[b], acc[a][b], 0, 0, 0);
         }
-        __syncthreads();
     }
+    // D[i][j]: j = lane % 16 (row), i = lane / 16 + 4 * register (sample); the 16 lanes of a sample in a fixed
+    // order, then the two waves that share its samples
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int64_t k = k0 + ty * 4 + i;
-        double s = 0.0;
+    for (int a = 0; a < 2; ++a)
 #pragma unroll
-        for (int j = 0; j < 4; ++j) s = fma(fac_aug(y.U, y.ldu, y.du, A.n, k, r0 + tx * 4 + j), acc[i][j], s);
-        // the 16 lanes of one sample row are consecutive: fixed-order butterfly
+        for (int q = 0; q < 4; ++q) {
+            const int i = wm + 16 * a + lk + 4 * q;
+            double s = 0.0;
 #pragma unroll
-        for (int o = 8; o >= 1; o >>= 1) s += __shfl_xor(s, o, 16);
-        if (tx == 0 && k < A.n) A.vpart[(int64_t)blockIdx.y * A.n + k] = s;
-    }
+            for (int b = 0; b < 2; ++b)
+                s = fma(fac_aug(y.U, y.ldu, y.du, A.n, k0 + i, r0 + wn + 16 * b + la), acc[a][b][q], s);
+#pragma unroll
+            for (int o = 8; o >= 1; o >>= 1) s += __shfl_xor(s, o, 16);
+            if (la == 0) part[wave & 1][i] = s;
+        }
+    __syncthreads();
+    if (tid < kFT && k0 + tid < A.n) A.vpart[(int64_t)blockIdx.y * A.n + k0 + tid] = part[0][tid] + part[1][tid];
 }
 
 // v[k] = sum of the slots in order; block 0 also sums |mu|^2 from the reduction blocks
@@ -304,48 +342,70 @@ __device__ inline void fac_tile(int64_t t, int64_t nt, int64_t &bi, int64_t &bj)
     bj = r + (t - start(r));
 }
 
-constexpr int kGK16 = 16;            // contraction step of the matrix-core kernel
-constexpr int kGLd16 = kGK16 + 1;    // LDS row stride (floats)
+constexpr int kGThreads = 512;
+constexpr int kGStep = 32;   // contraction steps per barrier of the matrix-core kernel
+constexpr int kGLd = 36;     // LDS row stride (floats): a fragment read covers all banks once
 
-// acc[a][b] (16 x 16 blocks of the wave's 32 x 32 quadrant) += F_I F_J^T over the first d columns
-__device__ inline void fac_gram_accumulate(const float *__restrict__ F, int64_t ld, int d, int64_t n, int64_t I0,
-                                           int64_t J0, float *As, float *Bs, f64x4 (&acc)[2][2])
+// acc[b] (two 16 x 16 blocks, the wave's 16 x 32 part of the tile) += F_I F_J^T over the first d columns.  The next 32
+// columns are loaded into registers during the products of the current ones and stored into the other LDS buffer,
+// one barrier per step: 1024 cycles of products a wave against one memory latency.
+__device__ __forceinline__ void fac_gram_accumulate(const float *__restrict__ F, int64_t ld, int d, int64_t n,
+                                                    int64_t I0, int64_t J0, float *As, float *Bs, f64x4 (&acc)[2])
 {
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int wm = (wave >> 1) * 32, wn = (wave & 1) * 32;
-    const int row = tid >> 2, k4 = (tid & 3) * 4;   // staging: 64 rows x 16 columns, 4 per thread
+    const int wm = (wave >> 1) * 16, wn = (wave & 1) * 32;
+    const int sc = tid & 31, sr = tid >> 5;   // staging: column sc of the rows sr, sr + 16, ...
     const int li = lane & 15, lk = lane >> 4;
-    for (int k0 = 0; k0 < d; k0 += kGK16) {
-        const int64_t gi = I0 + row, gj = J0 + row;
+    float av[4], bv[4];
+    auto load = [&](int k0) {
+        // every load is made, from a valid place (a branch around a load waits for all loads in flight); rows past
+        // the last feed outputs that are not stored
+        const int k = k0 + sc, kc = min(k, d - 1);
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const int k = k0 + k4 + e;
-            As[row * kGLd16 + k4 + e] = (gi < n && k < d) ? F[gi * ld + k] : 0.0f;
-            Bs[row * kGLd16 + k4 + e] = (gj < n && k < d) ? F[gj * ld + k] : 0.0f;
+        for (int i = 0; i < 4; ++i) {
+            const int64_t gi = min(I0 + sr + 16 * i, n - 1), gj = min(J0 + sr + 16 * i, n - 1);
+            const float a = F[gi * ld + kc], b = F[gj * ld + kc];
+            av[i] = k < d ? a : 0.0f;
+            bv[i] = k < d ? b : 0.0f;
         }
-        __syncthreads();
+    };
+    auto store = [&](int buf) {
 #pragma unroll
-        for (int s = 0; s < kGK16 / 4; ++s) {
+        for (int i = 0; i < 4; ++i) {
+            As[(buf * kFT + sr + 16 * i) * kGLd + sc] = av[i];
+            Bs[(buf * kFT + sr + 16 * i) * kGLd + sc] = bv[i];
+        }
+    };
+    load(0);
+    __syncthreads();   // the previous contraction's last reads
+    store(0);
+    int buf = 0;
+    for (int k0 = 0; k0 < d; k0 += kGStep) {
+        __syncthreads();
+        const bool more = k0 + kGStep < d;
+        if (more) load(k0 + kGStep);
+        const float *Ab = As + buf * kFT * kGLd, *Bb = Bs + buf * kFT * kGLd;
+#pragma unroll
+        for (int s = 0; s < kGStep / 4; ++s) {
             const int kk = s * 4 + lk;
-            double av[2], bv[2];
+            const double a = (double)Ab[(wm + li) * kGLd + kk];
 #pragma unroll
-            for (int q = 0; q < 2; ++q) {
-                av[q] = (double)As[(wm + 16 * q + li) * kGLd16 + kk];
-                bv[q] = (double)Bs[(wn + 16 * q + li) * kGLd16 + kk];
-            }
-#pragma unroll
-            for (int a = 0; a < 2; ++a)
-#pragma unroll
-                for (int b = 0; b < 2; ++b)
-                    acc[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[a], bv[b], acc[a][b], 0, 0, 0);
+            for (int j = 0; j < 2; ++j)
+                acc[j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, (double)Bb[(wn + 16 * j + li) * kGLd + kk], acc[j], 0,
+                                                              0, 0);
         }
-        __syncthreads();
+        if (more) store(buf ^ 1);
+        buf ^= 1;
     }
 }
 
-__global__ void __launch_bounds__(256) fac_gram_kernel(FacArgs A)
+// Bound by the FP64 matrix cores (busy in 67 % of the cycles).  Eight waves of 16 x 32 hold K and two products in 48
+// registers each, so that two blocks (four waves per SIMD) share a CU.  T of 6000 samples of the 100-400-200 network:
+// 1328 us with four waves of 32 x 32 and loads between two barriers of 16 columns, 1288 with the loads ahead at one
+// wave per SIMD, 946 at two, 923-938 (43 TFLOP/s on the computed tiles) now; 10 x 10 RBM, 4096 samples 202 -> 158 us.
+__global__ void __launch_bounds__(kGThreads, 4) fac_gram_kernel(FacArgs A)
 {
-    __shared__ float As[kFT * kGLd16], Bs[kFT * kGLd16];
+    __shared__ float As[2 * kFT * kGLd], Bs[2 * kFT * kGLd];
     // consecutive tiles (which share their row panel) on one XCD
     const int64_t tiles = A.nt * (A.nt + 1) / 2;
     const int64_t x = blockIdx.x, g = gridDim.x;
@@ -356,45 +416,37 @@ __global__ void __launch_bounds__(256) fac_gram_kernel(FacArgs A)
     fac_tile(t, A.nt, bi, bj);
     const int64_t I0 = bi * kFT, J0 = bj * kFT;
 
-    f64x4 K[2][2], gu[2][2], gv[2][2];
+    f64x4 K[2], gu[2], gv[2];
 #pragma unroll
-    for (int a = 0; a < 2; ++a)
-#pragma unroll
-        for (int b = 0; b < 2; ++b) K[a][b] = f64x4{0.0, 0.0, 0.0, 0.0};
+    for (int b = 0; b < 2; ++b) K[b] = f64x4{0.0, 0.0, 0.0, 0.0};
     for (int l = 0; l < A.L; ++l) {
         const FacLayer &y = A.lay[l];
 #pragma unroll
-        for (int a = 0; a < 2; ++a)
-#pragma unroll
-            for (int b = 0; b < 2; ++b) gu[a][b] = gv[a][b] = f64x4{0.0, 0.0, 0.0, 0.0};
+        for (int b = 0; b < 2; ++b) gu[b] = gv[b] = f64x4{0.0, 0.0, 0.0, 0.0};
         fac_gram_accumulate(y.U, y.ldu, y.du, A.n, I0, J0, As, Bs, gu);
         fac_gram_accumulate(y.V, y.ldv, y.dv, A.n, I0, J0, As, Bs, gv);
         const double c = (double)y.c;
 #pragma unroll
-        for (int a = 0; a < 2; ++a)
+        for (int b = 0; b < 2; ++b)
 #pragma unroll
-            for (int b = 0; b < 2; ++b)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) K[a][b][r] += fma(gu[a][b][r] + c, gv[a][b][r] + 1.0, -c);
+            for (int r = 0; r < 4; ++r) K[b][r] += fma(gu[b][r] + c, gv[b][r] + 1.0, -c);
     }
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int wm = (wave >> 1) * 32, wn = (wave & 1) * 32;
+    const int wm = (wave >> 1) * 16, wn = (wave & 1) * 32;
     const double inv = 1.0 / (double)A.n, m2 = A.m2[0];
     // D[i][j] of a 16 x 16 FP64 block: j = lane % 16, i = lane / 16 + 4 * register
 #pragma unroll
-    for (int a = 0; a < 2; ++a)
+    for (int b = 0; b < 2; ++b)
 #pragma unroll
-        for (int b = 0; b < 2; ++b)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int64_t gi = I0 + wm + 16 * a + (lane >> 4) + 4 * r;
-                const int64_t gj = J0 + wn + 16 * b + (lane & 15);
-                if (gi >= A.n || gj >= A.n || (bi == bj && gi > gj)) continue;
-                const float tv = (float)((K[a][b][r] - A.v[gi] - A.v[gj] + m2) * inv);
-                A.T[gi * A.n + gj] = tv;
-                if (gi != gj) A.T[gj * A.n + gi] = tv;
-            }
+        for (int r = 0; r < 4; ++r) {
+            const int64_t gi = I0 + wm + (lane >> 4) + 4 * r;
+            const int64_t gj = J0 + wn + 16 * b + (lane & 15);
+            if (gi >= A.n || gj >= A.n || (bi == bj && gi > gj)) continue;
+            const float tv = (float)((K[b][r] - A.v[gi] - A.v[gj] + m2) * inv);
+            A.T[gi * A.n + gj] = tv;
+            if (gi != gj) A.T[gj * A.n + gi] = tv;
+        }
 }
 
 __global__ void spins_to_f32_kernel(const int8_t *__restrict__ s, int64_t count, float *__restrict__ out)
@@ -521,7 +573,7 @@ nqs_status launch_fac_gram(const FacLayerDesc *lay, int L, int64_t n, float *T, 
     hipLaunchKernelGGL(fac_mean_reduce_kernel, dim3((unsigned)p.m2blocks), dim3(256), 0, stream, A);
     hipLaunchKernelGGL(fac_v_kernel, dim3((unsigned)ktiles, (unsigned)p.vs), dim3(256), 0, stream, A);
     hipLaunchKernelGGL(fac_vsum_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, stream, A);
-    hipLaunchKernelGGL(fac_gram_kernel, dim3((unsigned)tiles), dim3(256), 0, stream, A);
+    hipLaunchKernelGGL(fac_gram_kernel, dim3((unsigned)tiles), dim3(kGThreads), 0, stream, A);
     NQS_HIP_TRY(hipGetLastError());
     return NQS_OK;
 }
