@@ -165,6 +165,10 @@ private:
     hipStream_t stream_;
 };
 bool stream_capturing(hipStream_t stream);
+// Jacobi CG in one cooperative launch (sr_cg.hip); *done = false: not applicable, solve with separate launches
+size_t cg_resident_bytes(int64_t n);
+nqs_status cg_resident(const float *T, const double *eloc, int64_t n, double shift, double tol, int max_iter, int check,
+                       double *y, void *ws, int *iters, double *rel, bool *done, hipStream_t stream);
 // low-precision Cholesky factor of T + shift and its inverse (srmix.hip)
 size_t mix_workspace_bytes(int64_t n);
 nqs_status mix_factor(const float *T, int64_t n, double shift, int fmt, void *ws, float **Lin, float **LinT,

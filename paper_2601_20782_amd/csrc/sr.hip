@@ -8,7 +8,9 @@
 // vector-Jacobian product of the log-derivatives.
 //
 // nqs_sr_solve: Jacobi-preconditioned conjugate gradients, FP64 vectors and
-//   scalars, FP32 T read once per iteration (four rows per wave, FP64 sums).
+//   scalars.  Up to n = 5120 one launch for the whole solve, T in registers
+//   (sr_cg.hip); beyond, FP32 T read once per iteration (four rows per wave,
+//   FP64 sums).
 //   Up to n = 65536 an iteration is two launches: the product with its
 //   per-row p.Ap, then one block for the scalars and the vector updates.
 //   Every reduction is a fixed-order single-block tree, so the iterates do
@@ -275,8 +277,18 @@ nqs_status nqs_sr_solve(const float *T, const double *eloc, int64_t n, double sh
     hipStream_t s = (hipStream_t)stream;
     const size_t vec = r256(sizeof(double) * (size_t)n);
     const size_t nsc = (size_t)max_iter + 2;
-    char *ws = (char *)workspace_slot(1, 6 * vec + 3 * r256(sizeof(double) * nsc) + 256, s);
+    char *ws = (char *)workspace_slot(1, std::max(6 * vec + 3 * r256(sizeof(double) * nsc) + 256, cg_resident_bytes(n)), s);
     if (!ws) return set_error(NQS_ENOMEM, "workspace allocation failed");
+    bool done = false;
+    int its = 0;
+    double resid = 0.0;
+    const nqs_status st = cg_resident(T, eloc, n, shift, tol, max_iter, kCheck, y, ws, &its, &resid, &done, s);
+    if (st != NQS_OK) return st;
+    if (done) {
+        if (iters) *iters = its;
+        if (rel_resid) *rel_resid = resid;
+        return NQS_OK;
+    }
     double *d = (double *)ws, *r = (double *)(ws + vec), *z = (double *)(ws + 2 * vec), *p = (double *)(ws + 3 * vec),
            *Ap = (double *)(ws + 4 * vec), *prow = (double *)(ws + 5 * vec);
     double *rz = (double *)(ws + 6 * vec);                       // rz[k]: r.z after k iterations
