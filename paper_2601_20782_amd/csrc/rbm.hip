@@ -433,6 +433,11 @@ nqs_status rbm_plan_tuned(nqs_model *m, const nqs_sample_cfg &cfg, const int *Gs
 //  Combine: a reduce-scatter butterfly over the Q lanes multiplies the partial
 //   products and leaves 16/Q samples per lane; the per-site terms are formed in
 //   FP32, converted, and summed over sites in FP64 in a fixed order.
+// Bound by vector instructions (three per sample, site and unit, then phase 1's
+// tanh).  409,600 samples, 10 x 10, M = 200: 987 us with a test around every load
+// of phase 1 and FP32 spins, 876 us without; two sites per lane (half the LDS
+// reads) 928-955 us, two groups of samples per block (89 instead of 78 % of the
+// lanes) 934 us, units in pairs (fewer moves, more registers) 982 us.
 // ---------------------------------------------------------------------------
 
 typedef float floatx4 __attribute__((ext_vector_type(4)));
@@ -447,8 +452,8 @@ __global__ void __launch_bounds__(1024) rbm_eloc_tfim_kernel(RbmDev net, const i
     extern __shared__ __align__(16) float smem[];
     const int N = net.N, M = net.M;
     const int nwaves = blockDim.x >> 6;
-    float *spT = smem;                                   // [N][B] spins as +-1
-    float *tT = spT + (size_t)N * B;                     // [M][kElocTLd]
+    int8_t *spT = reinterpret_cast<int8_t *>(smem);      // [N][B] spins (bytes: 40 % less LDS, one more block per CU)
+    float *tT = smem + (size_t)N * (B / 4);              // [M][kElocTLd]
     double *red = (double *)(tT + (size_t)M * kElocTLd); // [nwaves][B]  (offset is a multiple of 16 floats)
     const int64_t base = (int64_t)blockIdx.x * B;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -456,35 +461,48 @@ __global__ void __launch_bounds__(1024) rbm_eloc_tfim_kernel(RbmDev net, const i
     for (int k = tid; k < N * B; k += blockDim.x) {
         const int b = k / N, i = k - b * N;
         const int64_t row = base + b;
-        spT[i * B + b] = row < n ? (float)samples[row * N + i] : 1.0f;
+        spT[i * B + b] = row < n ? samples[row * N + i] : (int8_t)1;
     }
     __syncthreads();
 
     // phase 1: D[j][b] = sum_i W[j][i] s_i^b, 16 x 16 tiles; lane holds D[j0 + 4*(lane/16) + r][b0 + lane % 16].
     // W values of 8 contraction steps are loaded ahead of their matrix-core steps.
     {
-        const int jt_count = (M + 15) >> 4, bt_count = (B + 15) >> 4, ksteps = (N + 3) >> 2;
-        const int la = lane & 15, lk = lane >> 4;
-        for (int t = wave; t < jt_count * bt_count; t += nwaves) {
-            const int jt = t / bt_count, bt = t - (t / bt_count) * bt_count;
-            const int j0 = jt * 16, ja = j0 + la, bc = bt * 16 + la;
+        static_assert(B == 16, "one tile of 16 samples");
+        const int jt_count = (M + 15) >> 4, la = lane & 15, lk = lane >> 4;
+        for (int jt = wave; jt < jt_count; jt += nwaves) {
+            const int j0 = jt * 16;
+            const int8_t *sg = spT + lk * B + la;
+            const float *wp = net.Wt + (size_t)lk * M + min(j0 + la, M - 1);
             floatx4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
-            for (int ks0 = 0; ks0 < ksteps; ks0 += 8) {
+            int k0 = 0;
+            // whole blocks of 8 steps (4 sites each) without a test per load (the tests took a quarter of the
+            // kernel's vector instructions), then the rest with zero spins past N
+            for (; k0 + 32 <= N; k0 += 32, wp += (size_t)32 * M, sg += 32 * B) {
+                float av[8];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) av[u] = wp[(size_t)(4 * u) * M];
+#pragma unroll
+                for (int u = 0; u < 8; ++u)
+                    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(av[u], (float)sg[4 * u * B], acc, 0, 0, 0);
+            }
+            if (k0 < N) {
                 float av[8], bv[8];
 #pragma unroll
                 for (int u = 0; u < 8; ++u) {
-                    const int k = (ks0 + u) * 4 + lk;
-                    const bool ok = ks0 + u < ksteps && k < N;
-                    av[u] = (ok && ja < M) ? net.Wt[(size_t)k * M + ja] : 0.0f;
-                    bv[u] = (ok && bc < B) ? spT[k * B + bc] : 0.0f;
+                    const int d = min(k0 + 4 * u + lk, N - 1) - (k0 + lk);   // sites from wp and sg
+                    av[u] = wp[(int64_t)d * M];
+                    const float x = (float)sg[d * B];
+                    bv[u] = k0 + 4 * u + lk < N ? x : 0.0f;
                 }
 #pragma unroll
-                for (int u = 0; u < 8; ++u) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(av[u], bv[u], acc, 0, 0, 0);
+                for (int u = 0; u < 8; ++u)
+                    if (k0 + 4 * u < N) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(av[u], bv[u], acc, 0, 0, 0);
             }
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
                 const int j = j0 + 4 * lk + r;
-                if (j < M && bc < B) tT[j * kElocTLd + bc] = tanhf(acc[r] + net.b[j]);
+                if (j < M) tT[j * kElocTLd + la] = tanhf(acc[r] + net.b[j]);
             }
         }
     }
@@ -502,15 +520,8 @@ __global__ void __launch_bounds__(1024) rbm_eloc_tfim_kernel(RbmDev net, const i
     }
     if (active) {
         float si[B];
-        const float4 *s4 = reinterpret_cast<const float4 *>(spT + i * B);
 #pragma unroll
-        for (int c = 0; c < B / 4; ++c) {
-            const float4 v = s4[c];
-            si[4 * c + 0] = v.x;
-            si[4 * c + 1] = v.y;
-            si[4 * c + 2] = v.z;
-            si[4 * c + 3] = v.w;
-        }
+        for (int b = 0; b < B; ++b) si[b] = (float)spT[i * B + b];
         const int iters = (M - q + Q - 1) / Q;
         // (C, S) of hidden unit j = t Q + q; the load for the next unit is issued one step
         // ahead (CSt carries 8 N slack entries, so the step past the last unit stays inside)
@@ -582,9 +593,9 @@ __global__ void __launch_bounds__(1024) rbm_eloc_tfim_kernel(RbmDev net, const i
 #pragma unroll
         for (int b = 0; b < BL; ++b) {
             const int bb = keep_base + b;
-            const float s = spT[i * B + bb];
-            const float ratio = ldexpf(__expf(-2.0f * ai * s) * prod[b], e2[b]);
-            float zz = 0.0f;
+            const int s = spT[i * B + bb];
+            const float ratio = ldexpf(__expf(-2.0f * ai * (float)s) * prod[b], e2[b]);
+            int zz = 0;
             if (nb1 >= 0) zz += spT[nb1 * B + bb];
             if (nb2 >= 0) zz += spT[nb2 * B + bb];
             contrib[b] = J * (double)(s * zz) + h * (double)ratio;
@@ -614,8 +625,10 @@ static nqs_status launch_eloc_q(const RbmDev &net, const nqs_ham_desc &ham, cons
 {
     const int N = net.N, M = net.M;
     const int threads = std::max(64, (int)(((int64_t)N * Q + 63) / 64 * 64));
-    const size_t lds = sizeof(float) * ((size_t)N * B + (size_t)M * (B + 4)) + sizeof(double) * (threads / 64) * B;
-    if (lds > kLdsBytes) return set_error(NQS_EUNSUPPORTED, "RBM too large for the local-energy kernel");
+    // networks that FP32 spins would not have left room for stay refused
+    const size_t lds32 = sizeof(float) * ((size_t)N * B + (size_t)M * (B + 4)) + sizeof(double) * (threads / 64) * B;
+    if (lds32 > kLdsBytes) return set_error(NQS_EUNSUPPORTED, "RBM too large for the local-energy kernel");
+    const size_t lds = lds32 - 3 * (size_t)N * B;
     const int64_t blocks = (n + B - 1) / B;
     if (blocks > INT32_MAX) return set_error(NQS_EINVAL, "too many samples");
     allow_lds(rbm_eloc_tfim_kernel<Q, B, RENORM>, lds);
