@@ -41,3 +41,20 @@ def test_vjp_matches_the_sum_over_O(nqs, arch, N, widths, n):
     again = torch.empty_like(out)
     nqs.nqs_logpsi_grad(model, x, vjp_in=g, vjp_out=again)
     assert torch.equal(out, again)
+
+
+@pytest.mark.parametrize("n,P", [(1, 4), (7, 8), (9, 1023), (64, 1024), (100, 1028), (1000, 4097), (513, 7)])
+def test_forces_at_row_and_slice_edges(nqs, n, P):
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(n * P)
+    O = torch.randn(n, P, generator=gen, device=DEV)
+    e = 3.0 * torch.randn(n, generator=gen, dtype=torch.float64, device=DEV) - 50.0
+    F = torch.empty(P, dtype=torch.float64, device=DEV)
+    mean = torch.empty(P, dtype=torch.float64, device=DEV)
+    nqs.nqs_forces(O, e, F, mean)
+    o = O.double()
+    # FP64 sums of n terms each: n 2^-53 of the sums of absolute values, here and in the reference
+    tol = 2.0 * (n + 4) * 2.0 ** -53
+    assert torch.all((mean - o.mean(dim=0)).abs() <= tol * o.abs().mean(dim=0) + 1e-300)
+    want = (o * e.unsqueeze(1)).mean(dim=0) - o.mean(dim=0) * e.mean()
+    assert torch.all((F - want).abs() <= 3.0 * tol * (o.abs() * e.abs().unsqueeze(1)).mean(dim=0) + tol * o.abs().mean(dim=0) * e.abs().mean() * 3.0)
