@@ -174,6 +174,20 @@ __device__ __forceinline__ uint32_t group_bcast(uint32_t v, int p)
     }
 }
 
+// Place of element (r, c) of an operand matrix (rows x Kp, row-contracted) kept in the order of the 32-row matrix
+// instructions: per 32 rows and contraction block one fragment, whose 16-byte pieces follow each other by lane, so
+// that a wave loads a fragment as consecutive kilobytes.  16-bit: 32x32x16 (lane = 32 ((c / 8) % 2) + r % 32 holds 8
+// values); E4M3: 32x32x64 (lane = 32 ((c / 32) % 2) + r % 32 holds 32 codes, two pieces).
+__host__ __device__ __forceinline__ size_t frag_index16(int r, int c, int Kp)
+{
+    return (((size_t)(r >> 5) * (Kp >> 4) + (c >> 4)) * 64 + ((c >> 3) & 1) * 32 + (r & 31)) * 8 + (c & 7);
+}
+__host__ __device__ __forceinline__ size_t frag_index8(int r, int c, int Kp)
+{
+    return (((((size_t)(r >> 5) * (Kp >> 6) + (c >> 6)) * 2 + ((c >> 4) & 1)) * 64) + ((c >> 5) & 1) * 32 + (r & 31)) * 16 +
+           (c & 15);
+}
+
 // log cosh z = |z| + log(1 + exp(-2|z|)) - log 2, FP32
 __device__ __forceinline__ float logcosh_f32(float z)
 {

@@ -3,22 +3,24 @@
 // (the batched forward pass of Sec. III, one matrix product per layer).
 //
 // Per step (move k):
-//   propose   one thread per chain draws (i, j, u) from its Philox stream; the
-//             proposals that change the state (every flip, an exchange of
-//             unequal spins) get a row in a compact list (atomic counter; the
-//             row order does not affect any value, only where it is stored).
-//   layer 1   GEMM whose A operand is built while staging: chain spins as
-//             +-1 with sites i, j negated (exact in every format).
+//   step      one thread per chain: the decision on move k - 1 (Delta = 2 (f' - f)
+//             in FP32, accept iff log2 u < Delta / ln 2; an accepted move flips the
+//             chain's spins and keeps f'; no incremental state: f is always a full
+//             forward), then the draw of (i, j, u) from the chain's Philox stream
+//             and whether the move changes the state (every flip, an exchange of
+//             unequal spins).
+//   rows      the moves that do get a row each, in chain order; 16-bit and E4M3
+//             copies: their configurations as operands, +-1 with sites i, j negated
+//             (exact in every format).
 //   layer l   GEMM  H_l = ReLU(H_{l-1} W_l^T + b_l), rounded to the operand
 //             format by the epilogue (the next product's input).
 //   last      GEMM with a log-cosh epilogue: per row, the partial sums over
 //             each 64-output slice are written, then added in slice order.
-//   decide    one thread per row: Delta = 2 (f' - f) in FP32, accept iff
-//             log2 u < Delta / ln 2; accepted rows flip the chain's spins and
-//             keep f'.  No incremental state: f is always a full forward.
-// The GEMM: 128 x 128 output tile per block of 4 waves (2 x 2 v_mfma 32x32
-// tiles each), contraction steps of 128 bytes per row, operands staged
-// through registers into double-buffered LDS (one barrier per step).
+// The GEMM of the 16-bit and E4M3 copies is deep_frag_gemm_kernel (operands kept
+// in the order of the matrix instructions); the FP32 copy runs deep_gemm_kernel:
+// 128 x 128 output tile per block of 4 waves (2 x 2 v_mfma 32x32 tiles each),
+// contraction steps of 128 bytes per row, operands staged through registers into
+// double-buffered LDS (one barrier per step).
 // Local energies use the same GEMMs on the rows (sample, connected
 // configuration) of a batch of samples.
 #include <hip/hip_runtime.h>
@@ -84,8 +86,6 @@ struct DeepGemmArgs {
     int ldo;
     int nct;                   // output column tiles
     int max_row_tiles;
-    float acc_scale;           // E4M3: accumulator -> pre-activation scale (weight scale x input scale)
-    float next_inv;            // E4M3: 1 / scale of the next layer's input
 };
 
 // Bit pattern of +-1 (or 0) in the operand format.
@@ -118,12 +118,10 @@ __device__ __forceinline__ void deep_load_w(const DeepGemmArgs &g, int r0, int k
     v.x3 = W[3 * step];
 }
 
-// The A operand of a GEMM: activations (AM_ACT), or the chain's spins with the row's sites negated, read 8
-// (16-bit formats) or 16 (E4M3) at a time when N is a multiple of that (AM_SPINS_VEC), else one by one
-// (AM_SPINS).  The AM_ACT and AM_SPINS_VEC paths have no branch: rows past the count and steps past N read a
-// valid address and are zeroed by selects, so the compiler can track the loads in flight exactly (a branch
-// around a load makes it wait for every outstanding load at the join).
-constexpr int AM_ACT = 0, AM_SPINS_VEC = 1, AM_SPINS = 2;
+// The A operand of a GEMM: activations (AM_ACT), or the chain's spins with the row's sites negated (AM_SPINS).  The
+// AM_ACT path has no branch: rows past the count read a valid address and are zeroed by selects, so the compiler can
+// track the loads in flight exactly (a branch around a load makes it wait for every outstanding load at the join).
+constexpr int AM_ACT = 0, AM_SPINS = 2;
 
 // Rows -> registers (rows r0 + tid / 8 + 32 q, 16 bytes of step ks each)
 template <typename T, int AM>
@@ -140,51 +138,6 @@ __device__ __forceinline__ void deep_load_a(const DeepGemmArgs &g, int r0, int k
             const u32x4 d = *reinterpret_cast<const u32x4 *>(A + (size_t)(row < nrows ? row : 0) * g.lda + k0);
             const bool ok = row < nrows;
             return u32x4{ok ? d.x : 0u, ok ? d.y : 0u, ok ? d.z : 0u, ok ? d.w : 0u};
-        } else if constexpr (AM == AM_SPINS_VEC) {
-            static_assert(sizeof(T) <= 2, "vector spin loads for 16-bit and E4M3 operands");
-            const bool ok = row < nrows && k0 < g.N;   // N is a multiple of EPC: a group is whole or past N
-            const size_t at = (size_t)rc[q] * g.N + (k0 < g.N ? k0 : 0);
-            uint32_t w0, w1, w2, w3;
-            if constexpr (sizeof(T) == 2) {
-                // 8 spins in one 8-byte load: the sign bit of each int8 (+1 = 0x01, -1 = 0xff)
-                // becomes the sign bit of a 16-bit +-1; then the row's sites are negated
-                const uint2 raw = *reinterpret_cast<const uint2 *>(g.spins + at);
-                constexpr uint32_t one2 = std::is_same<T, _Float16>::value ? 0x3C003C00u : 0x3F803F80u;
-                const uint32_t lo = (raw.x >> 7) & 0x01010101u, hi = (raw.y >> 7) & 0x01010101u;
-                w0 = one2 | ((lo & 0x1u) << 15) | ((lo & 0x100u) << 23);
-                w1 = one2 | ((lo & 0x10000u) >> 1) | ((lo & 0x1000000u) << 7);
-                w2 = one2 | ((hi & 0x1u) << 15) | ((hi & 0x100u) << 23);
-                w3 = one2 | ((hi & 0x10000u) >> 1) | ((hi & 0x1000000u) << 7);
-#pragma unroll
-                for (int t = 0; t < 2; ++t) {
-                    const uint32_t e = (uint32_t)((t == 0 ? ri[q] : rj[q]) - k0);
-                    const uint32_t m = e < 8u ? 1u << (15 + 16 * (e & 1u)) : 0u;
-                    const uint32_t wsel = e >> 1;
-                    w0 ^= wsel == 0 ? m : 0u;
-                    w1 ^= wsel == 1 ? m : 0u;
-                    w2 ^= wsel == 2 ? m : 0u;
-                    w3 ^= wsel == 3 ? m : 0u;
-                }
-            } else {
-                // 16 spins in one 16-byte load: +1 = 0x01, -1 = 0xff, so the E4M3 code of the spin is
-                // 0x38 (1.0) with the spin's sign bit; then the row's sites are negated
-                const u32x4 raw = *reinterpret_cast<const u32x4 *>(g.spins + at);
-                w0 = 0x38383838u | (raw.x & 0x80808080u);
-                w1 = 0x38383838u | (raw.y & 0x80808080u);
-                w2 = 0x38383838u | (raw.z & 0x80808080u);
-                w3 = 0x38383838u | (raw.w & 0x80808080u);
-#pragma unroll
-                for (int t = 0; t < 2; ++t) {
-                    const uint32_t e = (uint32_t)((t == 0 ? ri[q] : rj[q]) - k0);
-                    const uint32_t m = e < 16u ? 0x80u << (8 * (e & 3u)) : 0u;
-                    const uint32_t wsel = e >> 2;
-                    w0 ^= wsel == 0 ? m : 0u;
-                    w1 ^= wsel == 1 ? m : 0u;
-                    w2 ^= wsel == 2 ? m : 0u;
-                    w3 ^= wsel == 3 ? m : 0u;
-                }
-            }
-            return u32x4{ok ? w0 : 0u, ok ? w1 : 0u, ok ? w2 : 0u, ok ? w3 : 0u};
         } else {
             uint32_t w0 = 0u, w1 = 0u, w2 = 0u, w3 = 0u;
             if (row < nrows) {
@@ -226,16 +179,11 @@ __device__ __forceinline__ void deep_store(T *dst, const Stage4 &v)
     p[3 * step] = v.x3;
 }
 
-// A fragment of LDS (rows are 16-byte aligned; the 32-byte FP8 fragment is read as two halves)
+// A fragment of LDS
 template <typename T>
 __device__ __forceinline__ typename Mc<T>::frag deep_frag(const T *p)
 {
-    if constexpr (sizeof(T) == 1) {
-        const u32x4 lo = *reinterpret_cast<const u32x4 *>(p), hi = *reinterpret_cast<const u32x4 *>(p + 16);
-        return i32x8{(int)lo.x, (int)lo.y, (int)lo.z, (int)lo.w, (int)hi.x, (int)hi.y, (int)hi.z, (int)hi.w};
-    } else {
-        return *reinterpret_cast<const typename Mc<T>::frag *>(p);
-    }
+    return *reinterpret_cast<const typename Mc<T>::frag *>(p);
 }
 
 template <typename T, int AM, bool LOGCOSH>
@@ -323,7 +271,7 @@ __global__ void __launch_bounds__(256, 2) deep_gemm_kernel(DeepGemmArgs g)
                 bq[b][q] = *reinterpret_cast<const float4 *>(g.bias + n0 + wn + 32 * b + 8 * q + 4 * h);
         auto pre = [&](int a, int b, int q, int e) {   // the pre-activation of output 8q + 4h + e
             const float bb = e == 0 ? bq[b][q].x : (e == 1 ? bq[b][q].y : (e == 2 ? bq[b][q].z : bq[b][q].w));
-            return std::is_same<T, Fp8>::value ? fmaf(acc[a][b][4 * q + e], g.acc_scale, bb) : acc[a][b][4 * q + e] + bb;
+            return acc[a][b][4 * q + e] + bb;
         };
         if constexpr (LOGCOSH) {
             float *part = reinterpret_cast<float *>(g.out);
@@ -368,12 +316,7 @@ __global__ void __launch_bounds__(256, 2) deep_gemm_kernel(DeepGemmArgs g)
                         Out4 o;
 #pragma unroll
                         for (int e = 0; e < 4; ++e) {
-                            const float v = col0 + e < g.Nout ? fmaxf(pre(a, b, q, e), 0.0f) : 0.0f;
-                            if constexpr (std::is_same<T, Fp8>::value)
-                                // the next layer's input: ReLU(z) / s_next as an E4M3 code (s_next a power of two)
-                                o.v[e] = Fp8{(uint8_t)e4m3_code_nonneg(v * g.next_inv)};
-                            else
-                                o.v[e] = Mc<T>::from_f32(v);
+                            o.v[e] = Mc<T>::from_f32(col0 + e < g.Nout ? fmaxf(pre(a, b, q, e), 0.0f) : 0.0f);
                         }
                         *reinterpret_cast<Out4 *>(out + (size_t)row * g.ldo + col0) = o;
                     }
@@ -462,6 +405,289 @@ __global__ void __launch_bounds__(256, 2) deep_gemm_kernel(DeepGemmArgs g)
 }
 
 // ---------------------------------------------------------------------------
+// 16-bit and E4M3 products on operands in matrix-instruction order (frag_index16 / frag_index8)
+//
+// Weights are laid out once with the copy, the spins by deep_spins_kernel, a layer's output by its epilogue (a lane
+// holds four consecutive outputs of one row: half a fragment piece, so a wave's stores are whole lines); every load
+// is then consecutive kilobytes.  A block of four waves takes 128 RB rows x 32 NT outputs: a wave owns 32 RB rows,
+// whose operands it loads straight into registers (no other wave needs them), one contraction step (4 KB per 32 rows
+// or outputs) ahead, each piece as soon as its predecessor was used; the weights are shared through double-buffered
+// LDS, one barrier per step.  Tiles in sequence per block, the next tile's first loads issued in the last step.
+//
+// Why: with 64 x 64 outputs per wave, both operands in LDS, every product needed one LDS read, 128 bytes per clock
+// of the CU, the rate of its LDS; here 64 + 16 (RB = 2, NT = 5).  The spins were expanded from bytes for each of
+// the 13 column tiles, 140 vector instructions per 16 products.  400-1600-800-400 network, about 32,850 rows a
+// step, BF16: layers 1 to 3 took 128, 127 and 43 us each launch, now 57, 90 and 34 us (740, 930 and 610 TFLOP/s of the
+// widths asked for; bound by the LDS and operand loads of a step, which two blocks per CU overlap only in part);
+// E4M3 92, 77 and 28 us, now 52, 56 and 21 us.  Layer 1 writes 105 MB and is near the rate of a copy at its end.
+// Sums run over the contraction in the same order as before, so every value is the same bit for bit.
+// ---------------------------------------------------------------------------
+constexpr int kFragRows = 256;   // rows of the largest tile
+
+struct DeepFragArgs {
+    const u32x4 *A, *W;        // operands [32-row block][KB4][64 lanes] 16-byte pieces
+    const int *nrows;          // device: number of rows
+    const float *bias;         // [Np]
+    int KB4;                   // pieces per block of A and W (a multiple of 4)
+    int KBv;                   // contraction blocks with values
+    int nbw;                   // 32-output blocks of W
+    int Nout, nblk, nct;       // outputs, their 32-output blocks (what the next layer reads), column tiles
+    void *out;                 // ReLU: the next layer's operands, KB4o pieces per block; log-cosh: float [rows][nslice]
+    int KB4o, nslice;
+    int max_row_tiles;
+    float acc_scale;           // E4M3: accumulator -> pre-activation scale (weight scale x input scale)
+    float next_inv;            // E4M3: 1 / scale of the next layer's input
+};
+
+template <typename T>
+__device__ __forceinline__ typename Mc<T>::frag deep_frag_of(const u32x4 (&v)[sizeof(typename Mc<T>::frag) / 16])
+{
+    if constexpr (sizeof(typename Mc<T>::frag) == 32)
+        return i32x8{(int)v[0].x, (int)v[0].y, (int)v[0].z, (int)v[0].w,
+                     (int)v[1].x, (int)v[1].y, (int)v[1].z, (int)v[1].w};
+    else
+        return __builtin_bit_cast(typename Mc<T>::frag, v[0]);
+}
+
+template <typename T, int RB, int NT, bool LOGCOSH>
+__global__ void __launch_bounds__(256, 2) deep_frag_gemm_kernel(DeepFragArgs g)
+{
+    typedef typename Mc<T>::frag frag;
+    constexpr int P = sizeof(frag) / 16, KK = 4 / P;   // pieces per fragment, contraction blocks per step
+    __shared__ u32x4 lds[2][NT * 4][64];
+    const int nrows = *g.nrows;
+    constexpr int kTileRows = 128 * RB;
+    // tile ids are renumbered so that each XCD gets a contiguous range, whose rows stay in its L2
+    const int valid = ((nrows + kTileRows - 1) / kTileRows) * g.nct, G = gridDim.x;
+    if ((int)blockIdx.x >= valid) return;
+    const int q8 = valid >> 3, r8 = valid & 7;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int l32 = lane & 31, h = lane >> 5;
+    auto coords = [&](int x, int &rb, int &nb) {   // the wave's first 32-row block, the tile's first 32-output block
+        const int xcd = x & 7, lb = xcd * q8 + min(xcd, r8) + (x >> 3), rt = lb / g.nct;
+        rb = (rt * 4 + wave) * RB;
+        nb = (lb - rt * g.nct) * NT;
+    };
+    int x = blockIdx.x, rb, nb, rbn, nbn;
+    coords(x, rb, nb);
+
+    mc_floatx16 acc[RB][NT];
+    u32x4 a[RB][KK][P], wr[NT];
+    auto load_a = [&](int r0, int ks, int kk) {
+#pragma unroll
+        for (int r = 0; r < RB; ++r)
+#pragma unroll
+            for (int q = 0; q < P; ++q) a[r][kk][q] = g.A[((size_t)(r0 + r) * g.KB4 + (ks * KK + kk) * P + q) * 64 + lane];
+    };
+    auto load_w = [&](int n0, int ks) {
+#pragma unroll
+        for (int b = 0; b < NT; ++b) wr[b] = g.W[((size_t)min(n0 + b, g.nbw - 1) * g.KB4 + ks * 4 + wave) * 64 + lane];
+    };
+    auto store_w = [&](int buf) {
+#pragma unroll
+        for (int b = 0; b < NT; ++b) lds[buf][b * 4 + wave][lane] = wr[b];
+    };
+    auto zero_acc = [&]() {
+#pragma unroll
+        for (int r = 0; r < RB; ++r)
+#pragma unroll
+            for (int b = 0; b < NT; ++b)
+#pragma unroll
+                for (int e = 0; e < 16; ++e) acc[r][b][e] = 0.0f;
+    };
+
+    // The accumulators hold D[i = output][j = row]: lane = j + 32 ((i / 4) % 2), register = i % 4 + 4 (i / 8), so a lane
+    // has row l32 of its 32-row block and outputs 8q + 4h + 0..3 (q = 0..3) of each 32-output block.
+    auto epilogue = [&]() {
+        auto pre = [&](int r, int b, int q, int e, const float4 &bq) {
+            const float bb = e == 0 ? bq.x : (e == 1 ? bq.y : (e == 2 ? bq.z : bq.w));
+            return std::is_same<T, Fp8>::value ? fmaf(acc[r][b][4 * q + e], g.acc_scale, bb) : acc[r][b][4 * q + e] + bb;
+        };
+        if constexpr (LOGCOSH) {
+            // per row, the partial sums over each 64-output slice
+            static_assert(NT % 2 == 0, "whole slices");
+            float *part = reinterpret_cast<float *>(g.out);
+#pragma unroll
+            for (int sl = 0; sl < NT / 2; ++sl) {
+                if (nb + 2 * sl >= 2 * g.nslice) break;
+                float4 bq[2][4];
+#pragma unroll
+                for (int b = 0; b < 2; ++b)
+#pragma unroll
+                    for (int q = 0; q < 4; ++q)
+                        bq[b][q] = *reinterpret_cast<const float4 *>(g.bias + (nb + 2 * sl + b) * 32 + 8 * q + 4 * h);
+#pragma unroll
+                for (int r = 0; r < RB; ++r) {
+                    float abs_sum = 0.0f, prod = 1.0f;
+                    int cnt = 0;
+#pragma unroll
+                    for (int b = 0; b < 2; ++b)
+#pragma unroll
+                        for (int q = 0; q < 4; ++q)
+#pragma unroll
+                            for (int e = 0; e < 4; ++e)
+                                if ((nb + 2 * sl + b) * 32 + 8 * q + 4 * h + e < g.Nout) {
+                                    const float v = fabsf(pre(r, 2 * sl + b, q, e, bq[b][q]));
+                                    abs_sum += v;
+                                    prod *= 1.0f + __expf(-2.0f * v);   // 32 factors in (1, 2]
+                                    ++cnt;
+                                }
+                    float sv = abs_sum + __logf(prod) - (float)cnt * kLn2f;
+                    sv += __shfl_xor(sv, 32, 64);
+                    const int row = (rb + r) * 32 + l32;
+                    if (h == 0 && row < nrows) part[(size_t)row * g.nslice + (nb >> 1) + sl] = sv;
+                }
+            }
+        } else {
+            // rows past the last lie within the buffer (whole tiles) and are never used
+            unsigned char *out = reinterpret_cast<unsigned char *>(g.out);
+#pragma unroll
+            for (int b = 0; b < NT; ++b) {
+                if (nb + b >= g.nblk) break;
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const int col = (nb + b) * 32 + 8 * q + 4 * h;
+                    const float4 bq = *reinterpret_cast<const float4 *>(g.bias + col);
+#pragma unroll
+                    for (int r = 0; r < RB; ++r) {
+                        struct alignas(4 * sizeof(T)) {
+                            T v[4];
+                        } o;
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) {
+                            const float v = col + e < g.Nout ? fmaxf(pre(r, b, q, e, bq), 0.0f) : 0.0f;
+                            if constexpr (std::is_same<T, Fp8>::value)
+                                // the next layer's input: ReLU(z) / s_next as an E4M3 code (s_next a power of two)
+                                o.v[e] = Fp8{(uint8_t)e4m3_code_nonneg(v * g.next_inv)};
+                            else
+                                o.v[e] = Mc<T>::from_f32(v);
+                        }
+                        size_t piece;
+                        if constexpr (P == 2)
+                            piece = ((size_t)(rb + r) * g.KB4o + (col >> 6) * 2 + ((col >> 4) & 1)) * 64 + ((col >> 5) & 1) * 32;
+                        else
+                            piece = ((size_t)(rb + r) * g.KB4o + (col >> 4)) * 64 + ((col >> 3) & 1) * 32;
+                        constexpr int kPer = 16 / sizeof(T);   // values per piece
+                        *reinterpret_cast<decltype(o) *>(out + (piece + l32) * 16 + (col % kPer) * sizeof(T)) = o;
+                    }
+                }
+            }
+        }
+    };
+
+    const int KS = (g.KBv + KK - 1) / KK, rem = g.KBv - (KS - 1) * KK;   // steps, blocks of the last one
+    load_w(nb, 0);
+#pragma unroll
+    for (int kk = 0; kk < KK; ++kk) load_a(rb, 0, kk);
+    store_w(0);
+    zero_acc();
+    __syncthreads();
+    int cur = 0;
+    // one step: products of step ks; the loads of the step that follows (row block rf, output block nf, step kf)
+    auto step = [&](auto last, int rf, int nf, int kf) {
+        load_w(nf, kf);
+#pragma unroll
+        for (int kk = 0; kk < KK; ++kk) {
+            if (!decltype(last)::value || kk < rem) {
+                frag av[RB];
+#pragma unroll
+                for (int r = 0; r < RB; ++r) av[r] = deep_frag_of<T>(a[r][kk]);
+#pragma unroll
+                for (int b = 0; b < NT; ++b) {
+                    u32x4 wv[P];
+#pragma unroll
+                    for (int q = 0; q < P; ++q) wv[q] = lds[cur][b * 4 + kk * P + q][lane];
+                    const frag w = deep_frag_of<T>(wv);
+                    // D[i = output][j = row]
+#pragma unroll
+                    for (int r = 0; r < RB; ++r) acc[r][b] = Mc<T>::mma(w, av[r], acc[r][b]);
+                }
+            }
+            load_a(rf, kf, kk);
+        }
+        store_w(cur ^ 1);
+        __syncthreads();
+        cur ^= 1;
+    };
+    while (true) {
+        for (int ks = 0; ks + 1 < KS; ++ks) step(std::false_type{}, rb, nb, ks + 1);
+        const bool more = x + G < valid;
+        rbn = rb;
+        nbn = nb;
+        if (more) coords(x + G, rbn, nbn);
+        step(std::true_type{}, rbn, nbn, 0);
+        epilogue();
+        if (!more) break;
+        zero_acc();
+        x += G;
+        rb = rbn;
+        nb = nbn;
+    }
+}
+
+// Piece u of a first-layer operand row: 16 bytes, that is 8 or 16 spins, of lane half u % 2.
+template <typename T>
+struct SpinPiece {
+    static constexpr int EPC = 16 / sizeof(T);        // spins
+    static constexpr int P = sizeof(typename Mc<T>::frag) / 16;
+    typedef typename std::conditional<EPC == 16, unsigned __int128, uint64_t>::type raw_t;
+    static __device__ __forceinline__ int first(int u)
+    {
+        const int pc = u >> 1, h = u & 1;
+        return P == 2 ? (pc >> 1) * 64 + 32 * h + 16 * (pc & 1) : pc * 16 + 8 * h;
+    }
+    // the spins from the piece's first on, or the last EPC of the row where it ends past N (any bytes where N < EPC)
+    static __device__ __forceinline__ raw_t load(const int8_t *sp, int N, int u)
+    {
+        raw_t raw = 0;
+        if (N >= EPC) {
+            __builtin_memcpy(&raw, sp + min(first(u), N - EPC), EPC);
+        } else {
+            for (int e = 0; e < N; ++e) raw |= (raw_t)(uint8_t)sp[e] << (8 * e);
+        }
+        return raw;
+    }
+    // the operand of row `row`, sites fi and fj negated
+    static __device__ __forceinline__ void store(raw_t raw, int N, int u, int fi, int fj, int row, int KB4, u32x4 *X)
+    {
+        const int k0 = first(u), over = k0 + EPC - N;   // spins of the piece past N
+        if (N >= EPC && over > 0) raw = over < EPC ? raw >> (8 * over) : (raw_t)0;
+        uint32_t w[4] = {0u, 0u, 0u, 0u};
+#pragma unroll
+        for (int e = 0; e < EPC; ++e) {
+            const int k = k0 + e, sv = (int8_t)(uint8_t)(raw >> (8 * e));
+            const int v = k >= N ? 0 : k == fi || k == fj ? -sv : sv;
+            w[e * (int)sizeof(T) / 4] |= deep_pm1_bits<T>(v) << (8 * ((e * (int)sizeof(T)) & 3));
+        }
+        X[((size_t)(row >> 5) * KB4 + (u >> 1)) * 64 + (u & 1) * 32 + (row & 31)] = u32x4{w[0], w[1], w[2], w[3]};
+    }
+};
+// Pieces loaded before the first is stored: the stores could alias the spins, so the compiler waits for the loads there.
+constexpr int kPieceBatch = 4;
+
+// The rows' configurations as first-layer operands (the sampler's proposals write their own)
+template <typename T>
+__global__ void __launch_bounds__(256) deep_spins_kernel(const int8_t *__restrict__ spins, const int *__restrict__ nrows,
+                                                         const int *__restrict__ row_chain,
+                                                         const int *__restrict__ row_i, const int *__restrict__ row_j,
+                                                         int N, int KB4, int KBv, u32x4 *__restrict__ out)
+{
+    typedef SpinPiece<T> SP;
+    const int row = blockIdx.x * 32 + (threadIdx.x & 31);
+    if (row >= *nrows) return;
+    const int8_t *sp = spins + (size_t)row_chain[row] * N;
+    const int fi = row_i[row], fj = row_j[row], U = KBv * SP::P * 2;
+    for (int u0 = threadIdx.x >> 5; u0 < U; u0 += 8 * kPieceBatch) {
+        typename SP::raw_t raw[kPieceBatch];
+#pragma unroll
+        for (int q = 0; q < kPieceBatch; ++q) raw[q] = SP::load(sp, N, min(u0 + 8 * q, U - 1));
+#pragma unroll
+        for (int q = 0; q < kPieceBatch; ++q)
+            if (u0 + 8 * q < U) SP::store(raw[q], N, u0 + 8 * q, fi, fj, row, KB4, out);
+    }
+}
+
+// ---------------------------------------------------------------------------
 // Sampler steps
 // ---------------------------------------------------------------------------
 struct DeepStepArgs {
@@ -470,9 +696,13 @@ struct DeepStepArgs {
     int N, move;
     uint64_t seed, step_offset;
     uint32_t inst, chain_id_offset;
-    int *counter;             // [2] rows of the current / next step
-    int *row_chain, *row_i, *row_j;
+    int *counter;             // rows of the step
+    int *row_chain, *row_i, *row_j;   // FP32 copy: the rows' chains and sites
+    int *prop_i, *prop_j;     // [C] sites of the chain's current proposal
     uint32_t *ubits;          // [C] u bits of the chain's current proposal
+    unsigned long long *moves;   // [C / 64] chains whose current proposal changes the state, a bit each
+    uint8_t *count;           // [C / 64] their number (whole pieces of 16)
+    int *base;                // [C / 64] row of the first of them
     float *fcur;              // [C] log|psi| of the current state
     const float *part;        // [rows][npart]
     int npart;
@@ -486,71 +716,159 @@ struct DeepStepArgs {
     uint8_t *tr_acc;
 };
 
-__global__ void deep_propose_kernel(DeepStepArgs a, int64_t kk)
+// One wave per 64 chains: the decision on proposal k - 1 (decide), then proposal k (propose).  A chain's state is final
+// once its own decision is made, so both fit one launch; every load but the ones of a decision's partial sums and spins
+// starts at once (the new proposal's spins are read before the decided move is written and corrected for it).
+__global__ void __launch_bounds__(64) deep_step_kernel(DeepStepArgs a, int64_t kk, int decide, int propose)
 {
-    const int64_t c = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (c >= a.C) return;
-    const int64_t k = (a.kbase ? *a.kbase : 0) + kk;
-    const uint64_t step = a.step_offset + (uint64_t)k;
-    const uint32_t gid = a.chain_id_offset + (uint32_t)c;
-    const Block4 rb = philox4x32_10((uint32_t)step, (uint32_t)(step >> 32), gid, a.inst << 8, (uint32_t)a.seed,
-                                    (uint32_t)(a.seed >> 32));
-    const int i = index_from_word(rb.r0, a.N);
-    int j = -1;
-    if (a.move == 1) {
-        j = index_from_word(rb.r1, a.N - 1);
-        j += (j >= i) ? 1 : 0;
+    const int lane = threadIdx.x;
+    const int64_t c = blockIdx.x * (int64_t)64 + lane, k = (a.kbase ? *a.kbase : 0) + kk;
+    const bool in = c < a.C;
+    const int64_t cc = in ? c : a.C - 1;
+    int8_t *s = a.state + cc * a.N;
+    int i = 0, j = -1, si = 0, sj = 0;
+    uint32_t ub = 0;
+    if (propose) {
+        const uint64_t step = a.step_offset + (uint64_t)k;
+        const uint32_t gid = a.chain_id_offset + (uint32_t)cc;
+        const Block4 rb = philox4x32_10((uint32_t)step, (uint32_t)(step >> 32), gid, a.inst << 8, (uint32_t)a.seed,
+                                        (uint32_t)(a.seed >> 32));
+        i = index_from_word(rb.r0, a.N);
+        if (a.move == 1) {
+            j = index_from_word(rb.r1, a.N - 1);
+            j += (j >= i) ? 1 : 0;
+        }
+        si = s[i];
+        sj = s[j < 0 ? i : j];
+        ub = rb.r2 >> 8;
     }
-    const int8_t *s = a.state + c * a.N;
-    const bool eff = j < 0 || s[i] != s[j];
-    // (row order depends on timing; no value does)
-    const uint32_t ub = rb.r2 >> 8;
-    a.ubits[c] = ub;
-    if (eff) {
-        const int r = atomicAdd(a.counter + (k & 1), 1);
-        a.row_chain[r] = (int)c;
-        a.row_i[r] = i;
-        a.row_j[r] = j;
-    } else {
-        ++a.acc[c];   // a move that changes nothing is accepted
-    }
-    if (c < a.n_traced) {
-        const size_t idx = (size_t)c * (size_t)a.total + (size_t)k;
-        a.tr_site[idx] = i | ((j < 0 ? 0xFFFF : j) << 16);
-        a.tr_ubits[idx] = ub;
-        if (!eff) {
-            a.tr_delta[idx] = 0.0f;
-            a.tr_acc[idx] = 1;
+    unsigned long long n_acc = a.acc[cc];
+    if (decide) {
+        const unsigned long long mv = a.moves[blockIdx.x];
+        const int pi = a.prop_i[cc], pj = a.prop_j[cc];
+        const uint32_t pub = a.ubits[cc];
+        const float f = a.fcur[cc];
+        if (in && ((mv >> lane) & 1)) {
+            const float *part = a.part + (size_t)(a.base[blockIdx.x] + __popcll(mv & ((1ull << lane) - 1ull))) * a.npart;
+            const int vi = s[pi], vj = s[pj < 0 ? pi : pj];
+            float fnew = 0.0f;
+            for (int p = 0; p < a.npart; p += 4) {
+                float v[4];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) v[e] = part[min(p + e, a.npart - 1)];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) fnew = p + e < a.npart ? fnew + v[e] : fnew;
+            }
+            const float d2 = 2.0f * (fnew - f) / kLn2f;
+            const float l2u = __builtin_amdgcn_logf((float)pub * 5.9604644775390625e-8f);
+            const bool accept = l2u < d2;   // NaN rejects
+            if (accept) {
+                s[pi] = (int8_t)-vi;
+                if (pj >= 0) s[pj] = (int8_t)-vj;
+                a.fcur[c] = fnew;
+                ++n_acc;
+                if (i == pi || i == pj) si = -si;
+                if (j == pi || j == pj) sj = -sj;   // only used where j >= 0
+            }
+            if (c < a.n_traced) {
+                const size_t idx = (size_t)c * (size_t)a.total + (size_t)(k - 1);
+                a.tr_delta[idx] = d2 * kLn2f;
+                a.tr_acc[idx] = accept ? 1 : 0;
+            }
         }
     }
+    if (propose) {
+        const bool eff = in && (j < 0 || si != sj);
+        const unsigned long long bal = __ballot(eff);
+        if (lane == 0) {
+            a.moves[blockIdx.x] = bal;
+            a.count[blockIdx.x] = (uint8_t)__popcll(bal);
+        }
+        if (in) {
+            a.prop_i[c] = i;
+            a.prop_j[c] = j;
+            a.ubits[c] = ub;
+            if (!eff) ++n_acc;   // a move that changes nothing is accepted
+            if (c < a.n_traced) {
+                const size_t idx = (size_t)c * (size_t)a.total + (size_t)k;
+                a.tr_site[idx] = i | ((j < 0 ? 0xFFFF : j) << 16);
+                a.tr_ubits[idx] = ub;
+                if (!eff) {
+                    a.tr_delta[idx] = 0.0f;
+                    a.tr_acc[idx] = 1;
+                }
+            }
+        }
+    }
+    if (in) a.acc[c] = n_acc;
 }
 
-__global__ void deep_decide_kernel(DeepStepArgs a, int64_t kk)
+// The rows of the step: the proposals that change the state, in the order of their chains (64 per block).  Each block
+// adds up the counts before its own (one byte per 64 chains, so 4 KB of them per 262,144 chains), and, unless T is
+// float, writes its rows' configurations as first-layer operands (KB4 pieces per 32 rows, KBv contraction blocks).
+// Bound by the latency of three dependent loads below some 10,000 chains, then by the 2 N + N bytes a row.  With an
+// atomic count per wave in the proposals (12.7 ns each, one word) and the operands expanded by every block of the first
+// layer's product, proposal and decision took 21 us at 65,536 chains of 400 sites and 8.7 us at 8,000; step and rows take
+// 20 and 13.3 us and include the operands (a launch of their own: 10 us).
+template <typename T>
+__global__ void __launch_bounds__(256) deep_rows_kernel(DeepStepArgs a, int KB4, int KBv, u32x4 *X)
 {
-    const int64_t k = (a.kbase ? *a.kbase : 0) + kk;
-    const int n = a.counter[k & 1];
-    const int64_t r = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (r == 0) a.counter[(k + 1) & 1] = 0;   // the next step's counter (not in use now)
-    if (r >= n) return;
-    const int c = a.row_chain[r];
-    float fnew = 0.0f;
-    for (int p = 0; p < a.npart; ++p) fnew += a.part[(size_t)r * a.npart + p];
-    const float d2 = 2.0f * (fnew - a.fcur[c]) / kLn2f;
-    const uint32_t ub = a.ubits[c];
-    const float l2u = __builtin_amdgcn_logf((float)ub * 5.9604644775390625e-8f);
-    const bool accept = l2u < d2;   // NaN rejects
-    if (accept) {
-        int8_t *s = a.state + (size_t)c * a.N;
-        const int i = a.row_i[r], j = a.row_j[r];
-        s[i] = -s[i];
-        if (j >= 0) s[j] = -s[j];
-        a.fcur[c] = fnew;
-        ++a.acc[c];
+    __shared__ int l_chain[64], l_i[64], l_j[64], l_sum[4];
+    const int tid = threadIdx.x;
+    const int64_t blk = blockIdx.x;
+    const unsigned long long bal = a.moves[blk];
+    const int m = __popcll(bal);
+    uint32_t before = 0;
+    for (int64_t q = tid; q * 16 < blk; q += 256) {
+        const u32x4 v = reinterpret_cast<const u32x4 *>(a.count)[q];
+        const int64_t n = blk - q * 16;   // counts of the piece that come before
+        auto part = [&](uint32_t x, int w) { return n >= 4 * w + 4 ? x : n > 4 * w ? x & ((1u << (8 * (n - 4 * w))) - 1u) : 0u; };
+        before = __builtin_amdgcn_sad_u8(part(v.x, 0), 0u, before);
+        before = __builtin_amdgcn_sad_u8(part(v.y, 1), 0u, before);
+        before = __builtin_amdgcn_sad_u8(part(v.z, 2), 0u, before);
+        before = __builtin_amdgcn_sad_u8(part(v.w, 3), 0u, before);
     }
-    if (c < a.n_traced) {
-        const size_t idx = (size_t)c * (size_t)a.total + (size_t)k;
-        a.tr_delta[idx] = d2 * kLn2f;
-        a.tr_acc[idx] = accept ? 1 : 0;
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) before += __shfl_xor(before, o, 64);
+    if ((tid & 63) == 0) l_sum[tid >> 6] = (int)before;
+    if (tid < 64 && ((bal >> tid) & 1)) {
+        const int at = __popcll(bal & ((1ull << tid) - 1ull));
+        const int64_t c = blk * 64 + tid;
+        l_chain[at] = (int)c;
+        l_i[at] = a.prop_i[c];
+        l_j[at] = a.prop_j[c];
+    }
+    __syncthreads();
+    const int base = l_sum[0] + l_sum[1] + l_sum[2] + l_sum[3];
+    if (tid == 0) {
+        a.base[blk] = base;
+        if (blk + 1 == gridDim.x) *a.counter = base + m;
+    }
+    if constexpr (std::is_same<T, float>::value) {
+        if (tid < m) {
+            a.row_chain[base + tid] = l_chain[tid];
+            a.row_i[base + tid] = l_i[tid];
+            a.row_j[base + tid] = l_j[tid];
+        }
+    } else {
+        // item u m + r: piece u of row r, so that consecutive lanes store consecutive rows' pieces
+        typedef SpinPiece<T> SP;
+        const int items = KBv * SP::P * 2 * m;
+        const uint32_t inv = m > 1 ? 0xFFFFFFFFu / (uint32_t)m + 1u : 0u;   // it / m = umulhi(it, inv): it < 2^26, m <= 64
+        for (int i0 = tid; i0 < items; i0 += 256 * kPieceBatch) {
+            typename SP::raw_t raw[kPieceBatch];
+            int u[kPieceBatch], r[kPieceBatch];
+#pragma unroll
+            for (int q = 0; q < kPieceBatch; ++q) {
+                const int it = min(i0 + 256 * q, items - 1);
+                u[q] = m > 1 ? (int)__umulhi((uint32_t)it, inv) : it;
+                r[q] = it - u[q] * m;
+                raw[q] = SP::load(a.state + (size_t)l_chain[r[q]] * a.N, a.N, u[q]);
+            }
+#pragma unroll
+            for (int q = 0; q < kPieceBatch; ++q)
+                if (i0 + 256 * q < items) SP::store(raw[q], a.N, u[q], l_i[r[q]], l_j[r[q]], base + r[q], KB4, X);
+        }
     }
 }
 
@@ -560,7 +878,6 @@ __global__ void deep_rows_all_kernel(int64_t C, int *counter, int *row_chain, in
     const int64_t c = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
     if (c == 0) {
         counter[0] = (int)C;
-        counter[1] = 0;
     }
     if (c >= C) return;
     row_chain[c] = (int)c;
@@ -568,11 +885,9 @@ __global__ void deep_rows_all_kernel(int64_t C, int *counter, int *row_chain, in
     row_j[c] = -1;
 }
 
-__global__ void deep_set_f_kernel(int64_t C, const float *part, int npart, float *fcur, int *counter,
-                                  unsigned long long *acc)
+__global__ void deep_set_f_kernel(int64_t C, const float *part, int npart, float *fcur, unsigned long long *acc)
 {
     const int64_t c = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (c == 0) counter[0] = 0;
     if (c >= C) return;
     float f = 0.0f;
     for (int p = 0; p < npart; ++p) f += part[(size_t)c * npart + p];
@@ -629,23 +944,14 @@ static void deep_gemm_launch(const DeepGemmArgs &g, hipStream_t s)
     hipLaunchKernelGGL((deep_gemm_kernel<T, AM, LOGCOSH>), dim3(blocks), dim3(256), lds, s, g);
 }
 
-template <typename T>
-static void deep_gemm_dispatch(bool spins, bool logcosh, const DeepGemmArgs &g, hipStream_t s)
+template <typename T, int RB, int NT, bool LOGCOSH>
+static void deep_frag_launch(DeepFragArgs &g, int64_t cap, hipStream_t s)
 {
-    // spins read EPC at a time when N is a multiple of EPC (16-bit and E4M3 operands)
-    constexpr int EPC = 16 / sizeof(T);
-    if (spins && sizeof(T) <= 2 && g.N % EPC == 0) {
-        if constexpr (sizeof(T) <= 2) {
-            if (logcosh) deep_gemm_launch<T, AM_SPINS_VEC, true>(g, s);
-            else deep_gemm_launch<T, AM_SPINS_VEC, false>(g, s);
-        }
-    } else if (spins) {
-        if (logcosh) deep_gemm_launch<T, AM_SPINS, true>(g, s);
-        else deep_gemm_launch<T, AM_SPINS, false>(g, s);
-    } else {
-        if (logcosh) deep_gemm_launch<T, AM_ACT, true>(g, s);
-        else deep_gemm_launch<T, AM_ACT, false>(g, s);
-    }
+    g.nct = (g.nblk + NT - 1) / NT;
+    const int64_t tiles = (cap + 128 * RB - 1) / (128 * RB) * g.nct;
+    // persistent blocks, a multiple of 8 for the XCD renumbering
+    const int64_t blocks = std::min<int64_t>((tiles + 7) / 8 * 8, (RB == 2 ? 2 : 4) * (int64_t)device_cus());
+    hipLaunchKernelGGL((deep_frag_gemm_kernel<T, RB, NT, LOGCOSH>), dim3((unsigned)blocks), dim3(256), 0, s, g);
 }
 
 // Scratch of one forward pass over up to `cap` rows.
@@ -653,26 +959,41 @@ struct DeepBuffers {
     int *counter, *row_chain, *row_i, *row_j;
     void *H[2];
     float *part;
-    int maxK, npart;
+    int npart;
 };
 
 static size_t al256(size_t x) { return (x + 255) & ~(size_t)255; }
 
-static size_t deep_buffer_bytes(const FfnnDev &f, int64_t cap, int esize)
+// operand columns of the layer inputs (the fragment path keeps the spins as operands too), and the rows, whole
+// blocks of kFragRows there
+static int deep_max_k(const FfnnDev &f, int esize)
 {
     int maxK = 64;
-    for (int l = 1; l < f.n_layers; ++l) maxK = std::max(maxK, f.Kp[l]);
-    const int npart = 2 * (f.Np[f.n_layers - 1] / kDT);
-    return al256(sizeof(int) * 2) + 3 * al256(sizeof(int) * cap) + 2 * al256((size_t)esize * cap * maxK) +
-           al256(sizeof(float) * cap * npart);
+    for (int l = esize == 4 ? 1 : 0; l < f.n_layers; ++l) maxK = std::max(maxK, f.Kp[l]);
+    return maxK;
+}
+static int64_t deep_rows(int64_t cap, int esize)
+{
+    return esize == 4 ? cap : (cap + kFragRows - 1) / kFragRows * kFragRows;
+}
+
+// partial log-cosh sums per row: 64-output slices
+static int deep_npart(const FfnnDev &f, int esize)
+{
+    return esize == 4 ? 2 * (f.Np[f.n_layers - 1] / kDT) : (f.widths[f.n_layers] + 63) / 64;
+}
+
+static size_t deep_buffer_bytes(const FfnnDev &f, int64_t cap, int esize)
+{
+    const int npart = deep_npart(f, esize);
+    return al256(sizeof(int) * 2) + 3 * al256(sizeof(int) * cap) +
+           2 * al256((size_t)esize * deep_rows(cap, esize) * deep_max_k(f, esize)) + al256(sizeof(float) * cap * npart);
 }
 
 static DeepBuffers deep_carve(const FfnnDev &f, int64_t cap, int esize, char *base)
 {
     DeepBuffers b;
-    b.maxK = 64;
-    for (int l = 1; l < f.n_layers; ++l) b.maxK = std::max(b.maxK, f.Kp[l]);
-    b.npart = 2 * (f.Np[f.n_layers - 1] / kDT);
+    b.npart = deep_npart(f, esize);
     auto carve = [&](size_t sz) {
         char *p = base;
         base += al256(sz);
@@ -682,17 +1003,77 @@ static DeepBuffers deep_carve(const FfnnDev &f, int64_t cap, int esize, char *ba
     b.row_chain = (int *)carve(sizeof(int) * cap);
     b.row_i = (int *)carve(sizeof(int) * cap);
     b.row_j = (int *)carve(sizeof(int) * cap);
-    b.H[0] = carve((size_t)esize * cap * b.maxK);
-    b.H[1] = carve((size_t)esize * cap * b.maxK);
+    const size_t hb = (size_t)esize * deep_rows(cap, esize) * deep_max_k(f, esize);
+    b.H[0] = carve(hb);
+    b.H[1] = carve(hb);
     b.part = (float *)carve(sizeof(float) * cap * b.npart);
     return b;
 }
 
+// One forward pass of the rows listed in b on operands in matrix-instruction order (about `expect` of them, which
+// only chooses the tiles); spins NULL: the first layer's operands are there.
+template <typename T>
+static void deep_frag_forward(const FfnnDev &f, const DeepBuffers &b, const int8_t *spins, int64_t cap, int64_t expect,
+                              hipStream_t s)
+{
+    constexpr int KM = 2 * Mc<T>::EPL, P = sizeof(typename Mc<T>::frag) / 16;
+    const int L = f.n_layers, N = f.widths[0];
+    if (spins)
+        hipLaunchKernelGGL(deep_spins_kernel<T>, dim3((unsigned)((cap + 31) / 32)), dim3(256), 0, s, spins, b.counter,
+                           b.row_chain, b.row_i, b.row_j, N, f.Kp[0] / KM * P, (N + KM - 1) / KM, (u32x4 *)b.H[1]);
+    for (int l = 0; l < L; ++l) {
+        const bool last = l == L - 1;
+        DeepFragArgs g;
+        g.A = (const u32x4 *)b.H[(l + 1) & 1];
+        g.W = (const u32x4 *)f.Wd[l];
+        g.nrows = b.counter;
+        g.bias = f.bd[l];
+        g.KB4 = f.Kp[l] / KM * P;
+        g.KBv = (f.widths[l] + KM - 1) / KM;
+        g.nbw = f.Np[l] / 32;
+        g.Nout = f.widths[l + 1];
+        g.nblk = last || KM == 64 ? 2 * ((g.Nout + 63) / 64) : (g.Nout + 31) / 32;
+        g.out = last ? (void *)b.part : b.H[l & 1];
+        g.KB4o = last ? 0 : f.Kp[l + 1] / KM * P;
+        g.nslice = b.npart;
+        g.acc_scale = f.acc_scale[l];
+        g.next_inv = f.next_inv[l];
+        // The tile whose busiest CU is done first.  `pair`: two 256 x 32 NT tiles side by side on a CU, 0.31 us per 64
+        // of the contraction (measured 0.99, 1.32, 1.67 and 1.91 us for NT = 2 to 5 on 1600 x 800 weights); one tile
+        // alone takes 0.7 of that; 128 x 64 tiles, four side by side, 0.94 of the unit each, fewer 1.06 + 0.58 t.  With
+        // 1600 x 800 weights the choice is 128 x 64 below 5,500 rows (4,000: 21.4 us, 256 x 64 24.6), 256 x 64 at 8,200
+        // (29.6; 128 x 64 33.4, 256 x 128 34.7), 256 x 96 at 12,000 (36.6; 256 x 128 43.7), 256 x 128 at 16,400
+        // (46.3; 256 x 64 51.7, 256 x 160 51.5) and 256 x 160 at 32,800 (84.7; 256 x 128 89.8).
+        const int64_t cus = device_cus();
+        auto tiles = [&](int RB, int NT) {   // of the busiest CU
+            return (double)(((expect + 128 * RB - 1) / (128 * RB) * ((g.nblk + NT - 1) / NT) + cus - 1) / cus);
+        };
+        auto cost = [&](int NT, double pair) { return (tiles(2, NT) + 0.4 * std::fmod(tiles(2, NT), 2)) * 0.5 * pair; };
+        const double t = tiles(1, 2), c1 = std::max(0.94 * t, 1.06 + 0.58 * t);
+        const double c2 = cost(2, 3.2), c3 = cost(3, 4.25), c4 = cost(4, 5.4), c5 = cost(5, 6.15);
+        if (last) {
+            if (c1 <= std::min(c2, c4)) deep_frag_launch<T, 1, 2, true>(g, cap, s);
+            else if (c2 <= c4) deep_frag_launch<T, 2, 2, true>(g, cap, s);
+            else deep_frag_launch<T, 2, 4, true>(g, cap, s);
+        } else {
+            const double c = std::min(std::min(std::min(c1, c2), std::min(c3, c4)), c5);
+            if (c == c1) deep_frag_launch<T, 1, 2, false>(g, cap, s);
+            else if (c == c2) deep_frag_launch<T, 2, 2, false>(g, cap, s);
+            else if (c == c3) deep_frag_launch<T, 2, 3, false>(g, cap, s);
+            else if (c == c4) deep_frag_launch<T, 2, 4, false>(g, cap, s);
+            else deep_frag_launch<T, 2, 5, false>(g, cap, s);
+        }
+    }
+}
+
 // One forward pass of the rows listed in b (count on the device), spins from `spins`.
 static void deep_forward(int dtype, const FfnnDev &f, const DeepBuffers &b, const int8_t *spins, int64_t cap,
-                         hipStream_t s)
+                         int64_t expect, bool spins_ready, hipStream_t s)
 {
     const int L = f.n_layers;
+    if (dtype == NQS_BF16) return deep_frag_forward<__bf16>(f, b, spins_ready ? nullptr : spins, cap, expect, s);
+    if (dtype == NQS_F16) return deep_frag_forward<_Float16>(f, b, spins_ready ? nullptr : spins, cap, expect, s);
+    if (dtype == NQS_FP8_E4M3) return deep_frag_forward<Fp8>(f, b, spins_ready ? nullptr : spins, cap, expect, s);
     DeepGemmArgs g;
     g.spins = spins;
     g.row_chain = b.row_chain;
@@ -713,12 +1094,8 @@ static void deep_forward(int dtype, const FfnnDev &f, const DeepBuffers &b, cons
         g.nct = f.Np[l] / kDT;
         g.out = last ? (void *)b.part : b.H[l & 1];
         g.ldo = last ? 0 : f.Kp[l + 1];
-        g.acc_scale = f.acc_scale[l];
-        g.next_inv = f.next_inv[l];
-        if (dtype == NQS_F16) deep_gemm_dispatch<_Float16>(l == 0, last, g, s);
-        else if (dtype == NQS_BF16) deep_gemm_dispatch<__bf16>(l == 0, last, g, s);
-        else if (dtype == NQS_FP8_E4M3) deep_gemm_dispatch<Fp8>(l == 0, last, g, s);
-        else deep_gemm_dispatch<float>(l == 0, last, g, s);
+        if (l == 0) last ? deep_gemm_launch<float, AM_SPINS, true>(g, s) : deep_gemm_launch<float, AM_SPINS, false>(g, s);
+        else last ? deep_gemm_launch<float, AM_ACT, true>(g, s) : deep_gemm_launch<float, AM_ACT, false>(g, s);
     }
 }
 
@@ -732,17 +1109,29 @@ nqs_status deep_sample(nqs_model *m, const nqs_sample_cfg &cfg, int8_t *chain_st
     if (C > INT32_MAX / 2) return set_error(NQS_EINVAL, "too many chains");
     // scratch: forward buffers + per-chain state
     const size_t fwd = deep_buffer_bytes(f, C, esize);
-    const size_t per_chain = al256(sizeof(uint32_t) * C) + al256(sizeof(float) * C) + al256(sizeof(unsigned long long) * C) +
-                             al256(sizeof(int64_t));
+    const int64_t nw = (C + 63) / 64;
+    const size_t per_chain = 3 * al256(sizeof(int) * C) + al256(sizeof(float) * C) + al256(sizeof(unsigned long long) * C) +
+                             al256(sizeof(unsigned long long) * nw) + al256((size_t)(nw + 15) / 16 * 16) +
+                             al256(sizeof(int) * nw) + al256(sizeof(int64_t));
     char *ws = (char *)workspace(fwd + per_chain, stream);
     if (!ws) return set_error(NQS_ENOMEM, "workspace allocation failed");
     DeepBuffers b = deep_carve(f, C, esize, ws);
     char *pc = ws + fwd;
-    uint32_t *ubits = (uint32_t *)pc;
-    float *fcur = (float *)(pc + al256(sizeof(uint32_t) * C));
-    unsigned long long *acc = (unsigned long long *)(pc + al256(sizeof(uint32_t) * C) + al256(sizeof(float) * C));
-    int64_t *kbase = (int64_t *)(pc + al256(sizeof(uint32_t) * C) + al256(sizeof(float) * C) +
-                                 al256(sizeof(unsigned long long) * C));
+    auto carve = [&](size_t bytes) {
+        char *p = pc;
+        pc += al256(bytes);
+        return (void *)p;
+    };
+    DeepStepArgs a = {};
+    a.prop_i = (int *)carve(sizeof(int) * C);
+    a.prop_j = (int *)carve(sizeof(int) * C);
+    a.ubits = (uint32_t *)carve(sizeof(uint32_t) * C);
+    float *fcur = (float *)carve(sizeof(float) * C);
+    unsigned long long *acc = (unsigned long long *)carve(sizeof(unsigned long long) * C);
+    a.moves = (unsigned long long *)carve(sizeof(unsigned long long) * nw);
+    a.count = (uint8_t *)carve((size_t)(nw + 15) / 16 * 16);
+    a.base = (int *)carve(sizeof(int) * nw);
+    int64_t *kbase = (int64_t *)carve(sizeof(int64_t));
 
     if (cfg.init_chains) {
         nqs_status st = launch_init_chains(chain_state, C, N, cfg.move, cfg.seed, cfg.instance_id, cfg.chain_id_offset,
@@ -752,11 +1141,10 @@ nqs_status deep_sample(nqs_model *m, const nqs_sample_cfg &cfg, int8_t *chain_st
     const unsigned cb = (unsigned)((C + 255) / 256);
     // f of the start states
     hipLaunchKernelGGL(deep_rows_all_kernel, dim3(cb), dim3(256), 0, stream, C, b.counter, b.row_chain, b.row_i, b.row_j);
-    deep_forward(cfg.dtype, f, b, chain_state, C, stream);
-    hipLaunchKernelGGL(deep_set_f_kernel, dim3(cb), dim3(256), 0, stream, C, b.part, b.npart, fcur, b.counter, acc);
+    deep_forward(cfg.dtype, f, b, chain_state, C, C, false, stream);
+    hipLaunchKernelGGL(deep_set_f_kernel, dim3(cb), dim3(256), 0, stream, C, b.part, b.npart, fcur, acc);
     NQS_HIP_TRY(hipGetLastError());
 
-    DeepStepArgs a;
     a.state = chain_state;
     a.C = C;
     a.N = N;
@@ -769,7 +1157,6 @@ nqs_status deep_sample(nqs_model *m, const nqs_sample_cfg &cfg, int8_t *chain_st
     a.row_chain = b.row_chain;
     a.row_i = b.row_i;
     a.row_j = b.row_j;
-    a.ubits = ubits;
     a.fcur = fcur;
     a.part = b.part;
     a.npart = b.npart;
@@ -783,14 +1170,33 @@ nqs_status deep_sample(nqs_model *m, const nqs_sample_cfg &cfg, int8_t *chain_st
     a.tr_delta = tr ? trace->delta : nullptr;
     a.tr_acc = tr ? trace->accepted : nullptr;
     a.kbase = nullptr;
+    // half of the exchanges swap unequal spins
+    const int64_t expect = cfg.move == NQS_MOVE_EXCHANGE ? std::max<int64_t>(1, C / 2 * N / (N - 1)) : C;
+    // the decision on proposal k - 1, unless k is a sweep's first, and proposal k with its forward pass; the decision on a
+    // sweep's last proposal
+    auto decide = [&](int64_t k, int dec, int pro, hipStream_t s) {
+        hipLaunchKernelGGL(deep_step_kernel, dim3((unsigned)nw), dim3(64), 0, s, a, k, dec, pro);
+    };
+    auto step = [&](int64_t k, int first, hipStream_t s) {
+        decide(k, !first, 1, s);
+        auto rows = [&](auto kernel, int KM, int P) {
+            hipLaunchKernelGGL(kernel, dim3((unsigned)nw), dim3(256), 0, s, a, f.Kp[0] / KM * P, (N + KM - 1) / KM,
+                               (u32x4 *)b.H[1]);
+        };
+        if (cfg.dtype == NQS_BF16) rows(deep_rows_kernel<__bf16>, 16, 1);
+        else if (cfg.dtype == NQS_F16) rows(deep_rows_kernel<_Float16>, 16, 1);
+        else if (cfg.dtype == NQS_FP8_E4M3) rows(deep_rows_kernel<Fp8>, 64, 2);
+        else rows(deep_rows_kernel<float>, 16, 1);
+        deep_forward(cfg.dtype, f, b, chain_state, C, expect, true, s);
+    };
 
-    // Two or more sweeps of an even size: capture one sweep's launches (proposal, forward pass, decision for each
+    // Two or more sweeps: capture one sweep's launches (proposal, forward pass, decision for each
     // of its proposals, then the sample emit) once into a graph and replay it per sweep; the proposal index and
     // the sweep come from a device counter that the graph's last node advances, so every replay is the same graph.
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
     NQS_HIP_TRY(hipStreamIsCapturing(stream, &cap));
     const int n_sw = cfg.n_burnin + cfg.n_sweeps;
-    if (sw % 2 == 0 && n_sw >= 2 && cap == hipStreamCaptureStatusNone) {
+    if (n_sw >= 2 && cap == hipStreamCaptureStatusNone) {
         a.kbase = kbase;
         hipLaunchKernelGGL(deep_set_i64_kernel, dim3(1), dim3(1), 0, stream, kbase, (int64_t)0, (int64_t)0);
         std::string sig;
@@ -812,13 +1218,8 @@ nqs_status deep_sample(nqs_model *m, const nqs_sample_cfg &cfg, int8_t *chain_st
             hipStream_t cs = capture_stream();
             if (!cs) return set_error(NQS_EDEVICE, "could not create the capture stream");
             NQS_HIP_TRY(hipStreamBeginCapture(cs, hipStreamCaptureModeRelaxed));
-            for (int j = 0; j < sw; ++j) {
-                hipLaunchKernelGGL(deep_propose_kernel, dim3(cb), dim3(256), 0, cs, a, (int64_t)j);
-                DeepBuffers bk = b;
-                bk.counter = b.counter + (j & 1);   // k = kbase + j with kbase even
-                deep_forward(cfg.dtype, f, bk, chain_state, C, cs);
-                hipLaunchKernelGGL(deep_decide_kernel, dim3(cb), dim3(256), 0, cs, a, (int64_t)j);
-            }
+            for (int j = 0; j < sw; ++j) step(j, j == 0, cs);
+            decide(sw, 1, 0, cs);
             if (samples || logpsi) {
                 const int eb = (int)std::min<int64_t>((C * N + 255) / 256, 8192);
                 hipLaunchKernelGGL(deep_emit_sweep_kernel, dim3(eb), dim3(256), 0, cs, chain_state, C, N, fcur, samples,
@@ -847,14 +1248,10 @@ nqs_status deep_sample(nqs_model *m, const nqs_sample_cfg &cfg, int8_t *chain_st
     int in_sweep = 0;
     int64_t sweep = 0;
     for (int64_t k = 0; k < a.total; ++k) {
-        // rows of step k are counted in counter[k & 1]; the forward pass reads that slot
-        hipLaunchKernelGGL(deep_propose_kernel, dim3(cb), dim3(256), 0, stream, a, k);
-        DeepBuffers bk = b;
-        bk.counter = b.counter + (k & 1);
-        deep_forward(cfg.dtype, f, bk, chain_state, C, stream);
-        hipLaunchKernelGGL(deep_decide_kernel, dim3(cb), dim3(256), 0, stream, a, k);
+        step(k, in_sweep == 0, stream);
         if (++in_sweep == sw) {
             in_sweep = 0;
+            decide(k + 1, 1, 0, stream);
             const int64_t out = sweep - cfg.n_burnin;
             if (out >= 0 && (samples || logpsi)) {
                 const int eb = (int)std::min<int64_t>((C * N + 255) / 256, 8192);
@@ -1064,7 +1461,9 @@ nqs_status deep_local_energy(nqs_model *m, const nqs_ham_desc &ham, const int8_t
         nqs_status z = launch_zero_u64(b.counter, 1, stream);
         if (z != NQS_OK) return z;
         hipLaunchKernelGGL(deep_eloc_rows_kernel, dim3(nbat), dim3(256), 0, stream, a);
-        deep_forward(dtype, f, b, samples, cap, stream);
+        // a row per site (TFIM), or per unequal pair, about half of the bonds; and the sample itself
+        const int64_t expect = (int64_t)nbat * (1 + (ham.kind == NQS_TFIM ? N : ham.dim * N / 2));
+        deep_forward(dtype, f, b, samples, cap, expect, false, stream);
         hipLaunchKernelGGL(deep_eloc_reduce_kernel, dim3((nbat + 3) / 4), dim3(256), 0, stream, nbat, base, count, diag,
                            row_coef, b.part, b.npart, eloc + s0);
         NQS_HIP_TRY(hipGetLastError());

@@ -37,9 +37,10 @@ __global__ void ffnn_round_layer_kernel(const double *__restrict__ Wsrc, const d
     }
 }
 
-// dst[r][c] (ld_dst, zero padded to rows_p x cols_p) from src[r][c] (ld_src)
+// dst[r][c] (ld_dst, zero padded to rows_p x cols_p) from src[r][c] (ld_src); frag: the codes in matrix-instruction
+// order (frag_index16) instead of row by row
 __global__ void ffnn_pad_kernel(const float *__restrict__ src, int rows, int cols, int ld_src, int rows_p, int cols_p,
-                                int dtype, uint16_t *codes, float *f32)
+                                int dtype, uint16_t *codes, float *f32, int frag)
 {
     const int64_t n = (int64_t)rows_p * cols_p;
     for (int64_t p = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; p < n; p += (int64_t)gridDim.x * blockDim.x) {
@@ -54,7 +55,7 @@ __global__ void ffnn_pad_kernel(const float *__restrict__ src, int rows, int col
             } else {
                 code = (uint16_t)(__float_as_uint(v) >> 16);   // exact: v is a bf16 value
             }
-            codes[p] = code;
+            codes[frag ? frag_index16(r, c, cols_p) : (size_t)p] = code;
         }
     }
 }
@@ -84,7 +85,7 @@ __device__ __forceinline__ uint8_t e4m3_code_exact(double q)
     return (uint8_t)(sign | ((uint32_t)(E + 7) << 3) | (uint32_t)((2.0 * m - 1.0) * 8.0));
 }
 
-// codes[Np][Kp] of W[out][in] / scale (zero padded) and the transposed FP32 values
+// codes of W[out][in] / scale (zero padded to Np x Kp, in matrix-instruction order) and the transposed FP32 values
 __global__ void ffnn_e4m3_codes_kernel(const double *__restrict__ W, int out, int in,
                                        const unsigned long long *__restrict__ amax_bits, int Np, int Kp,
                                        uint8_t *__restrict__ codes, float *__restrict__ Wt)
@@ -100,7 +101,7 @@ __global__ void ffnn_e4m3_codes_kernel(const double *__restrict__ W, int out, in
             code = e4m3_code_exact(q);
             Wt[(int64_t)c * out + r] = (float)(q * (double)scale);
         }
-        codes[p] = code;
+        codes[frag_index8(r, c, Kp)] = code;
     }
 }
 
@@ -173,7 +174,7 @@ static nqs_status ffnn_build_e4m3(nqs_model *m, hipStream_t stream)
                            0, stream, Wm, out, in, (const unsigned long long *)(amax + 2 * l), f.Np[l], f.Kp[l],
                            (uint8_t *)f.Wd[l], f.Wt[l]);
         hipLaunchKernelGGL(ffnn_pad_kernel, dim3((f.Np[l] + 255) / 256), dim3(256), 0, stream, f.b[l], 1, out, out, 1,
-                           f.Np[l], (int)kF32, (uint16_t *)nullptr, f.bd[l]);
+                           f.Np[l], (int)kF32, (uint16_t *)nullptr, f.bd[l], 0);
         hipLaunchKernelGGL(ffnn_e4m3_rowsum_kernel, dim3((out + 3) / 4), dim3(256), 0, stream, Wm, bm, out, in,
                            (const unsigned long long *)(amax + 2 * l), (const unsigned long long *)(amax + 2 * l + 1),
                            rs[l], bq[l]);
@@ -283,7 +284,7 @@ nqs_status ffnn_build_copy(nqs_model *m, int dtype, hipStream_t stream)
             const int64_t n = (int64_t)rows_p * cols_p;
             const int blocks = (int)std::min<int64_t>((n + 255) / 256, 8192);
             hipLaunchKernelGGL(ffnn_pad_kernel, dim3(blocks), dim3(256), 0, stream, src, rows, cols, ld, rows_p, cols_p,
-                               dtype, codes, f32);
+                               dtype, codes, f32, 0);
         };
         pad(f.W[1], M2, M1, M1, f.m2p, f.m1p, lp ? f.W2c : nullptr, f.W2p);
         pad(f.Wt[0], N, M1, M1, N, f.m1p, lp ? f.W1ct : nullptr, f.W1tp);
@@ -298,9 +299,9 @@ nqs_status ffnn_build_copy(nqs_model *m, int dtype, hipStream_t stream)
         const int64_t n = (int64_t)f.Np[l] * f.Kp[l];
         const int blocks = (int)std::min<int64_t>((n + 255) / 256, 8192);
         hipLaunchKernelGGL(ffnn_pad_kernel, dim3(blocks), dim3(256), 0, stream, f.W[l], out, in, in, f.Np[l], f.Kp[l],
-                           dtype, lp ? (uint16_t *)f.Wd[l] : nullptr, lp ? nullptr : (float *)f.Wd[l]);
+                           dtype, lp ? (uint16_t *)f.Wd[l] : nullptr, lp ? nullptr : (float *)f.Wd[l], 1);
         hipLaunchKernelGGL(ffnn_pad_kernel, dim3((f.Np[l] + 255) / 256), dim3(256), 0, stream, f.b[l], 1, out, out, 1,
-                           f.Np[l], dtype, (uint16_t *)nullptr, f.bd[l]);
+                           f.Np[l], dtype, (uint16_t *)nullptr, f.bd[l], 0);
         NQS_HIP_TRY(hipGetLastError());
     }
     NQS_HIP_TRY(hipStreamSynchronize(stream));
