@@ -884,8 +884,15 @@ nqs_status ffnn_sample(nqs_model *m, const nqs_sample_cfg &cfg, int8_t *chain_st
         return NQS_OK;
     }
     const int QK = (f.m1p + 63) / 64;
-    const int64_t blocks = (cfg.n_chains + kRows - 1) / kRows;   // kRows == kRegRows: 64 chains per block
     if (use_reg) {
+        // 8, 4, 2 or 1 chains per wave: the fewest whose blocks (one per CU, the LDS holds W1) all run at once.  A step
+        // is a chain of latencies (draws, staging, products, decision) that shortens with the rows of a block:
+        // 100-400-200, 100 exchange steps of 16,384, 4,096 and 1,024 chains take 568, 526 and 512 us with 8 per wave,
+        // 325 us with 2 (4,096) and 264 us with 1 (1,024); 8 stays best where the blocks no longer fit (16,384 chains
+        // with 4: 763 us).
+        A.rpw = kRegRows / kRegWaves;
+        while (A.rpw > 1 && (cfg.n_chains + kRegWaves * (A.rpw / 2) - 1) / (kRegWaves * (A.rpw / 2)) <= device_cus()) A.rpw /= 2;
+        const int64_t blocks = (cfg.n_chains + kRegWaves * A.rpw - 1) / (kRegWaves * A.rpw);
         // With exchange moves about half the proposals swap equal spins: chains that
         // advance on their own decide those on the spot and fill every tile with
         // effective rows.  Flip moves are all effective, so the chains step together.
@@ -896,7 +903,7 @@ nqs_status ffnn_sample(nqs_model *m, const nqs_sample_cfg &cfg, int8_t *chain_st
         NQS_HIP_TRY(hipGetLastError());
         return NQS_OK;
     }
-    return ffnn_sample_dispatch(cfg.dtype, QK, tr, A, (int)blocks, lds, stream);
+    return ffnn_sample_dispatch(cfg.dtype, QK, tr, A, (int)((cfg.n_chains + kRows - 1) / kRows), lds, stream);
 }
 
 nqs_status ffnn_local_energy(nqs_model *m, const nqs_ham_desc &ham, const int8_t *samples, int64_t n, int dtype,

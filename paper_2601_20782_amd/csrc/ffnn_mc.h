@@ -154,6 +154,7 @@ struct FfnnSampleArgs {
     int64_t n_chains;
     int n_sweeps, n_burnin, sweep_size, refresh_sweeps;
     int move;          // 0 flip, 1 exchange
+    int rpw;           // chains per wave of the register-resident kernel
     uint64_t seed, step_offset;
     uint32_t inst, chain_id_offset;
     int n_traced;

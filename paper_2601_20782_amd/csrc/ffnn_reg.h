@@ -10,7 +10,7 @@
 // turns its 32 x 32 tile into per-row partial log-cosh sums over its 32
 // outputs; the partials of the waves are added in wave order.
 //
-// Sampler: 64 chains per block; wave w keeps z1 of chains 8w .. 8w+7 in
+// Sampler: up to 64 chains per block; wave w keeps z1 of its up to 8 chains in
 // registers (lane c owns hidden units 8c .. 8c + 7, so that a W1 column or an h1
 // row moves in one 16-byte access per lane) and updates it by the rank-1
 // (flip) or rank-2 (exchange) change of an accepted move.  Proposals that
@@ -30,7 +30,18 @@ namespace nqs {
 
 constexpr int kRegThreads = 512;
 constexpr int kRegWaves = kRegThreads / 64;
-constexpr int kRegRows = 64;       // chains per sampler block
+constexpr int kRegRows = 64;       // chains per sampler block at most
+
+// p[0] + p[stride] + ... (n <= kRegWaves values, in order), all read at once
+__device__ __forceinline__ float sum_partials(const float *p, int stride, int n)
+{
+    float v[kRegWaves], f = 0.0f;
+#pragma unroll
+    for (int w = 0; w < kRegWaves; ++w) v[w] = p[min(w, n - 1) * stride];
+#pragma unroll
+    for (int w = 0; w < kRegWaves; ++w) f = w < n ? f + v[w] : f;
+    return f;
+}
 
 // A fragments of this wave's 32 rows of W2 ([m2p][m1p], operand format); zero
 // beyond m2p.
@@ -155,7 +166,7 @@ struct Dot2<_Float16> {
     }
 };
 
-// Each wave owns 8 chains: it draws their proposals (lanes 0..7), stages the
+// Each wave owns up to 8 chains: it draws their proposals (lanes 0..7), stages the
 // effective ones at slots taken from a shared counter, and after the matrix
 // product decides them and updates their state.  Two barriers per step: after
 // the staging (h1 rows complete) and after the product (partial sums complete).
@@ -181,10 +192,12 @@ __global__ void __launch_bounds__(kRegThreads) ffnn_sample_reg_kernel(FfnnSample
     int *cnt = reinterpret_cast<int *>(words + kRegRows * NW);   // [4] rows and live chains of this / the next round
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int64_t c0 = (int64_t)blockIdx.x * kRegRows;
-    const int nvalid = (int)min<int64_t>(kRegRows, A.n_chains - c0);
+    // the block's chains are A.rpw per wave; wave w's chain r has row w RPW + r
+    const int rpw = A.rpw;
+    const int64_t cw = ((int64_t)blockIdx.x * kRegWaves + __builtin_amdgcn_readfirstlane(wave)) * rpw;   // the wave's first
+    const int wvalid = (int)max<int64_t>(0, min<int64_t>(rpw, A.n_chains - cw));
     const int myrow = wave * RPW + (lane & (RPW - 1));           // the chain of proposal lanes 0..7
-    const bool plane = lane < RPW && myrow < nvalid;
+    const bool plane = lane < wvalid;
     const int c8 = 8 * (lane < NCH ? lane : NCH - 1);   // this lane's units (lanes past the last chunk repeat it)
     const bool live = __builtin_amdgcn_readfirstlane(wave) * 32 < m2;   // this wave owns real outputs
 
@@ -200,9 +213,10 @@ __global__ void __launch_bounds__(kRegThreads) ffnn_sample_reg_kernel(FfnnSample
         for (int k = tid; k < m2p; k += kRegThreads) b2s[k] = net.b2p[k];
         for (int k = tid; k < kRegRows * NW; k += kRegThreads) {
             const int r = k / NW, w = k % NW;
+            const int64_t c = ((int64_t)blockIdx.x * kRegWaves + r / RPW) * rpw + r % RPW;
             uint32_t bits = 0;
-            if (r < nvalid) {
-                const int8_t *s = A.chain_state + (c0 + r) * N + 32 * w;
+            if (r % RPW < rpw && c < A.n_chains) {
+                const int8_t *s = A.chain_state + c * N + 32 * w;
                 const int nb = min(32, N - 32 * w);
                 for (int b = 0; b < nb; ++b) bits |= (s[b] > 0 ? 1u : 0u) << b;
             }
@@ -265,27 +279,69 @@ __global__ void __launch_bounds__(kRegThreads) ffnn_sample_reg_kernel(FfnnSample
         }
     };
     constexpr unsigned kAllRows = (1u << RPW) - 1u;
-    // layer-1 change of flipping i (and j >= 0) where site i holds spin si (no branch: W1[:, max(j, 0)] is read
-    // and weighted by 0 for a flip, which leaves W1[:, i] exact)
-    auto delta_z1 = [&](int i, int j, float si, float (&dz)[8]) {
-        const float g = -2.0f * si, jm = j >= 0 ? 1.0f : 0.0f;
+    // layer-1 change of flipping i (and j >= 0): W1[:, i] - W1[:, j] of this lane's units, to be weighted by -2 s_i (no
+    // branch: W1[:, max(j, 0)] is read and weighted by 0 for a flip, which leaves W1[:, i] exact)
+    auto delta_z1 = [&](int i, int j, float (&d)[8]) {
         const frag wi = *reinterpret_cast<const frag *>(W1l + i * K + c8);
         const frag wj = *reinterpret_cast<const frag *>(W1l + (j >= 0 ? j : 0) * K + c8);
+        const float jm = j >= 0 ? 1.0f : 0.0f;
 #pragma unroll
-        for (int e = 0; e < 8; ++e) dz[e] = g * fmaf(-jm, Mc<T>::to_f32(wj[e]), Mc<T>::to_f32(wi[e]));
+        for (int e = 0; e < 8; ++e) d[e] = fmaf(-jm, Mc<T>::to_f32(wj[e]), Mc<T>::to_f32(wi[e]));
     };
-    // h1 = ReLU(z + dz) of one row, this lane's 8 units
-    auto store_row = [&](int row, const float (&z)[8], const float (&dz)[8]) {
+    // h1 = ReLU(z + g d) of one row, this lane's 8 units (g d is exact for g = 0, +-2)
+    auto store_row = [&](int row, const float (&z)[8], float g, const float (&d)[8]) {
         frag h;
 #pragma unroll
-        for (int e = 0; e < 8; ++e) h[e] = Mc<T>::from_f32(fmaxf(z[e] + dz[e], 0.0f));
+        for (int e = 0; e < 8; ++e) h[e] = Mc<T>::from_f32(fmaxf(fmaf(g, d[e], z[e]), 0.0f));
         *reinterpret_cast<frag *>(Hs + row * ldh + c8) = h;
+    };
+    // the rows of this wave's chains' proposals: every chain's row is formed, one without a row goes to the spare row
+    // kRegRows, so that the code has no branch and later reads overlap earlier stores (but one branch per 1, 2 and 4
+    // chains where a wave has fewer)
+    auto stage_rows = [&](int slot, int pi, int pj, float si) {
+        auto one = [&](auto r_c) {
+            constexpr int r = decltype(r_c)::value;
+            const int sl = __builtin_amdgcn_readlane(slot, r);
+            const int i = __builtin_amdgcn_readlane(pi, r), j = __builtin_amdgcn_readlane(pj, r);
+            const float s_i = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(si), r));
+            float d[8];
+            delta_z1(i, j, d);
+            store_row(sl >= 0 ? sl : kRegRows, z1[r], -2.0f * s_i, d);
+        };
+        one(std::integral_constant<int, 0>{});
+        if (rpw > 1) {
+            one(std::integral_constant<int, 1>{});
+            if (rpw > 2) {
+                one(std::integral_constant<int, 2>{});
+                one(std::integral_constant<int, 3>{});
+                if (rpw > 4) {
+                    one(std::integral_constant<int, 4>{});
+                    one(std::integral_constant<int, 5>{});
+                    one(std::integral_constant<int, 6>{});
+                    one(std::integral_constant<int, 7>{});
+                }
+            }
+        }
+    };
+    // the accepted moves (bit r of um: chain r's) applied to z1
+    auto apply_moves = [&](unsigned long long um, int pi, int pj, float si) {
+#pragma unroll
+        for (int r = 0; r < RPW; ++r) {
+            if ((um >> r) & 1ull) {
+                const int i = __builtin_amdgcn_readlane(pi, r), j = __builtin_amdgcn_readlane(pj, r);
+                const float s_i = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(si), r));
+                float d[8];
+                delta_z1(i, j, d);
+#pragma unroll
+                for (int e = 0; e < 8; ++e) z1[r][e] = fmaf(-2.0f * s_i, d[e], z1[r][e]);
+            }
+        }
     };
     // log|psi| of this wave's chains from the current z1 (lanes 0..7 return their chain's value)
     auto full_eval = [&]() -> float {
         const float zero[8] = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-        for (int r = 0; r < RPW; ++r) store_row(wave * RPW + r, z1[r], zero);
+        for (int r = 0; r < RPW; ++r) store_row(wave * RPW + r, z1[r], 0.0f, zero);
         __syncthreads();
         if (live)
             for (int t = 0; t < kRegRows / 32; ++t) {
@@ -293,9 +349,7 @@ __global__ void __launch_bounds__(kRegThreads) ffnn_sample_reg_kernel(FfnnSample
                 if (lane < 32) part[wave * kRegRows + 32 * t + lane] = s;
             }
         __syncthreads();
-        float f = 0.0f;
-        for (int w = 0; w < nwt; ++w) f += part[w * kRegRows + myrow];
-        return f;
+        return sum_partials(part + myrow, kRegRows, nwt);
     };
 
     refresh_rows(kAllRows);
@@ -322,7 +376,7 @@ __global__ void __launch_bounds__(kRegThreads) ffnn_sample_reg_kernel(FfnnSample
         // the decision of an ineffective proposal (its log-ratio is 0)
         auto trace = [&](int64_t k, int pi_, int pj_, uint32_t ub_, float d2, bool accept) {
             if constexpr (TRACE) {
-                const int64_t c = c0 + myrow;
+                const int64_t c = cw + lane;
                 if (c < A.n_traced) {
                     const size_t idx = (size_t)c * (size_t)total + (size_t)k;
                     A.tr_site[idx] = pi_ | ((pj_ < 0 ? 0xFFFF : pj_) << 16);
@@ -357,7 +411,7 @@ __global__ void __launch_bounds__(kRegThreads) ffnn_sample_reg_kernel(FfnnSample
             bool wup = false, weff = false;
             if (inwin) {
                 const uint64_t step = A.step_offset + (uint64_t)(kc_g + gd);
-                const uint32_t gidg = A.chain_id_offset + (uint32_t)(c0 + wave * RPW + gr);
+                const uint32_t gidg = A.chain_id_offset + (uint32_t)(cw + gr);
                 const Block4 rb = philox4x32_10((uint32_t)step, (uint32_t)(step >> 32), gidg, A.inst << 8, key0, key1);
                 wpi = index_from_word(rb.r0, N);
                 if (A.move == 1) {
@@ -379,7 +433,7 @@ __global__ void __launch_bounds__(kRegThreads) ffnn_sample_reg_kernel(FfnnSample
                 const float l2u = __builtin_amdgcn_logf((float)wub * 5.9604644775390625e-8f);
                 skip_acc = l2u < 0.0f;
                 if constexpr (TRACE) {
-                    const int64_t c = c0 + wave * RPW + gr;
+                    const int64_t c = cw + gr;
                     if (c < A.n_traced) {
                         const size_t idx = (size_t)c * (size_t)total + (size_t)(kc_g + gd);
                         A.tr_site[idx] = wpi | ((wpj < 0 ? 0xFFFF : wpj) << 16);
@@ -431,17 +485,7 @@ __global__ void __launch_bounds__(kRegThreads) ffnn_sample_reg_kernel(FfnnSample
             // chains that refresh: z1 recomputed from their spins
             const unsigned rm = (unsigned)__ballot(mode == 2) & kAllRows;
             if (rm) refresh_rows(rm);
-            // stage the rows (wave-uniform per chain): every chain's row is formed, one without a row goes to the
-            // spare row kRegRows, so that the code has no branch and later reads overlap earlier stores
-    #pragma unroll
-            for (int r = 0; r < RPW; ++r) {
-                const int sl = __builtin_amdgcn_readlane(slot, r);
-                const int i = __builtin_amdgcn_readlane(pi, r), j = __builtin_amdgcn_readlane(pj, r);
-                const float s_i = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(si), r));
-                float dz[8];
-                delta_z1(i, j, s_i, dz);
-                store_row(sl >= 0 ? sl : kRegRows, z1[r], dz);
-            }
+            stage_rows(slot, pi, pj, si);
             // chains with work left are counted with the rows: none left ends the call for the whole block
             if (plane && (kc < total || need_refresh || emit_q >= 0)) atomicAdd(&cnt[2 + par], 1);
             __syncthreads();
@@ -461,8 +505,7 @@ __global__ void __launch_bounds__(kRegThreads) ffnn_sample_reg_kernel(FfnnSample
             // decisions and refreshed values of this wave's chains
             bool upd = false;
             if (plane && mode != 0) {
-                float fnew = 0.0f;
-                for (int w = 0; w < nwt; ++w) fnew += part[w * kRegRows + slot];
+                const float fnew = sum_partials(part + slot, kRegRows, nwt);
                 if (mode == 2) {
                     fcur = fnew;
                     need_refresh = false;
@@ -484,18 +527,7 @@ __global__ void __launch_bounds__(kRegThreads) ffnn_sample_reg_kernel(FfnnSample
                 }
             }
             // apply the accepted moves to z1
-            const unsigned long long um = __ballot(upd);
-    #pragma unroll
-            for (int r = 0; r < RPW; ++r) {
-                if ((um >> r) & 1ull) {
-                    const int i = __builtin_amdgcn_readlane(pi, r), j = __builtin_amdgcn_readlane(pj, r);
-                    const float s_i = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(si), r));
-                    float dz[8];
-                    delta_z1(i, j, s_i, dz);
-    #pragma unroll
-                    for (int e = 0; e < 8; ++e) z1[r][e] += dz[e];
-                }
-            }
+            apply_moves(__ballot(upd), pi, pj, si);
             // samples due (no refresh pending): the chain's spins and log|psi|
             const bool emit = plane && emit_q >= 0 && !need_refresh;
             const unsigned long long em = __ballot(emit);
@@ -507,12 +539,12 @@ __global__ void __launch_bounds__(kRegThreads) ffnn_sample_reg_kernel(FfnnSample
                     const int row = wave * RPW + r;
                     if (out >= 0 && A.samples)
                         for (int i = lane; i < N; i += 64)
-                            A.samples[((size_t)out * A.n_chains + c0 + row) * N + i] =
+                            A.samples[((size_t)out * A.n_chains + cw + r) * N + i] =
                                 ((words[row * NW + (i >> 5)] >> (i & 31)) & 1u) ? 1 : -1;
                 }
             }
             if (emit) {
-                if (out_lane >= 0 && A.logpsi) A.logpsi[(size_t)out_lane * A.n_chains + c0 + myrow] = fcur;
+                if (out_lane >= 0 && A.logpsi) A.logpsi[(size_t)out_lane * A.n_chains + cw + lane] = fcur;
                 emit_q = -1;
             }
             par ^= 1;
@@ -531,7 +563,7 @@ __global__ void __launch_bounds__(kRegThreads) ffnn_sample_reg_kernel(FfnnSample
             uint32_t ub = 0;
             if (plane) {
                 const uint64_t step = A.step_offset + (uint64_t)k;
-                const uint32_t gid = A.chain_id_offset + (uint32_t)(c0 + myrow);
+                const uint32_t gid = A.chain_id_offset + (uint32_t)(cw + lane);
                 const Block4 rb = philox4x32_10((uint32_t)step, (uint32_t)(step >> 32), gid, A.inst << 8, key0, key1);
                 pi = index_from_word(rb.r0, N);
                 if (A.move == 1) {
@@ -545,18 +577,7 @@ __global__ void __launch_bounds__(kRegThreads) ffnn_sample_reg_kernel(FfnnSample
                 if (eff) slot = atomicAdd(&cnt[k & 1], 1);
                 ub = rb.r2 >> 8;
             }
-            // stage h1 of the effective proposals (rows are wave-uniform); every chain's row is formed and an
-            // ineffective one goes to the spare row kRegRows, so that the code has no branch and the reads of later
-            // chains can be issued before earlier rows are stored
-    #pragma unroll
-            for (int r = 0; r < RPW; ++r) {
-                const int sl = __builtin_amdgcn_readlane(slot, r);
-                const int i = __builtin_amdgcn_readlane(pi, r), j = __builtin_amdgcn_readlane(pj, r);
-                const float s_i = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(si), r));
-                float dz[8];
-                delta_z1(i, j, s_i, dz);
-                store_row(sl >= 0 ? sl : kRegRows, z1[r], dz);
-            }
+            stage_rows(slot, pi, pj, si);
             __syncthreads();
             const int neff = cnt[k & 1];
             for (int t = 0; live && 32 * t < neff; ++t) {
@@ -568,9 +589,7 @@ __global__ void __launch_bounds__(kRegThreads) ffnn_sample_reg_kernel(FfnnSample
             // decisions of this wave's chains
             bool upd = false;
             if (plane) {
-                float fnew = 0.0f;
-                if (slot >= 0)
-                    for (int w = 0; w < nwt; ++w) fnew += part[w * kRegRows + slot];
+                const float fnew = sum_partials(part + max(slot, 0), kRegRows, nwt);
                 const float d2 = slot >= 0 ? 2.0f * (fnew - fcur) / kLn2f : 0.0f;
                 const float l2u = __builtin_amdgcn_logf((float)ub * 5.9604644775390625e-8f);
                 const bool accept = l2u < d2;   // NaN rejects
@@ -583,7 +602,7 @@ __global__ void __launch_bounds__(kRegThreads) ffnn_sample_reg_kernel(FfnnSample
                     fcur = fnew;
                 }
                 if constexpr (TRACE) {
-                    const int64_t c = c0 + myrow;
+                    const int64_t c = cw + lane;
                     if (c < A.n_traced) {
                         const size_t idx = (size_t)c * (size_t)total + (size_t)k;
                         A.tr_site[idx] = pi | ((pj < 0 ? 0xFFFF : pj) << 16);
@@ -594,18 +613,7 @@ __global__ void __launch_bounds__(kRegThreads) ffnn_sample_reg_kernel(FfnnSample
                 }
             }
             // apply the accepted moves to z1
-            const unsigned long long um = __ballot(upd);
-    #pragma unroll
-            for (int r = 0; r < RPW; ++r) {
-                if ((um >> r) & 1ull) {
-                    const int i = __builtin_amdgcn_readlane(pi, r), j = __builtin_amdgcn_readlane(pj, r);
-                    const float s_i = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(si), r));
-                    float dz[8];
-                    delta_z1(i, j, s_i, dz);
-    #pragma unroll
-                    for (int e = 0; e < 8; ++e) z1[r][e] += dz[e];
-                }
-            }
+            apply_moves(__ballot(upd), pi, pj, si);
             if (++in_sweep == sw) {
                 in_sweep = 0;
                 const int64_t out = sweep - A.n_burnin;
@@ -620,12 +628,12 @@ __global__ void __launch_bounds__(kRegThreads) ffnn_sample_reg_kernel(FfnnSample
                         // this wave's chains: lane = site within a word row
                         for (int idx = lane; idx < RPW * N; idx += 64) {
                             const int r = idx / N, i = idx % N, row = wave * RPW + r;
-                            if (row < nvalid)
-                                A.samples[((size_t)out * A.n_chains + c0 + row) * N + i] =
+                            if (r < wvalid)
+                                A.samples[((size_t)out * A.n_chains + cw + r) * N + i] =
                                     ((words[row * NW + (i >> 5)] >> (i & 31)) & 1u) ? 1 : -1;
                         }
                     }
-                    if (A.logpsi && plane) A.logpsi[(size_t)out * A.n_chains + c0 + myrow] = fcur;
+                    if (A.logpsi && plane) A.logpsi[(size_t)out * A.n_chains + cw + lane] = fcur;
                 }
                 ++sweep;
             }
@@ -633,10 +641,10 @@ __global__ void __launch_bounds__(kRegThreads) ffnn_sample_reg_kernel(FfnnSample
     }
     for (int idx = lane; idx < RPW * N; idx += 64) {
         const int r = idx / N, i = idx % N, row = wave * RPW + r;
-        if (row < nvalid)
-            A.chain_state[(c0 + row) * N + i] = ((words[row * NW + (i >> 5)] >> (i & 31)) & 1u) ? 1 : -1;
+        if (r < wvalid)
+            A.chain_state[(cw + r) * N + i] = ((words[row * NW + (i >> 5)] >> (i & 31)) & 1u) ? 1 : -1;
     }
-    if (A.n_acc && plane) A.n_acc[c0 + myrow] = acc;
+    if (A.n_acc && plane) A.n_acc[cw + lane] = acc;
 }
 
 // ---------------------------------------------------------------------------
