@@ -918,14 +918,25 @@ nqs_status ffnn_local_energy(nqs_model *m, const nqs_ham_desc &ham, const int8_t
     const FfnnDev &f = m->copies[dtype].ffnn;
     const int N = f.widths[0];
     size_t lds;
-    // the register-resident kernel: W1 (16 KE columns) in LDS and groups of G samples, the largest G of 8, 4, 2,
-    // 1 whose rows the LDS holds (N < 8191 for the packed row codes)
+    // the register-resident kernel: W1 (16 KE columns) in LDS and groups of G samples (N < 8191 for the candidate
+    // table), the G up to 8 whose rows the LDS holds that ends first: a group takes its passes and the time of about four
+    // more, the CUs as many groups each.  100-400-200, BF16: groups of 2, 3, 4 and 5 samples take 22.5, 28.0, 33.7 and
+    // 41.4 us; 1,025 samples end after 55.3 us with 5 (one group a CU; 58.7 with 4), 3,000 after 118 us with 4 (138 with 5).
     const int KE = f.n_layers >= 2 ? (f.widths[1] + 15) / 16 : 0;   // 16-wide fragments multiplied
     auto reg_lds_for = [&](int G) {
         return dtype == NQS_F16 ? ffnn_reg_eloc_lds_f16(N, KE, f.m2p, G) : ffnn_reg_eloc_lds_bf16(N, KE, f.m2p, G);
     };
-    int reg_G = 8;
-    while (reg_G > 1 && reg_lds_for(reg_G) > 160 * 1024) reg_G /= 2;
+    int reg_G = 1;
+    double best = 0.0;
+    const double rows = 1.0 + (ham.kind == NQS_TFIM ? N : 0.5 * ham.dim * N);   // of a sample, about
+    for (int G = 1; G <= 8 && (G == 1 || reg_lds_for(G) <= 160 * 1024); ++G) {
+        const int64_t rounds = ((n + G - 1) / G + device_cus() - 1) / device_cus();
+        const double t = (double)rounds * (G * rows / kElocRows + 4.5);
+        if (G == 1 || t < 0.97 * best) {
+            reg_G = G;
+            best = t;
+        }
+    }
     const size_t reg_lds = reg_path(dtype, f) ? reg_lds_for(reg_G) : 0;
     const bool use_reg = reg_path(dtype, f) && reg_lds <= 160 * 1024 && N < 8191;
     if (use_reg) lds = reg_lds;

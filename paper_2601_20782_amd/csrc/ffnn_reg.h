@@ -651,8 +651,8 @@ __global__ void __launch_bounds__(kRegThreads) ffnn_sample_reg_kernel(FfnnSample
 // Local energies
 //
 // The W1 columns the network uses (16 KE hidden units, KE = ceil(m1 / 16)) are
-// copied to LDS once per block.  A group of G samples (G <= 8, as many as the
-// LDS holds): the block forms z1 = W1 s + b1 of each sample (lane pairs split
+// copied to LDS once per block.  A group of G samples (G <= 8, those that the
+// LDS holds at most): the block forms z1 = W1 s + b1 of each sample (lane pairs split
 // the sites), lists each sample's rows (the sample itself, then its connected
 // configurations) and evaluates the rows of the whole group end to end,
 // kElocRows = 32 at a time.  Passes are software-pipelined over two LDS
@@ -675,7 +675,7 @@ __host__ __device__ inline size_t reg_eloc_lds_bytes(int N, int KE, int m2p, int
     const size_t K = 16 * (size_t)KE, ldh = K + hs_pad<T>();
     const size_t maxrows = (size_t)G * (2 * N + 1);
     size_t b = 0;
-    b += sizeof(T) * (size_t)N * K;                     // W1 columns
+    b += sizeof(T) * (size_t)(N + 1) * K;               // W1 columns and a column of zeros
     b += sizeof(T) * 2 * (size_t)kElocRows * ldh;       // h1 rows of two passes
     b += sizeof(float) * (size_t)G * K;                 // z1 of the group's samples
     b += sizeof(float) * K;                             // b1
@@ -683,49 +683,60 @@ __host__ __device__ inline size_t reg_eloc_lds_bytes(int N, int KE, int m2p, int
     b += sizeof(float) * 2 * kRegWaves * kElocRows;     // partial sums of two passes
     b += sizeof(float) * (size_t)G * N;                 // spins
     b += sizeof(int) * 2 * (size_t)N;                   // candidate table (flips and bonds)
-    b += (sizeof(int) + 3 * sizeof(float)) * maxrows;   // rows: packed (i, j, sample), coefficient, g, f
+    b += (sizeof(int) + 2 * sizeof(float)) * maxrows;   // rows: code, coefficient, f
     b += sizeof(double) * G + sizeof(int) * G + 32;
     return b;
 }
 
-// row code: (i + 1) | (j + 1) << 13 | s << 26, i = j = -1 for the sample itself
-__device__ __forceinline__ int eloc_row_code(int i, int j, int s) { return (i + 1) | ((j + 1) << 13) | (s << 26); }
-
-// h1 = ReLU(z1 + g (W1[:, i] - W1[:, j])) of row `row` (g = -2 s_i, 0 for the sample's own row; the W1[:, j]
-// term only for an exchange), hidden units 8c .. 8c + 7, c = min(lane, nch - 1) (lanes past the row's chunks
-// repeat the last one), into Hs row lr.  W1l: [N][K] in LDS; zs: [G][2][K / 8][4] (units 8c .. 8c + 3 of
-// every chunk, then units 8c + 4 .. 8c + 7, so that the 16-byte reads of consecutive lanes are consecutive).
-// `code` is the row's code, uniform over the wave (read ahead by the caller or from rcode).
-template <typename T>
-__device__ __forceinline__ void eloc_stage_row_code(const T *W1l, int code, const float *rg, const float *zs,
-                                                    T *Hs, int ldh, int K, int nch, int row, int lr, int lane)
+// Row code: column i | column j << 13 | sample << 26 | (s_i < 0) << 31, a column by its first 16 bytes' place (2 KE i: the
+// columns take at most 96 KB).  A flip has the column of zeros (N) for j, a sample's own row i = j = 0.
+__device__ __forceinline__ uint32_t eloc_row_code(int KE, int i, int j, int s, bool down)
 {
+    return (uint32_t)(2 * KE * i) | (uint32_t)(2 * KE * j) << 13 | (uint32_t)s << 26 | (down ? 0x80000000u : 0u);
+}
+
+// h1 = ReLU(z1 + g (W1[:, i] - W1[:, j])) of a row (g = -2 s_i), the 16 bytes c16 / 16 of it (lanes past the row's
+// chunks repeat the last one).  W1l: [N + 1][K] in LDS; zs: [G][2][K / 8][4] (units 8c .. 8c + 3 of every
+// chunk, then units 8c + 4 .. 8c + 7, so that the 16-byte reads of consecutive lanes are consecutive).
+// A pass is bound by the instructions its waves issue: with two waves on a SIMD each issues a vector one about every 5
+// cycles (8.3 where it needs the one before) and a scalar one every 8.4.  So the code holds places, not sites, needs no
+// select for flips, and is decoded in vector registers: 47 vector and no scalar instructions a row instead of 53 and 16 (BF16).
+// 400-200, 65,001 samples of 100 sites: 2,090 -> 1,950 to 1,980 us.  (Waves of their own for staging and for the next group's
+// preparation, four or twelve waves in all, took 2,380 to 2,810 us.)
+template <typename T, int K>
+struct ElocRow {
     typedef typename Mc<T>::frag frag;
-    const float g = rg[row];
-    const int i = (code & 0x1FFF) - 1, j = ((code >> 13) & 0x1FFF) - 1, s = code >> 26;
-    const int ic = i >= 0 ? i : 0, jc = j >= 0 ? j : 0;
-    const float jm = j >= 0 ? 1.0f : 0.0f;
-    const int c = lane < nch ? lane : nch - 1;
-    const frag wi = *reinterpret_cast<const frag *>(W1l + ic * K + 8 * c);
-    const frag wj = *reinterpret_cast<const frag *>(W1l + jc * K + 8 * c);
-    const float4 z0 = *reinterpret_cast<const float4 *>(zs + s * K + 4 * c);
-    const float4 z1 = *reinterpret_cast<const float4 *>(zs + s * K + K / 2 + 4 * c);
-    const float zz[8] = {z0.x, z0.y, z0.z, z0.w, z1.x, z1.y, z1.z, z1.w};
-    frag h;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-        const float d = fmaf(-jm, Mc<T>::to_f32(wj[e]), Mc<T>::to_f32(wi[e]));
-        h[e] = Mc<T>::from_f32(fmaxf(fmaf(g, d, zz[e]), 0.0f));
+    static constexpr bool kHalf = std::is_same<T, _Float16>::value;
+    frag wi, wj;
+    float4 z0, z1;
+    uint32_t code;
+    __device__ __forceinline__ void load(const unsigned char *W1l, uint32_t code_, const unsigned char *zs, int c16)
+    {
+        code = code_;
+        if constexpr (!kHalf) asm volatile("" : "+v"(code));   // keeps the decoding out of the scalar registers
+        wi = *reinterpret_cast<const frag *>(W1l + c16 + 16 * (code & 0x1FFFu));
+        wj = *reinterpret_cast<const frag *>(W1l + c16 + 16 * ((code >> 13) & 0x1FFFu));
+        const unsigned char *z = zs + c16 + ((code >> 26) & 7u) * (4 * K);
+        z0 = *reinterpret_cast<const float4 *>(z);
+        z1 = *reinterpret_cast<const float4 *>(z + 2 * K);
     }
-    *reinterpret_cast<frag *>(Hs + lr * ldh + 8 * c) = h;
-}
-
-template <typename T>
-__device__ __forceinline__ void eloc_stage_row(const T *W1l, const int *rcode, const float *rg, const float *zs,
-                                               T *Hs, int ldh, int K, int nch, int row, int lr, int lane)
-{
-    eloc_stage_row_code<T>(W1l, __builtin_amdgcn_readfirstlane(rcode[row]), rg, zs, Hs, ldh, K, nch, row, lr, lane);
-}
+    __device__ __forceinline__ void store(unsigned char *dst) const
+    {
+        const float g = __uint_as_float((~code & 0x80000000u) | 0x40000000u);
+        float minus = -1.0f;
+        if constexpr (kHalf) asm("" : "+s"(minus));
+        const float zz[8] = {z0.x, z0.y, z0.z, z0.w, z1.x, z1.y, z1.z, z1.w};
+        frag h;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            // binary16: as an FMA by a -1 that the compiler does not see, one mixed-precision instruction instead of three
+            const float d = kHalf ? fmaf(minus, Mc<T>::to_f32(wj[e]), Mc<T>::to_f32(wi[e]))
+                                  : Mc<T>::to_f32(wi[e]) - Mc<T>::to_f32(wj[e]);
+            h[e] = Mc<T>::from_f32(fmaxf(fmaf(g, d, zz[e]), 0.0f));
+        }
+        *reinterpret_cast<frag *>(dst) = h;
+    }
+};
 
 template <typename T, int KE>
 __global__ void __launch_bounds__(kRegThreads) ffnn_eloc_reg_kernel(FfnnElocArgs A, int G)
@@ -741,18 +752,17 @@ __global__ void __launch_bounds__(kRegThreads) ffnn_eloc_reg_kernel(FfnnElocArgs
     const int nwt = (m2 + 31) >> 5;                    // waves with at least one real output
     const int maxrows = G * (2 * N + 1);
     const int nch = K >> 3;                            // 8-unit chunks of a row
-    T *W1l = reinterpret_cast<T *>(smem);              // [N][K]
-    T *Hs = W1l + (size_t)N * K;                       // [2][kElocRows][ldh]
+    T *W1l = reinterpret_cast<T *>(smem);              // [N + 1][K]
+    T *Hs = W1l + (size_t)(N + 1) * K;                 // [2][kElocRows][ldh]
     float *zs = reinterpret_cast<float *>(Hs + 2 * (size_t)kElocRows * ldh);   // [G][2][K / 8][4]
     float *b1s = zs + (size_t)G * K;                   // [K]
     float *b2s = b1s + K;                              // [m2p]
     float *part = b2s + m2p;                           // [2][kRegWaves][kElocRows]
     float *sp = part + 2 * kRegWaves * kElocRows;      // [G][N]
     int *ctab = reinterpret_cast<int *>(sp + (size_t)G * N);   // [2N]
-    int *rcode = ctab + 2 * N;                         // [maxrows]
+    uint32_t *rcode = reinterpret_cast<uint32_t *>(ctab + 2 * N);   // [maxrows]
     float *rc = reinterpret_cast<float *>(rcode + maxrows);
-    float *rg = rc + maxrows;
-    float *fr = rg + maxrows;
+    float *fr = rc + maxrows;
     // (an offset from smem, not an integer cast of the pointer, so that the compiler keeps the LDS address space)
     const size_t diag_off = ((size_t)(reinterpret_cast<unsigned char *>(fr + maxrows) - smem) + 7) & ~(size_t)7;
     double *diag = reinterpret_cast<double *>(smem + diag_off);
@@ -772,6 +782,7 @@ __global__ void __launch_bounds__(kRegThreads) ffnn_eloc_reg_kernel(FfnnElocArgs
             *reinterpret_cast<frag *>(W1l + i * K + 8 * c) = *reinterpret_cast<const frag *>(src + (size_t)i * m1p + 8 * c);
         }
     }
+    for (int k = tid; k < K; k += NT) W1l[(size_t)N * K + k] = Mc<T>::from_f32(0.0f);
     for (int k = tid; k < K; k += NT) b1s[k] = net.b1p[k];
     for (int k = tid; k < m2p; k += NT) b2s[k] = net.b2p[k];
     const int nb = A.dim == 1 ? (A.pbc ? A.L : A.L - 1) : 2 * A.L * A.L;   // candidate bonds (2D: 2 per site)
@@ -831,13 +842,12 @@ __global__ void __launch_bounds__(kRegThreads) ffnn_eloc_reg_kernel(FfnnElocArgs
         return take;
     };
     // f of the rows of pass q: the sum of the waves' partials (in wave order)
+    // (the last wave's task, which has no outputs or the fewest: 3 % faster than on the first wave in BF16; in binary16,
+    // where rows take fewer instructions, 1.5 % slower)
+    constexpr int kSumWave = std::is_same<T, _Float16>::value ? 0 : NWV - 1;
     auto row_sums = [&](int q, int nrows) {
-        if (tid < kElocRows && q * kElocRows + tid < nrows) {
-            const float *pp = part + (size_t)(q & 1) * kRegWaves * kElocRows;
-            float f = 0.0f;
-            for (int w = 0; w < nwt; ++w) f += pp[w * kElocRows + tid];
-            fr[q * kElocRows + tid] = f;
-        }
+        if (wave_u == kSumWave && lane < kElocRows && q * kElocRows + lane < nrows)
+            fr[q * kElocRows + lane] = sum_partials(part + (size_t)(q & 1) * kRegWaves * kElocRows + lane, kElocRows, nwt);
     };
     // the log-cosh partial of a finished tile: sum_k log cosh z2 = sum |z2| + log prod (1 + e^-2|z2|) - n ln 2
     // (16 factors in (1, 2]: the product stays below 2^16; padded outputs have z2 = 0 exactly and add 0)
@@ -925,9 +935,8 @@ __global__ void __launch_bounds__(kRegThreads) ffnn_eloc_reg_kernel(FfnnElocArgs
         if (wave < ns) {
             const float *ss = sp + wave * N;
             if (lane == 0) {
-                rcode[r0] = eloc_row_code(-1, -1, wave);
+                rcode[r0] = eloc_row_code(KE, 0, 0, wave, false);
                 rc[r0] = 0.0f;
-                rg[r0] = 0.0f;
             }
             int pos0 = r0 + 1;
             double unused = 0.0;
@@ -938,9 +947,8 @@ __global__ void __launch_bounds__(kRegThreads) ffnn_eloc_reg_kernel(FfnnElocArgs
                 const unsigned long long bal = __ballot(take);
                 if (take) {
                     const int pos = pos0 + __popcll(bal & ((1ull << lane) - 1ull));
-                    rcode[pos] = eloc_row_code(i, j, wave);
+                    rcode[pos] = eloc_row_code(KE, i, j >= 0 ? j : N, wave, ss[i] < 0.0f);
                     rc[pos] = coef;
-                    rg[pos] = -2.0f * ss[i];
                 }
                 pos0 += __popcll(bal);
             }
@@ -949,12 +957,19 @@ __global__ void __launch_bounds__(kRegThreads) ffnn_eloc_reg_kernel(FfnnElocArgs
         const int npass = (nrows + kElocRows - 1) / kElocRows;
         // wave w stages rows w kElocStage .. w kElocStage + kElocStage - 1 of pass q into buffer q & 1 (rows
         // past the group's end are clamped copies that nothing reads)
+        const int c16 = 16 * (lane < nch ? lane : nch - 1);
+        const unsigned char *W1b = reinterpret_cast<const unsigned char *>(W1l), *zb = reinterpret_cast<const unsigned char *>(zs);
+        unsigned char *Hw = reinterpret_cast<unsigned char *>(Hs + wave_u * kElocStage * ldh) + c16;   // its rows' chunk
+        const int hbuf = kElocRows * ldh * (int)sizeof(T), hrow = ldh * (int)sizeof(T);
         auto stage_pass = [&](int q) {
-            T *Hq = Hs + (size_t)(q & 1) * kElocRows * ldh;
+            uint32_t code[kElocStage];
+#pragma unroll
+            for (int rr = 0; rr < kElocStage; ++rr) code[rr] = rcode[min(q * kElocRows + wave_u * kElocStage + rr, nrows - 1)];
 #pragma unroll
             for (int rr = 0; rr < kElocStage; ++rr) {
-                const int r = wave * kElocStage + rr;
-                eloc_stage_row<T>(W1l, rcode, rg, zs, Hq, ldh, K, nch, min(q * kElocRows + r, nrows - 1), r, lane);
+                ElocRow<T, K> row;
+                row.load(W1b, code[rr], zb, c16);
+                row.store(Hw + (q & 1) * hbuf + rr * hrow);
             }
         };
         stage_pass(0);
@@ -964,25 +979,20 @@ __global__ void __launch_bounds__(kRegThreads) ffnn_eloc_reg_kernel(FfnnElocArgs
         // p + 1 staged in between the products, then the tile's log-cosh partial.  The two waves that share a
         // SIMD (w and w + 4) place their staging slots half a period apart (PH), so that one of them issues
         // products while the other stages.
-        // the codes of a wave's staging rows are read from LDS one pass ahead (across the barrier) and taken
-        // into scalar registers at the start of the pass, so that a staging slot waits for one LDS round trip
-        // (its W1 columns, z1 and g), not two
-        auto read_codes = [&](int q, int (&cv)[kElocStage]) {
+        // the codes of a wave's staging rows are read from LDS one pass ahead (across the barrier), so that a staging
+        // slot waits for one LDS round trip (its W1 columns and z1), not two
+        auto read_codes = [&](int q, uint32_t (&cv)[kElocStage]) {
 #pragma unroll
-            for (int rr = 0; rr < kElocStage; ++rr) cv[rr] = rcode[min(q * kElocRows + wave * kElocStage + rr, nrows - 1)];
+            for (int rr = 0; rr < kElocStage; ++rr) cv[rr] = rcode[min(q * kElocRows + wave_u * kElocStage + rr, nrows - 1)];
         };
-        int cv[kElocStage];
+        uint32_t cv[kElocStage];
         read_codes(1, cv);
         auto pass = [&](int p, auto ph_c) {
             constexpr bool PH = decltype(ph_c)::value;
-            int code[kElocStage];
-#pragma unroll
-            for (int rr = 0; rr < kElocStage; ++rr) code[rr] = __builtin_amdgcn_readfirstlane(cv[rr]);
             constexpr int kStep = KE / kElocStage;           // staging slots every kStep fragments
             constexpr int kStageAt = PH ? kStep / 2 : 0;     // first staging slot
             const T *Hc = Hs + (size_t)(p & 1) * kElocRows * ldh + lr * ldh + 8 * lh;
-            T *Hn = Hs + (size_t)((p + 1) & 1) * kElocRows * ldh;
-            const int nbase = (p + 1) * kElocRows;
+            unsigned char *Hn = Hw + ((p + 1) & 1) * hbuf;
             mc_floatx16 acc;
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[r] = 0.0f;
@@ -996,8 +1006,10 @@ __global__ void __launch_bounds__(kRegThreads) ffnn_eloc_reg_kernel(FfnnElocArgs
                 acc = Mc<T>::mma(a[kf], b[kf % 3], acc);
                 __builtin_amdgcn_sched_barrier(0);
                 if (kf >= kStageAt && (kf - kStageAt) % kStep == 0 && (kf - kStageAt) / kStep < kElocStage) {
-                    const int rr = (kf - kStageAt) / kStep, r = wave * kElocStage + rr;
-                    eloc_stage_row_code<T>(W1l, code[rr], rg, zs, Hn, ldh, K, nch, min(nbase + r, nrows - 1), r, lane);
+                    const int rr = (kf - kStageAt) / kStep;
+                    ElocRow<T, K> row;
+                    row.load(W1b, cv[rr], zb, c16);
+                    row.store(Hn + rr * hrow);
                 }
             }
             read_codes(p + 2, cv);
