@@ -96,6 +96,14 @@ nqs_status crbm_build_copy(nqs_model *m, int dtype, hipStream_t stream)
 // multiplied (renormalised every four factors) and take one logarithm.  The
 // (C, S) column of the next proposal is loaded while the current one is
 // decided; the table sits in LDS when it fits, else it is read through L2.
+//
+// With one or two waves per SIMD a step is its wave's chain of instructions (8.3
+// cycles where one needs the one before): broadcasts run two proposals ahead, the
+// next proposal's spin is read before this one's decision and corrected for it,
+// all but the last FMA of the move's sinh is formed while the decision's sum is
+// under way, and the steps between two refreshes or draws run without tests.
+// 3,000 chains of 16, 64 and 100 sites with as many units: 517, 839 and 755 ns a
+// step before (the second with 128 units), 404, 781 and 690 ns now.
 
 struct CrbmSampleArgs {
     CrbmDev net;
@@ -251,36 +259,39 @@ __global__ void __launch_bounds__(G == 16 ? 256 : 512) crbm_sample_kernel(CrbmSa
     int in_sweep = 0;
     int64_t sweep = 0;
 
-    // proposal pipeline: `cur` covers steps [base, base+G), `nxt` the next G
+    // proposal pipeline: `cur` covers steps [base, base+G), `nxt` the next G; a step starts with its own and the next
+    // proposal in registers and broadcasts the one after
     uint64_t base = A.step_offset;
     CrbmProp cur = crbm_prop(A.net, base + gl, gid, A.inst, key0, key1);
     CrbmProp nxt = crbm_prop(A.net, base + G + gl, gid, A.inst, key0, key1);
     int p = 0;
-    int i_c = (int)group_bcast<G>(cur.i, 0);
-    uint32_t ub_c = group_bcast<G>(cur.ub, 0);
+    int i_c = (int)group_bcast<G>(cur.i, 0), i_n = (int)group_bcast<G>(cur.i, 1);
     float l2u_c = __uint_as_float(group_bcast<G>(__float_as_uint(cur.l2u), 0));
+    float l2u_n = __uint_as_float(group_bcast<G>(__float_as_uint(cur.l2u), 1));
     float a2_c = __uint_as_float(group_bcast<G>(__float_as_uint(cur.a2), 0));
+    float a2_n = __uint_as_float(group_bcast<G>(__float_as_uint(cur.a2), 1));
+    bool up = (group_bcast<G>(word, i_c >> 5) >> (i_c & 31)) & 1u;   // spin of site i_c
     float4 csA[K], csB[K];
-    if constexpr (LDS_TAB) crbm_column<G, K>(s_ctab, i_c, M, gl, last_off, last_ok, csA);
-    else crbm_column<G, K>(A.net.CS, i_c, M, gl, last_off, last_ok, csA);
+    auto column = [&](int i, float4 (&cs)[K]) {
+        if constexpr (LDS_TAB) crbm_column<G, K>(s_ctab, i, M, gl, last_off, last_ok, cs);
+        else crbm_column<G, K>(A.net.CS, i, M, gl, last_off, last_ok, cs);
+    };
+    column(i_c, csA);
 
     // one proposal: evaluate with cs_c (column of i_c), prefetch the next column into cs_n
     auto step = [&](int64_t k, float4 (&cs_c)[K], float4 (&cs_n)[K]) {
-        const int pn = p + 1;
-        const CrbmProp &src = pn < G ? cur : nxt;
-        const int pl = pn < G ? pn : 0;
-        const int i_n = (int)group_bcast<G>(src.i, pl);
-        const uint32_t ub_n = group_bcast<G>(src.ub, pl);
-        const float l2u_n = __uint_as_float(group_bcast<G>(__float_as_uint(src.l2u), pl));
-        const float a2_n = __uint_as_float(group_bcast<G>(__float_as_uint(src.a2), pl));
-        if constexpr (LDS_TAB) crbm_column<G, K>(s_ctab, i_n, M, gl, last_off, last_ok, cs_n);
-        else crbm_column<G, K>(A.net.CS, i_n, M, gl, last_off, last_ok, cs_n);
+        column(i_n, cs_n);
+        // the spin of the next proposal's site before this one's decision, and the proposal after the next
+        const uint32_t wbits_n = group_bcast<G>(word, i_n >> 5);
+        const bool in_cur = p + 2 < G;
+        const int pl = in_cur ? p + 2 : p + 2 - G;
+        const int i_f = (int)group_bcast<G>(in_cur ? cur.i : nxt.i, pl);
+        const float l2u_f = __uint_as_float(group_bcast<G>(__float_as_uint(in_cur ? cur.l2u : nxt.l2u), pl));
+        const float a2_f = __uint_as_float(group_bcast<G>(__float_as_uint(in_cur ? cur.a2 : nxt.a2), pl));
 
         // proposal k: flip site i_c
-        const uint32_t wbits = group_bcast<G>(word, i_c >> 5);
-        const bool up = (wbits >> (i_c & 31)) & 1u;
         const float si = up ? 1.0f : -1.0f;
-        float2 nn[K];
+        float2 nn[K], ns[K];
         float prod = 1.0f;
         int e2 = 0;
 #pragma unroll
@@ -300,44 +311,74 @@ __global__ void __launch_bounds__(G == 16 ? 256 : 512) crbm_sample_kernel(CrbmSa
             }
         }
         const float lnew = __builtin_amdgcn_logf(prod) + (float)e2;     // log2 prod |n|^2
-        const float d2 = group_sum_uniform<G>(lnew - lpart) + (up ? -a2_c : a2_c);
+        float d2 = lnew - lpart;
+        // the move's s_j C - s_i c_j S, all but its last FMA, while the sum over the lanes is under way
+#pragma unroll
+        for (int q = 0; q < K; ++q) {
+            const float4 t = cs_c[q];
+            const float spx = si * t.z, spy = si * t.w;
+            float sx = fmaf(sh[q].x, t.x, -sh[q].y * t.y);                  // s C
+            float sy = fmaf(sh[q].x, t.y, sh[q].y * t.x);
+            ns[q] = make_float2(fmaf(cc[q].y, spy, sx), fmaf(-cc[q].y, spx, sy));   // - c (s_i S), first half
+            asm volatile("" : "+v"(ns[q].x), "+v"(ns[q].y));               // not sunk below the decision
+        }
+        d2 = group_sum_uniform<G>(d2) + (up ? -a2_c : a2_c);
         const bool accept = l2u_c < d2;                                 // NaN rejects
         if (accept) {
 #pragma unroll
             for (int q = 0; q < K; ++q) {
                 const float4 t = cs_c[q];
                 const float spx = si * t.z, spy = si * t.w;
-                float sx = fmaf(sh[q].x, t.x, -sh[q].y * t.y);              // s C
-                float sy = fmaf(sh[q].x, t.y, sh[q].y * t.x);
-                sx = fmaf(-cc[q].x, spx, fmaf(cc[q].y, spy, sx));           // - c (s_i S)
-                sy = fmaf(-cc[q].x, spy, fmaf(-cc[q].y, spx, sy));
-                sh[q] = make_float2(sx, sy);
+                sh[q] = make_float2(fmaf(-cc[q].x, spx, ns[q].x), fmaf(-cc[q].x, spy, ns[q].y));
                 cc[q] = nn[q];
             }
             lpart = lnew;
             if (gl == (i_c >> 5)) word ^= 1u << (i_c & 31);
             ++acc;
         }
-        if (traced && gl == 0) {
-            const size_t idx = (size_t)c * (size_t)total + (size_t)k;
-            A.tr_site[idx] = i_c | (0xFFFF << 16);
-            A.tr_ubits[idx] = ub_c;
-            A.tr_delta[idx] = d2 * 0.69314718055994531f;
-            A.tr_acc[idx] = accept ? 1 : 0;
+        if (traced) {
+            const uint32_t ub_c = group_bcast<G>(cur.ub, p);
+            if (gl == 0) {
+                const size_t idx = (size_t)c * (size_t)total + (size_t)k;
+                A.tr_site[idx] = i_c | (0xFFFF << 16);
+                A.tr_ubits[idx] = ub_c;
+                A.tr_delta[idx] = d2 * 0.69314718055994531f;
+                A.tr_acc[idx] = accept ? 1 : 0;
+            }
         }
         // advance the pipeline
+        up = (bool)((wbits_n >> (i_n & 31)) & 1u) != (accept && i_n == i_c);
         i_c = i_n;
-        ub_c = ub_n;
         l2u_c = l2u_n;
         a2_c = a2_n;
-        p = pn;
+        i_n = i_f;
+        l2u_n = l2u_f;
+        a2_n = a2_f;
+        ++p;
+    };
+
+    for (int64_t k = 0; k < total;) {
+        // the steps up to the end of the sweep or of the drawn proposals
+        const int run = min(sw - in_sweep, G - p);
+        int r = 0;
+        for (; r + 1 < run; r += 2) {
+            step(k + r, csA, csB);
+            step(k + r + 1, csB, csA);
+        }
+        if (r < run) {
+            step(k + r, csA, csB);
+#pragma unroll
+            for (int q = 0; q < K; ++q) csA[q] = csB[q];
+        }
+        k += run;
+        in_sweep += run;
         if (p == G) {
             p = 0;
             base += G;
             cur = nxt;
             nxt = crbm_prop(A.net, base + G + gl, gid, A.inst, key0, key1);
         }
-        if (++in_sweep == sw) {
+        if (in_sweep == sw) {
             in_sweep = 0;
             const int64_t out = sweep - A.n_burnin;
             const bool need_f = A.logpsi != nullptr && out >= 0;
@@ -353,14 +394,7 @@ __global__ void __launch_bounds__(G == 16 ? 256 : 512) crbm_sample_kernel(CrbmSa
             }
             ++sweep;
         }
-    };
-
-    int64_t k = 0;
-    for (; k + 1 < total; k += 2) {
-        step(k, csA, csB);
-        step(k + 1, csB, csA);
     }
-    if (k < total) step(k, csA, csB);
 
     if (gl < NW) {
         int8_t *dst = A.chain_state + (size_t)c * N + gl * 32;
@@ -372,12 +406,19 @@ __global__ void __launch_bounds__(G == 16 ? 256 : 512) crbm_sample_kernel(CrbmSa
 
 // ---- TFIM local energies, complex: B samples per workgroup ----
 //
-// Each table element (W for theta, (C, S) for the flip ratios) read from L2
-// serves the B samples of the workgroup.  Per sample: t = tanh theta in LDS;
-// one thread per site forms the complex flip ratios of all B samples,
-// exp(-2 a_i s_i) prod_j (C - s_i t_j S), with frexp renormalisation every 8
-// factors, and stores them in FP64; then one wave per sample sums ratios and
-// diagonal bonds in a fixed order.
+// Per sample: t = tanh theta in LDS; one thread per site and kCrbmSB samples
+// forms their complex flip ratios, exp(-2 a_i s_i) prod_j (C - s_i t_j S), with
+// frexp renormalisation every 8 factors, and stores them in FP64; then one wave
+// per sample sums ratios and diagonal bonds in a fixed order.  A table element
+// (W for theta, (C, S) for the ratios) is read once per kCrbmSB samples, mostly
+// from L1 where the workgroup's other samples want it too.
+//
+// Bound by the vector unit (about 12 instructions per sample, site and unit)
+// once enough waves hide a factor's chain of dependent products.  100 x 200,
+// 30,000 samples: 277 us with four samples per thread and eight per workgroup
+// (12 waves on a CU); 734 us with sixteen samples per thread (4 waves, the table
+// elements one at a time).
+constexpr int kCrbmSB = 4;   // samples per thread (1 where the LDS holds fewer)
 
 __device__ inline double crbm_bonds(const float *s, int i, int dim, int L, int pbc)
 {
@@ -401,10 +442,11 @@ __host__ __device__ inline size_t crbm_eloc_lds(int B, int N, int M)
     return sizeof(double2) * (size_t)B * N + sizeof(float2) * (size_t)B * M + sizeof(float) * (size_t)B * N;
 }
 
-template <int B>
+template <int SB>
 __global__ void __launch_bounds__(256) crbm_eloc_tfim_kernel(CrbmDev net, const int8_t *__restrict__ samples,
-                                                             int64_t n, int dim, int L, int pbc, double J, double h,
-                                                             double *__restrict__ eloc_re, double *__restrict__ eloc_im)
+                                                             int64_t n, int B, int dim, int L, int pbc, double J,
+                                                             double h, double *__restrict__ eloc_re,
+                                                             double *__restrict__ eloc_im)
 {
     extern __shared__ double2 crbm_esm[];
     const int N = net.N, M = net.M, tid = threadIdx.x, nt = blockDim.x;
@@ -413,65 +455,84 @@ __global__ void __launch_bounds__(256) crbm_eloc_tfim_kernel(CrbmDev net, const 
     float *s = reinterpret_cast<float *>(tt + (size_t)B * M);           // [B][N]
     for (int64_t k0 = (int64_t)blockIdx.x * B; k0 < n; k0 += (int64_t)gridDim.x * B) {
         const int nb = (int)(n - k0 < B ? n - k0 : B);
+        const int ng = (nb + SB - 1) / SB;   // groups of SB samples
         for (int e = tid; e < B * N; e += nt) {
             const int bb = e / N, i = e - bb * N;
             s[e] = bb < nb ? (float)samples[(k0 + bb) * N + i] : 1.0f;
         }
         __syncthreads();
-        for (int j = tid; j < M; j += nt) {
-            float2 th[B];
+        for (int t = tid; t < M * ng; t += nt) {
+            const int g = t / M, j = t - g * M;
+            const float *sg = s + g * SB * N;
+            float2 th[SB];
             const float2 bj = net.b[j];
 #pragma unroll
-            for (int bb = 0; bb < B; ++bb) th[bb] = bj;
+            for (int bb = 0; bb < SB; ++bb) th[bb] = bj;
+#pragma unroll 8
             for (int i = 0; i < N; ++i) {
                 const float2 w = net.Wt[(int64_t)i * M + j];
 #pragma unroll
-                for (int bb = 0; bb < B; ++bb) {
-                    const float sb = s[bb * N + i];
+                for (int bb = 0; bb < SB; ++bb) {
+                    const float sb = sg[bb * N + i];
                     th[bb].x = fmaf(w.x, sb, th[bb].x);
                     th[bb].y = fmaf(w.y, sb, th[bb].y);
                 }
             }
 #pragma unroll
-            for (int bb = 0; bb < B; ++bb) tt[bb * M + j] = ctanh(th[bb]);
+            for (int bb = 0; bb < SB; ++bb) tt[(g * SB + bb) * M + j] = ctanh(th[bb]);
         }
         __syncthreads();
-        for (int i = tid; i < N; i += nt) {
-            float2 pr[B];
-            int e2[B];
-            float si[B];
+        for (int t = tid; t < N * ng; t += nt) {
+            const int g = t / N, i = t - g * N;
+            const float2 *tg = tt + g * SB * M;
+            float2 pr[SB];
+            int e2[SB];
+            float si[SB];
 #pragma unroll
-            for (int bb = 0; bb < B; ++bb) {
+            for (int bb = 0; bb < SB; ++bb) {
                 pr[bb] = make_float2(1.0f, 0.0f);
                 e2[bb] = 0;
-                si[bb] = s[bb * N + i];
+                si[bb] = s[(g * SB + bb) * N + i];
             }
-            for (int j = 0; j < M; ++j) {
-                const float4 cs = net.CSt[(int64_t)j * N + i];
+            auto factor = [&](float4 cs, int j) {
 #pragma unroll
-                for (int bb = 0; bb < B; ++bb) {
-                    const float2 ts = cmul(tt[bb * M + j], make_float2(cs.z, cs.w));
+                for (int bb = 0; bb < SB; ++bb) {
+                    const float2 ts = cmul(tg[bb * M + j], make_float2(cs.z, cs.w));
                     pr[bb] = cmul(pr[bb], make_float2(fmaf(-si[bb], ts.x, cs.x), fmaf(-si[bb], ts.y, cs.y)));
                 }
-                if ((j & 7) == 7) {
+            };
+            int j = 0;
+            for (; j + 8 <= M; j += 8) {
+                float4 cs[8];
 #pragma unroll
-                    for (int bb = 0; bb < B; ++bb) {
-                        int e;
-                        (void)frexpf(fmaxf(fabsf(pr[bb].x), fabsf(pr[bb].y)), &e);
-                        pr[bb].x = ldexpf(pr[bb].x, -e);
-                        pr[bb].y = ldexpf(pr[bb].y, -e);
-                        e2[bb] += e;
-                    }
+                for (int u = 0; u < 8; ++u) cs[u] = net.CSt[(int64_t)(j + u) * N + i];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) factor(cs[u], j + u);
+#pragma unroll
+                for (int bb = 0; bb < SB; ++bb) {
+                    int e;
+                    (void)frexpf(fmaxf(fabsf(pr[bb].x), fabsf(pr[bb].y)), &e);
+                    pr[bb].x = ldexpf(pr[bb].x, -e);
+                    pr[bb].y = ldexpf(pr[bb].y, -e);
+                    e2[bb] += e;
                 }
             }
+            for (; j < M; ++j) factor(net.CSt[(int64_t)j * N + i], j);
+            // exp(-2 a_i s) for both spins
             const float2 ai = net.a[i];
+            double mag[2], sn[2], cn[2];
 #pragma unroll
-            for (int bb = 0; bb < B; ++bb) {
-                const double mg = exp(-2.0 * (double)ai.x * si[bb]) * ldexp(1.0, e2[bb]);
-                double sn, cn;
-                sincos(-2.0 * (double)ai.y * si[bb], &sn, &cn);
-                const double pre = mg * cn, pim = mg * sn;
-                rat[bb * N + i] = make_double2(pre * pr[bb].x - pim * pr[bb].y, pre * pr[bb].y + pim * pr[bb].x);
+            for (int v = 0; v < 2; ++v) {
+                const float sv = v ? 1.0f : -1.0f;
+                mag[v] = exp(-2.0 * (double)ai.x * sv);
+                sincos(-2.0 * (double)ai.y * sv, &sn[v], &cn[v]);
+            }
+#pragma unroll
+            for (int bb = 0; bb < SB; ++bb) {
+                const bool up = si[bb] > 0.0f;
+                const double mg = (up ? mag[1] : mag[0]) * ldexp(1.0, e2[bb]);
+                const double pre = mg * (up ? cn[1] : cn[0]), pim = mg * (up ? sn[1] : sn[0]);
+                rat[(g * SB + bb) * N + i] = make_double2(pre * pr[bb].x - pim * pr[bb].y, pre * pr[bb].y + pim * pr[bb].x);
             }
         }
         __syncthreads();
@@ -574,7 +635,10 @@ nqs_status crbm_sample(nqs_model *m, const nqs_sample_cfg &cfg, int8_t *chain_st
     const int max_threads = G == 16 ? 256 : 512;
     const int blocks_per_cu = lds ? (int)std::max<size_t>(1, std::min<size_t>(8, kLds / tab_bytes)) : 8;
     const int64_t slots = (int64_t)device_cus() * blocks_per_cu;
-    const int cpb = (int)std::min<int64_t>(max_threads / G, std::max<int64_t>(1, (cfg.n_chains + slots - 1) / slots));
+    // whole waves once there are more chains than SIMDs: 100 x 200, G = 32, ten sweeps and two of burn-in, 2,048 chains
+    // 1,231 us with one chain per wave, 905 with two (1,024 chains: 893 us with one)
+    const int64_t least = cfg.n_chains > 4 * (int64_t)device_cus() ? 64 / G : 1;
+    const int cpb = (int)std::min<int64_t>(max_threads / G, std::max<int64_t>(least, (cfg.n_chains + slots - 1) / slots));
     const int64_t blocks = (cfg.n_chains + cpb - 1) / cpb;
     if (blocks > INT32_MAX) return set_error(NQS_EINVAL, "too many chains");
     const size_t lds_bytes = lds ? tab_bytes : 0;
@@ -594,29 +658,24 @@ nqs_status crbm_local_energy(nqs_model *m, const nqs_ham_desc &ham, const int8_t
     nqs_status st = ensure_copy(m, dtype, stream);
     if (st != NQS_OK) return st;
     const CrbmDev &net = m->copies[dtype].crbm;
-    // samples per workgroup: the largest of 16, 8, 4, 2, 1 whose LDS stays within 64 KB
-    int B = 16;
-    while (B > 1 && crbm_eloc_lds(B, net.N, net.M) > 64 * 1024) B /= 2;
+    // samples per workgroup: two groups, one, or one sample, whose LDS stays within 64 KB, else 160 KB; threads for two
+    // groups' sites (30,000 samples of 64 sites, 128 units: 120 us with 128 threads, 156 with 256; 100 sites, 200 units:
+    // 323 and 277 us)
+    int B = 2 * kCrbmSB;
+    if (crbm_eloc_lds(B, net.N, net.M) > 64 * 1024) B = kCrbmSB;
+    if (crbm_eloc_lds(B, net.N, net.M) > 160 * 1024) B = 1;
     const size_t lds = crbm_eloc_lds(B, net.N, net.M);
     if (lds > 160 * 1024) return set_error(NQS_EUNSUPPORTED, "complex RBM too large for the local-energy kernel");
     if (n == 0) return NQS_OK;
-    const int threads = net.N <= 128 ? 128 : 256;
-    const int64_t blocks = std::min<int64_t>((n + B - 1) / B, (int64_t)device_cus() * 8);
-    switch (B) {
-#define NQS_CE(BB)                                                                                                   \
-    case BB:                                                                                                         \
-        allow_lds(crbm_eloc_tfim_kernel<BB>, lds);                                                                   \
-        hipLaunchKernelGGL(crbm_eloc_tfim_kernel<BB>, dim3((unsigned)blocks), dim3(threads), lds, stream, net,       \
-                           samples, n, ham.dim, ham.L, ham.pbc, ham.J, ham.h, eloc_re, eloc_im);                     \
-        break;
-        NQS_CE(16) NQS_CE(8) NQS_CE(4) NQS_CE(2)
-#undef NQS_CE
-    default:
-        allow_lds(crbm_eloc_tfim_kernel<1>, lds);
-        hipLaunchKernelGGL(crbm_eloc_tfim_kernel<1>, dim3((unsigned)blocks), dim3(threads), lds, stream, net, samples,
-                           n, ham.dim, ham.L, ham.pbc, ham.J, ham.h, eloc_re, eloc_im);
-        break;
-    }
+    const int threads = 2 * net.N <= 128 ? 128 : 256;
+    const int64_t blocks = std::min<int64_t>((n + B - 1) / B, (int64_t)device_cus() * 32);
+    auto launch = [&](auto kernel) {
+        allow_lds(kernel, lds);
+        hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(threads), lds, stream, net, samples, n, B, ham.dim, ham.L,
+                           ham.pbc, ham.J, ham.h, eloc_re, eloc_im);
+    };
+    if (B == 1) launch(crbm_eloc_tfim_kernel<1>);
+    else launch(crbm_eloc_tfim_kernel<kCrbmSB>);
     NQS_HIP_TRY(hipGetLastError());
     return NQS_OK;
 }
