@@ -143,13 +143,19 @@ __device__ __forceinline__ float readlane_f32(float v, int lane)
 }
 
 template <int G>
-__device__ __forceinline__ float group_sum_uniform(float v)
+__device__ __forceinline__ float group_sum_uniform(float v0)
 {
-    v = group_scan_total<G>(v);
+    const float v = group_scan_total<G>(v0);
     if constexpr (G == 16) {
         return dpp_f32<0x15F, 0xF, 0xF>(v);   // row_newbcast:15: every lane of the row takes lane 15's total
     } else if constexpr (G == 64) {
         return readlane_f32(v, 63);
+    } else if constexpr (G == 32) {
+        // each row's total in all its lanes, then the two rows exchanged (no scalar register: a wave issues scalar
+        // instructions and what waits for them 8 cycles apart)
+        const uint32_t x = __float_as_uint(dpp_f32<0x15F, 0xF, 0xF>(group_scan_total<16>(v0)));
+        const auto r = __builtin_amdgcn_permlane16_swap(x, x, false, false);
+        return __uint_as_float(r[1]) + __uint_as_float(r[0]);
     } else {
         const int grp = (int)(threadIdx.x & 63) / G;
         float r = readlane_f32(v, G - 1);
@@ -170,8 +176,15 @@ __device__ __forceinline__ uint32_t group_bcast(uint32_t v, int p)
         return (uint32_t)__builtin_amdgcn_readlane((int)v, p);
     } else {
         const int base = (int)(threadIdx.x & 63) & ~(G - 1);
-        return (uint32_t)__shfl((int)v, base + p, 64);
+        return (uint32_t)__builtin_amdgcn_ds_bpermute((base + p) << 2, (int)v);
     }
+}
+// the same for lane at / 4 of the group, at a multiple of 4 (base4: 4 x the group's first lane)
+template <int G>
+__device__ __forceinline__ uint32_t group_bcast4(uint32_t v, int base4, int at)
+{
+    if constexpr (G == 64) return (uint32_t)__builtin_amdgcn_readlane((int)v, __builtin_amdgcn_readfirstlane(at) >> 2);
+    else return (uint32_t)__builtin_amdgcn_ds_bpermute(base4 | at, (int)v);
 }
 
 // Place of element (r, c) of an operand matrix (rows x Kp, row-contracted) kept in the order of the 32-row matrix

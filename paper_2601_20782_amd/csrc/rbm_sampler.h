@@ -23,9 +23,11 @@
 // proposals ahead, the next proposal's spin is read before this one's decision
 // and corrected for it, what an accepted move needs is formed while the
 // decision's sum is under way, and the steps between two refreshes or draws run
-// without tests.  1,024 chains of 100 sites with 100 and 200 units: 361 and 400 ns
-// a step before, 275 and 329 now; 16,384 chains, bound by the vector unit: 1,008
-// and 1,627 before, 1,006 and 1,598 now.
+// without tests.  With more it is the number of instructions: -s_j is kept, not
+// s_j, places are kept in bytes, the group's sum does not pass through scalar
+// registers.  1,024 chains of 100 sites with 100 and 200 units: 361 and 400 ns a
+// step before, 263 and 291 now; 16,384 chains: 1,005 and 1,638 before, 863 and
+// 1,402 now.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -114,7 +116,7 @@ __device__ __forceinline__ float rbm_refresh(const RbmDev &net, uint32_t word, i
 }
 
 // Proposals of one batch: lane g of a group holds site, log2 u, u bits and the
-// bias term of proposal (batch start + g).
+// negative bias term of proposal (batch start + g).
 struct PropBatch {
     uint32_t i, ub;
     float l2u, a2;
@@ -128,18 +130,8 @@ __device__ __forceinline__ PropBatch make_batch(const RbmDev &net, uint64_t step
     pb.i = (uint32_t)index_from_word(rb.r0, net.N);
     pb.ub = rb.r2 >> 8;
     pb.l2u = __builtin_amdgcn_logf((float)pb.ub * 5.9604644775390625e-8f);   // log2(u), u = ub * 2^-24
-    pb.a2 = net.a2[pb.i];
+    pb.a2 = -net.a2[pb.i];
     return pb;
-}
-
-template <int G, int K, bool LDS_TAB>
-__device__ __forceinline__ void load_column(const float2 *__restrict__ tab, int i, int M, int gl, int last_off,
-                                            bool last_ok, float2 (&cs)[K])
-{
-    const int base = i * M + gl;
-#pragma unroll
-    for (int k = 0; k < K - 1; ++k) cs[k] = tab[base + k * G];
-    cs[K - 1] = tab[last_ok ? base + (K - 1) * G : last_off];
 }
 
 // zeta(x) / ln 2 of the noisy target, log pi~ = log pi + zeta: Philox4x32-10 with
@@ -169,8 +161,11 @@ __device__ __forceinline__ void rbm_run_chain(const RbmSampleArgs &A, int64_t c,
     const uint32_t gid = A.chain_id_offset + (uint32_t)c;
     const uint32_t key0 = (uint32_t)A.seed, key1 = (uint32_t)(A.seed >> 32);
     const int NW = (N + 31) >> 5;
-    const int last_off = N * M;
     const bool last_ok = gl + (K - 1) * G < M;
+    const int base4 = ((int)(threadIdx.x & 63) & ~(G - 1)) << 2;
+    // byte offsets of a column's entries of this lane: its first, and its last or the neutral entry behind the table
+    const int col_step = 8 * M, col_first = 8 * gl;
+    const int last_step = last_ok ? 8 * M : 0, last_first = last_ok ? 8 * (gl + (K - 1) * G) : 8 * N * M;
 
     uint32_t word = 0;
     if (gl < NW) {
@@ -185,9 +180,18 @@ __device__ __forceinline__ void rbm_run_chain(const RbmSampleArgs &A, int64_t c,
         }
     }
 
-    float cc[K], sh[K], lpart;
+    // cc: c_j, msh: -s_j (the sign that both update formulas take without a negation); down: the spin words, a bit set
+    // for a spin down
+    float cc[K], msh[K], lpart;
     const bool diag = TRACE && A.dg_drift != nullptr;
-    float f = rbm_refresh<G, K>(A.net, word, gl, cc, sh, lpart, diag);
+    auto refresh = [&](uint32_t up, bool want_f) {
+        const float r = rbm_refresh<G, K>(A.net, up, gl, cc, msh, lpart, want_f);
+#pragma unroll
+        for (int q = 0; q < K; ++q) msh[q] = -msh[q];
+        return r;
+    };
+    float f = refresh(word, diag);
+    uint32_t down = ~word;
     unsigned long long dg_nonfinite = 0, dg_acc0 = 0;
     uint32_t dg_run = 0, dg_longest = 0;
     float dg_f = f, dg_drift = 0.0f;   // log psi carried by the accepted log-ratios since the last refresh
@@ -232,11 +236,14 @@ __device__ __forceinline__ void rbm_run_chain(const RbmSampleArgs &A, int64_t c,
     PropBatch nxt = make_batch(A.net, base + G + gl, gid, A.inst, key0, key1);
     int p = 0;
     // sign bit of the current proposal's spin: 0 up, 2^31 down
-    uint32_t smask = (~group_bcast<G>(word, i_c >> 5) >> (i_c & 31)) << 31;
+    uint32_t smask = (group_bcast<G>(down, i_c >> 5) >> (i_c & 31)) << 31;
     float2 csA[K], csB[K];
     auto column = [&](int i, float2 (&cs)[K]) {
-        if constexpr (LDS_TAB) load_column<G, K, true>(s_tab, i, M, gl, last_off, last_ok, cs);
-        else load_column<G, K, false>(tab, i, M, gl, last_off, last_ok, cs);
+        const unsigned char *t = reinterpret_cast<const unsigned char *>(LDS_TAB ? s_tab : tab);
+        const float2 *col = reinterpret_cast<const float2 *>(t + (i * col_step + col_first));
+#pragma unroll
+        for (int q = 0; q < K - 1; ++q) cs[q] = col[q * G];
+        cs[K - 1] = *reinterpret_cast<const float2 *>(t + (i * last_step + last_first));
     };
     column(i_c, csA);
 
@@ -244,12 +251,12 @@ __device__ __forceinline__ void rbm_run_chain(const RbmSampleArgs &A, int64_t c,
     auto step = [&](int64_t k, float2 (&cs_c)[K], float2 (&cs_n)[K]) {
         column(i_n, cs_n);
         // the spin of the next proposal's site before this one's decision, and the proposal after the next
-        const uint32_t smask_b = (~group_bcast<G>(word, i_n >> 5) >> (i_n & 31)) << 31;
-        const int i_f = (int)group_bcast<G>(cur.i, p);
-        const float l2u_f = __uint_as_float(group_bcast<G>(__float_as_uint(cur.l2u), p));
-        const float a2_f = __uint_as_float(group_bcast<G>(__float_as_uint(cur.a2), p));
+        const uint32_t smask_b = (group_bcast4<G>(down, base4, (i_n >> 3) & ~3) >> (i_n & 31)) << 31;
+        const int i_f = (int)group_bcast4<G>(cur.i, base4, p << 2);
+        const float l2u_f = __uint_as_float(group_bcast4<G>(__float_as_uint(cur.l2u), base4, p << 2));
+        const float a2_f = __uint_as_float(group_bcast4<G>(__float_as_uint(cur.a2), base4, p << 2));
         uint32_t ub_f = 0u;
-        if constexpr (TRACE) ub_f = group_bcast<G>(cur.ub, p);
+        if constexpr (TRACE) ub_f = group_bcast4<G>(cur.ub, base4, p << 2);
 
         // proposal k: flip site i_c;  S' = s_i S by flipping the sign bit
         float sp[K], nn[K], mm[K];
@@ -258,7 +265,7 @@ __device__ __forceinline__ void rbm_run_chain(const RbmSampleArgs &A, int64_t c,
 #pragma unroll
         for (int q = 0; q < K; ++q) {
             sp[q] = __uint_as_float(__float_as_uint(cs_c[q].y) ^ smask);
-            nn[q] = fmaf(-sh[q], sp[q], cc[q] * cs_c[q].x);
+            nn[q] = fmaf(msh[q], sp[q], cc[q] * cs_c[q].x);
             prod *= nn[q];
             if ((q & 7) == 7 && q + 1 < K) {
                 int e;
@@ -266,7 +273,7 @@ __device__ __forceinline__ void rbm_run_chain(const RbmSampleArgs &A, int64_t c,
                 e2 += e;
             }
         }
-        const float lnew = __builtin_amdgcn_logf(prod) + (float)e2;    // log2
+        const float lnew = K > 8 ? __builtin_amdgcn_logf(prod) + (float)e2 : __builtin_amdgcn_logf(prod);   // log2
         // what an accepted move needs, formed while the sum over the lanes is under way (kept from being sunk below the
         // decision where the registers hold it)
         constexpr bool kEarly = G == 16 || K <= 8;
@@ -275,12 +282,12 @@ __device__ __forceinline__ void rbm_run_chain(const RbmSampleArgs &A, int64_t c,
         uint32_t flip = gl == fw ? fbit : 0u, same = i_n == i_c ? 0x80000000u : 0u;
 #pragma unroll
         for (int q = 0; q < K; ++q) {
-            mm[q] = sh[q] * cs_c[q].x;
+            mm[q] = msh[q] * cs_c[q].x;
             if constexpr (kEarly) asm volatile("" : "+v"(mm[q]));
         }
         if constexpr (kEarly) asm volatile("" : "+v"(flip), "+v"(same));
         const float dsum = group_sum_uniform<G>(lnew - lpart);
-        float d2 = fmaf(2.0f, dsum, __uint_as_float(__float_as_uint(-a2_c) ^ smask));   // log2 of the acceptance ratio
+        float d2 = fmaf(2.0f, dsum, __uint_as_float(__float_as_uint(a2_c) ^ smask));   // log2 of the acceptance ratio
         float zn = 0.0f;
         if constexpr (NOISE) {
             zn = noise_zeta_log2(nw0 ^ (fw == 0 ? fbit : 0u), nw1 ^ (fw == 1 ? fbit : 0u),
@@ -291,11 +298,12 @@ __device__ __forceinline__ void rbm_run_chain(const RbmSampleArgs &A, int64_t c,
         if (accept) {
 #pragma unroll
             for (int q = 0; q < K; ++q) {
-                sh[q] = fmaf(-cc[q], sp[q], mm[q]);
+                // fmaf(cc, sp, mm) into msh's own register (the compiler takes the two-operand form, and a copy)
+                asm("v_fma_f32 %0, %1, %2, %3" : "+v"(msh[q]) : "v"(cc[q]), "v"(sp[q]), "v"(mm[q]));
                 cc[q] = nn[q];
             }
             lpart = lnew;
-            word ^= flip;
+            down ^= flip;
             if constexpr (NOISE) {
                 nw0 ^= fw == 0 ? fbit : 0u;
                 nw1 ^= fw == 1 ? fbit : 0u;
@@ -365,7 +373,7 @@ __device__ __forceinline__ void rbm_run_chain(const RbmSampleArgs &A, int64_t c,
                 }
             }
             if (++since_refresh == A.refresh_sweeps || need_logpsi) {
-                f = rbm_refresh<G, K>(A.net, word, gl, cc, sh, lpart, need_logpsi || diag);
+                f = refresh(~down, need_logpsi || diag);
                 since_refresh = 0;
                 if constexpr (TRACE) {
                     if (diag) {
@@ -378,7 +386,7 @@ __device__ __forceinline__ void rbm_run_chain(const RbmSampleArgs &A, int64_t c,
                 if (A.samples && gl < NW) {
                     int8_t *dst = A.samples + ((size_t)out * A.n_chains + c) * N + gl * 32;
                     const int nb = min(32, N - gl * 32);
-                    for (int bb = 0; bb < nb; ++bb) dst[bb] = ((word >> bb) & 1u) ? 1 : -1;
+                    for (int bb = 0; bb < nb; ++bb) dst[bb] = ((down >> bb) & 1u) ? -1 : 1;
                 }
                 if (A.logpsi && gl == 0) A.logpsi[(size_t)out * A.n_chains + c] = f;
             }
@@ -389,7 +397,7 @@ __device__ __forceinline__ void rbm_run_chain(const RbmSampleArgs &A, int64_t c,
     if (gl < NW) {
         int8_t *dst = A.chain_state + (size_t)c * N + gl * 32;
         const int nb = min(32, N - gl * 32);
-        for (int bb = 0; bb < nb; ++bb) dst[bb] = ((word >> bb) & 1u) ? 1 : -1;
+        for (int bb = 0; bb < nb; ++bb) dst[bb] = ((down >> bb) & 1u) ? -1 : 1;
     }
     if (A.n_acc && gl == 0) A.n_acc[c] = acc;
     if constexpr (TRACE) {
