@@ -460,7 +460,8 @@ constexpr int kMcWaves = kMcThreads / 64;
 template <int DT> struct CnnMcT { typedef uint16_t E; };   // activations in LDS: raw codes
 template <> struct CnnMcT<kF32> { typedef float E; };      // FP32 (rounded to the copy's format by the caller's `rnd`)
 
-// phi(v) rounded to the 16-bit format DT, as its code: exactly round(cnn_gelu(v)), at a third of its instructions.
+// phi(v) rounded to the 16-bit format DT, as its code: exactly round(cnn_gelu(v)) (binary16: its last product rounded
+// once), at a third of its instructions.
 // phi(x) = x / (1 + e), e = exp(-2 sqrt(2 / pi) (x + 0.044715 x^3)), takes one exponential and one reciprocal.
 // Its error and that of the tanhf form are both below d = 1 + e units in the last place of the result (the tanhf
 // form loses digits where 1 + tanh cancels, as d grows), so the two round to the same code unless the result lies
@@ -476,13 +477,19 @@ __device__ __forceinline__ uint16_t cnn_gelu_code(float x)
     const int off = (int)(__float_as_uint(r) & ((1u << kDrop) - 1u)) - (1 << (kDrop - 1));
     bool sure = fabsf((float)off) > 4.0f * d;
     if constexpr (DT == kF16) sure = sure && fabsf(r) >= 6.2e-5f;
-    if (!sure) r = cnn_gelu(x);
     if constexpr (DT == kBF16) {
+        if (!sure) r = cnn_gelu(x);
         const __bf16 c = (__bf16)r;       // one hardware conversion, to nearest even, NaN kept quiet
         return __builtin_bit_cast(uint16_t, c);
     } else {
-        const _Float16 c = (_Float16)r;
-        return __builtin_bit_cast(uint16_t, c);
+        uint32_t c = __builtin_bit_cast(uint16_t, (_Float16)r);
+        if (!sure) {
+            // the last product of cnn_gelu rounded once, to binary16 (what the compiler makes of the product and a
+            // conversion where it sees both)
+            const float h = 0.5f * x, t = 1.0f + tanhf(0.7978845608028654f * fmaf(0.044715f * x * x, x, x));
+            asm("v_fma_mixlo_f16 %0, %1, %2, 0" : "=v"(c) : "v"(h), "v"(t));
+        }
+        return (uint16_t)c;
     }
 }
 
