@@ -201,6 +201,13 @@ __host__ __device__ __forceinline__ size_t frag_index8(int r, int c, int Kp)
            (c & 15);
 }
 
+// The same for FP32 operands of the 32x32x2 instruction (lane = 32 (c % 2) + r % 32): per 32 rows and eight columns one
+// fragment of 64 16-byte pieces, the four values a lane takes in four products in sequence.
+__host__ __device__ __forceinline__ size_t frag_index32(int r, int c, int Kp)
+{
+    return (((size_t)(r >> 5) * (Kp >> 3) + (c >> 3)) * 64 + (c & 1) * 32 + (r & 31)) * 4 + ((c >> 1) & 3);
+}
+
 // log cosh z = |z| + log(1 + exp(-2|z|)) - log 2, FP32
 __device__ __forceinline__ float logcosh_f32(float z)
 {

@@ -37,16 +37,16 @@ __global__ void ffnn_round_layer_kernel(const double *__restrict__ Wsrc, const d
     }
 }
 
-// dst[r][c] (ld_dst, zero padded to rows_p x cols_p) from src[r][c] (ld_src); frag: the codes in matrix-instruction
-// order (frag_index16) instead of row by row
+// dst[r][c] (ld_dst, zero padded to rows_p x cols_p) from src[r][c] (ld_src); frag, frag32: the codes, the FP32 values
+// in matrix-instruction order (frag_index16, frag_index32) instead of row by row
 __global__ void ffnn_pad_kernel(const float *__restrict__ src, int rows, int cols, int ld_src, int rows_p, int cols_p,
-                                int dtype, uint16_t *codes, float *f32, int frag)
+                                int dtype, uint16_t *codes, float *f32, int frag, int frag32)
 {
     const int64_t n = (int64_t)rows_p * cols_p;
     for (int64_t p = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; p < n; p += (int64_t)gridDim.x * blockDim.x) {
         const int r = (int)(p / cols_p), c = (int)(p % cols_p);
         const float v = (r < rows && c < cols) ? src[(int64_t)r * ld_src + c] : 0.0f;
-        if (f32) f32[p] = v;
+        if (f32) f32[frag32 ? frag_index32(r, c, cols_p) : (size_t)p] = v;
         if (codes) {
             uint16_t code;
             if (dtype == kF16) {
@@ -174,7 +174,7 @@ static nqs_status ffnn_build_e4m3(nqs_model *m, hipStream_t stream)
                            0, stream, Wm, out, in, (const unsigned long long *)(amax + 2 * l), f.Np[l], f.Kp[l],
                            (uint8_t *)f.Wd[l], f.Wt[l]);
         hipLaunchKernelGGL(ffnn_pad_kernel, dim3((f.Np[l] + 255) / 256), dim3(256), 0, stream, f.b[l], 1, out, out, 1,
-                           f.Np[l], (int)kF32, (uint16_t *)nullptr, f.bd[l], 0);
+                           f.Np[l], (int)kF32, (uint16_t *)nullptr, f.bd[l], 0, 0);
         hipLaunchKernelGGL(ffnn_e4m3_rowsum_kernel, dim3((out + 3) / 4), dim3(256), 0, stream, Wm, bm, out, in,
                            (const unsigned long long *)(amax + 2 * l), (const unsigned long long *)(amax + 2 * l + 1),
                            rs[l], bq[l]);
@@ -279,14 +279,14 @@ nqs_status ffnn_build_copy(nqs_model *m, int dtype, hipStream_t stream)
         f.W1tp = (float *)carve(sizeof(float) * (size_t)N * f.m1p);
         f.b1p = (float *)carve(sizeof(float) * f.m1p);
         f.b2p = (float *)carve(sizeof(float) * f.m2p);
-        auto pad = [&](const float *src, int rows, int cols, int ld, int rows_p, int cols_p, uint16_t *codes,
-                       float *f32) {
+        auto pad = [&](const float *src, int rows, int cols, int ld, int rows_p, int cols_p, uint16_t *codes, float *f32,
+                       int frag32 = 0) {
             const int64_t n = (int64_t)rows_p * cols_p;
             const int blocks = (int)std::min<int64_t>((n + 255) / 256, 8192);
             hipLaunchKernelGGL(ffnn_pad_kernel, dim3(blocks), dim3(256), 0, stream, src, rows, cols, ld, rows_p, cols_p,
-                               dtype, codes, f32, 0);
+                               dtype, codes, f32, 0, frag32);
         };
-        pad(f.W[1], M2, M1, M1, f.m2p, f.m1p, lp ? f.W2c : nullptr, f.W2p);
+        pad(f.W[1], M2, M1, M1, f.m2p, f.m1p, lp ? f.W2c : nullptr, lp ? nullptr : f.W2p, 1);
         pad(f.Wt[0], N, M1, M1, N, f.m1p, lp ? f.W1ct : nullptr, f.W1tp);
         pad(f.b[0], 1, M1, M1, 1, f.m1p, nullptr, f.b1p);
         pad(f.b[1], 1, M2, M2, 1, f.m2p, nullptr, f.b2p);
@@ -299,9 +299,9 @@ nqs_status ffnn_build_copy(nqs_model *m, int dtype, hipStream_t stream)
         const int64_t n = (int64_t)f.Np[l] * f.Kp[l];
         const int blocks = (int)std::min<int64_t>((n + 255) / 256, 8192);
         hipLaunchKernelGGL(ffnn_pad_kernel, dim3(blocks), dim3(256), 0, stream, f.W[l], out, in, in, f.Np[l], f.Kp[l],
-                           dtype, lp ? (uint16_t *)f.Wd[l] : nullptr, lp ? nullptr : (float *)f.Wd[l], 1);
+                           dtype, lp ? (uint16_t *)f.Wd[l] : nullptr, lp ? nullptr : (float *)f.Wd[l], 1, 0);
         hipLaunchKernelGGL(ffnn_pad_kernel, dim3((f.Np[l] + 255) / 256), dim3(256), 0, stream, f.b[l], 1, out, out, 1,
-                           f.Np[l], dtype, (uint16_t *)nullptr, f.bd[l], 0);
+                           f.Np[l], dtype, (uint16_t *)nullptr, f.bd[l], 0, 0);
         NQS_HIP_TRY(hipGetLastError());
     }
     NQS_HIP_TRY(hipStreamSynchronize(stream));
@@ -792,7 +792,6 @@ size_t ffnn_reg_eloc_lds_bf16(int N, int ke, int m2p, int G);
 size_t ffnn_reg_eloc_lds_f16(int N, int ke, int m2p, int G);
 // Layer 2 can live in registers (8 waves x 32 output rows) for 16-bit operands
 // with 128 <= m1p <= 512 and m2p <= 256.
-static_assert(kRows == kRegRows, "both samplers take 64 chains per block");
 static bool reg_path(int dtype, const FfnnDev &f)
 {
     return (dtype == NQS_BF16 || dtype == NQS_F16) && f.m1p >= 128 && f.m1p <= 512 && f.m2p <= 256;
@@ -816,6 +815,13 @@ static nqs_status ffnn_mc_ready(nqs_model *m, int dtype, hipStream_t stream, boo
     *deep = dtype == NQS_FP8_E4M3 || m->desc.n_layers != 2 || f.m1p > 512 ||
             (int64_t)f.widths[0] * f.m1p * (dtype == NQS_F32 ? 0 : 2) > 96 * 1024;
     return NQS_OK;
+}
+
+// The networks that the FP32 kernels take are those whose kRows rows fit; theirs are kRows32.
+static size_t f32_spare(int dtype, const FfnnDev &f)
+{
+    if (dtype != NQS_F32) return 0;
+    return sizeof(float) * ((size_t)kRows * (f.m1p + hs_pad<float>()) - (size_t)(f.m1p / 8) * kHBlock);
 }
 
 static size_t sample_lds_bytes(int dtype, int N, int m1p, int m2p)
@@ -849,7 +855,8 @@ nqs_status ffnn_sample(nqs_model *m, const nqs_sample_cfg &cfg, int8_t *chain_st
     const size_t reg_lds = cfg.dtype == NQS_F16 ? ffnn_reg_sample_lds_f16(N, KE, f.m2p) : ffnn_reg_sample_lds_bf16(N, KE, f.m2p);
     const bool use_reg = reg_path(cfg.dtype, f) && reg_lds <= 160 * 1024;
     const size_t lds = use_reg ? reg_lds : sample_lds_bytes(cfg.dtype, N, f.m1p, f.m2p);
-    if (lds > 160 * 1024) return set_error(NQS_EUNSUPPORTED, "network too large for the LDS-resident sampler");
+    if (lds + (use_reg ? 0 : f32_spare(cfg.dtype, f)) > 160 * 1024)
+        return set_error(NQS_EUNSUPPORTED, "network too large for the LDS-resident sampler");
     if (cfg.init_chains) {
         st = launch_init_chains(chain_state, cfg.n_chains, N, cfg.move, cfg.seed, cfg.instance_id, cfg.chain_id_offset,
                                 stream);
@@ -903,7 +910,8 @@ nqs_status ffnn_sample(nqs_model *m, const nqs_sample_cfg &cfg, int8_t *chain_st
         NQS_HIP_TRY(hipGetLastError());
         return NQS_OK;
     }
-    return ffnn_sample_dispatch(cfg.dtype, QK, tr, A, (int)((cfg.n_chains + kRows - 1) / kRows), lds, stream);
+    const int rows = cfg.dtype == NQS_F32 ? kRows32 : kRows;
+    return ffnn_sample_dispatch(cfg.dtype, QK, tr, A, (int)((cfg.n_chains + rows - 1) / rows), lds, stream);
 }
 
 nqs_status ffnn_local_energy(nqs_model *m, const nqs_ham_desc &ham, const int8_t *samples, int64_t n, int dtype,
@@ -943,7 +951,8 @@ nqs_status ffnn_local_energy(nqs_model *m, const nqs_ham_desc &ham, const int8_t
     else if (dtype == NQS_F32) lds = ffnn_eloc_lds_bytes<float>(N, f.m1p, f.m2p);
     else if (dtype == NQS_F16) lds = ffnn_eloc_lds_bytes<_Float16>(N, f.m1p, f.m2p);
     else lds = ffnn_eloc_lds_bytes<__bf16>(N, f.m1p, f.m2p);
-    if (lds > 160 * 1024) return set_error(NQS_EUNSUPPORTED, "network too large for the local-energy kernel");
+    if (lds + (use_reg ? 0 : f32_spare(dtype, f)) > 160 * 1024)
+        return set_error(NQS_EUNSUPPORTED, "network too large for the local-energy kernel");
     if (m->desc.marshall && (m->desc.lat_dim != ham.dim || m->desc.lat_L != ham.L))
         return set_error(NQS_EINVAL, "Marshall lattice differs from the Hamiltonian lattice");
     FfnnElocArgs A;

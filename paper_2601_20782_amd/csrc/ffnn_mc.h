@@ -1,13 +1,14 @@
 // Two-layer dense network on the matrix cores:
 //   z1 = W1 s + b1,  h1 = ReLU(z1),  z2 = W2 h1 + b2,  log|psi| = sum_k log cosh(z2_k).
 //
-// A block of 256 threads (4 waves) evaluates 64 "rows" at a time (64 chains
-// of the sampler, or 64 moves of one sample in the local energy).  Each row's
+// A block of 256 threads (4 waves) evaluates 64 "rows" at a time, 32 in FP32 (chains
+// of the sampler, or moves of one sample in the local energy).  Each row's
 // first layer is updated incrementally from a kept z1 (a flip of site i adds
 // -2 s_i W1[:,i]; an exchange of antiparallel i, j adds -2 s_i (W1[:,i] -
 // W1[:,j])), passed through ReLU and rounded to the operand format into LDS.
 // The second layer is one GEMM on the matrix cores, Z2^T = W2 H1^T, with W2
-// streamed through L2 (A operand) and H1 from LDS (B operand), so that each
+// streamed through L2 (A operand) and H1 from LDS (B operand; FP32: both in the
+// order of the matrix instructions), so that each
 // lane's output fragment covers 16 outputs of ONE row: the log-cosh sum then
 // needs no cross-lane work except one exchange between the two half-waves.
 // log cosh is summed as  sum |z| + log prod (1 + e^{-2|z|}) - n log 2, one
@@ -15,6 +16,8 @@
 #pragma once
 
 #include <hip/hip_runtime.h>
+
+#include <type_traits>
 
 #include "common.h"
 #include "internal.h"
@@ -65,6 +68,7 @@ struct Mc<float> {
 };
 
 constexpr int kRows = 64;        // rows evaluated per block pass
+constexpr int kRows32 = 32;      // in FP32: a block's rows leave the LDS room for a second one, whose products overlap its staging
 constexpr float kLn2f = 0.69314718055994531f;
 
 template <typename T>
@@ -140,6 +144,107 @@ __device__ __forceinline__ void gemm_logcosh_rows(const T *__restrict__ W2, cons
     }
 }
 
+// The same in FP32 with W2 and the staged rows in matrix-instruction order (frag_index32; the rows' fragments padded to
+// kHBlock words): four products per 16-byte read, each wave's reads consecutive.  RB blocks of 32 rows.  A product adds
+// its two columns one after the other, as FMAs, so the sums are those of any other order of reads.  Blocks of 32
+// outputs past m2 are left out: they add log cosh 0 = 0 exactly.
+//
+// Why: with a word per lane from 32 rows of W2 each product's read touched 64 lines, and 16,384 chains of 100-400-200
+// took 74 us a step, the products alone need 21.  Now 35 us (two blocks of 32 rows per CU, one's staging beside the
+// other's products), 4,096 chains 23 us instead of 74; 32,768 samples' local energies 10.8 ms instead of 21.6.
+constexpr int kHBlock = 2 * 132;   // words of a fragment of staged rows: the pad keeps the staging stores off each other's banks
+__device__ __forceinline__ int h_index(int r, int k, int KB)
+{
+    return ((r >> 5) * KB + (k >> 3)) * kHBlock + (k & 1) * 132 + (r & 31) * 4 + ((k >> 1) & 3);
+}
+
+template <int RB>
+__device__ __forceinline__ void gemm_logcosh_f32(const float4 *__restrict__ W2f, const float *b2s, const float *Hs, int KB,
+                                                 int KBp, int m2, int m2p, float *part)
+{
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int lr = lane & 31, lh = lane >> 5;
+    float abs_sum[RB], prod[RB];
+    int e2[RB];
+#pragma unroll
+    for (int b = 0; b < RB; ++b) {
+        abs_sum[b] = 0.0f;
+        prod[b] = 1.0f;
+        e2[b] = 0;
+    }
+    int nrow = 0;
+    auto blocks = [&](int rb, auto na_c) {
+        constexpr int NA = decltype(na_c)::value;
+        mc_floatx16 acc[NA][RB];
+#pragma unroll
+        for (int a = 0; a < NA; ++a)
+#pragma unroll
+            for (int b = 0; b < RB; ++b)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) acc[a][b][r] = 0.0f;
+        const float4 *w = W2f + (size_t)(rb >> 5) * KBp * 64 + lane;
+        const float *h = Hs + lh * 132 + lr * 4;
+        float4 wv[2][NA], hv[2][RB];
+        auto load = [&](int kb, int s) {
+            const int k = min(kb, KB - 1);
+#pragma unroll
+            for (int a = 0; a < NA; ++a) wv[s][a] = w[((size_t)a * KBp + k) * 64];
+#pragma unroll
+            for (int b = 0; b < RB; ++b) hv[s][b] = *reinterpret_cast<const float4 *>(h + (b * KB + k) * kHBlock);
+        };
+        auto mul = [&](int s) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+#pragma unroll
+                for (int a = 0; a < NA; ++a)
+#pragma unroll
+                    for (int b = 0; b < RB; ++b) {
+                        const float4 x = wv[s][a], y = hv[s][b];
+                        const float xe = e == 0 ? x.x : e == 1 ? x.y : e == 2 ? x.z : x.w;
+                        const float ye = e == 0 ? y.x : e == 1 ? y.y : e == 2 ? y.z : y.w;
+                        acc[a][b] = Mc<float>::mma(xe, ye, acc[a][b]);
+                    }
+        };
+        load(0, 0);
+        load(1, 1);
+        for (int kb = 0; kb < KB; kb += 2) {
+            mul(0);
+            load(kb + 2, 0);
+            if (kb + 1 < KB) mul(1);
+            load(kb + 3, 1);
+        }
+#pragma unroll
+        for (int a = 0; a < NA; ++a)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const float bias = b2s[rb + 32 * a + 8 * (r >> 2) + 4 * lh + (r & 3)];
+#pragma unroll
+                for (int b = 0; b < RB; ++b) {
+                    const float v = fabsf(acc[a][b][r] + bias);
+                    abs_sum[b] += v;
+                    prod[b] *= 1.0f + __expf(-2.0f * v);
+                }
+            }
+        nrow += 16 * NA;
+#pragma unroll
+        for (int b = 0; b < RB; ++b) {
+            int e;
+            prod[b] = frexpf(prod[b], &e);
+            e2[b] += e;
+        }
+    };
+    for (int rb = wave * 64; rb < m2p; rb += 256) {
+        if (rb + 32 < m2) blocks(rb, std::integral_constant<int, 2>{});
+        else if (rb < m2) blocks(rb, std::integral_constant<int, 1>{});
+    }
+#pragma unroll
+    for (int b = 0; b < RB; ++b) {
+        float s = abs_sum[b] + __logf(prod[b]) + ((float)e2[b] - (float)nrow) * kLn2f;
+        s += __shfl_xor(s, 32, 64);
+        if (lh == 0) part[wave * kRows + 32 * b + lr] = s;
+    }
+}
+
 // ---------------------------------------------------------------------------
 // Sampler
 // ---------------------------------------------------------------------------
@@ -173,7 +278,8 @@ struct FfnnLds {
         const int NW = (N + 31) / 32;
         size_t b = 0;
         if (sizeof(T) == 2) b += sizeof(T) * (size_t)N * m1p;   // W1t (16-bit operands only)
-        b += sizeof(T) * (size_t)kRows * ldh;                  // Hs
+        if (sizeof(T) == 2) b += sizeof(T) * (size_t)kRows * ldh;   // Hs
+        else b += sizeof(float) * (size_t)(m1p / 8) * kHBlock;
         b += sizeof(float) * m2p;                              // b2s
         b += sizeof(float) * 4 * kRows;                        // part
         b += sizeof(uint32_t) * (size_t)kRows * NW;            // spin words
@@ -183,18 +289,20 @@ struct FfnnLds {
 };
 
 template <typename T, int QK, bool TRACE>
-__global__ void __launch_bounds__(256) ffnn_sample_kernel(FfnnSampleArgs A)
+__global__ void __launch_bounds__(256, sizeof(T) == 4 ? 2 : 1) ffnn_sample_kernel(FfnnSampleArgs A)
 {
     extern __shared__ __align__(16) unsigned char smem[];
     const FfnnDev &net = A.net;
     const int N = net.widths[0], m1p = net.m1p, m2p = net.m2p;
     const int NW = (N + 31) >> 5;
     const int ldh = m1p + hs_pad<T>();
-    constexpr bool W1_LDS = sizeof(T) == 2;
+    constexpr bool W1_LDS = sizeof(T) == 2, F32 = !W1_LDS;
+    constexpr int ROWS = F32 ? kRows32 : kRows;
+    const int KB = (net.widths[1] + 7) / 8;         // FP32: fragments of eight units with values
     T *W1l = reinterpret_cast<T *>(smem);
     T *Hs = W1l + (W1_LDS ? (size_t)N * m1p : 0);
     const T *W1s = W1_LDS ? W1l : reinterpret_cast<const T *>(A.W1t);
-    float *b2s = reinterpret_cast<float *>(Hs + (size_t)kRows * ldh);
+    float *b2s = reinterpret_cast<float *>(Hs + (F32 ? (size_t)(m1p / 8) * kHBlock : (size_t)kRows * ldh));
     float *part = b2s + m2p;
     uint32_t *words = reinterpret_cast<uint32_t *>(part + 4 * kRows);
     int *pi = reinterpret_cast<int *>(words + kRows * NW);
@@ -206,8 +314,8 @@ __global__ void __launch_bounds__(256) ffnn_sample_kernel(FfnnSampleArgs A)
     float *psgn = fcur + kRows;
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int64_t c0 = (int64_t)blockIdx.x * kRows;
-    const int nvalid = (int)min<int64_t>(kRows, A.n_chains - c0);
+    const int64_t c0 = (int64_t)blockIdx.x * ROWS;
+    const int nvalid = (int)min<int64_t>(ROWS, A.n_chains - c0);
 
     // stage layer-1 columns and the bias, load spins
     {
@@ -217,7 +325,7 @@ __global__ void __launch_bounds__(256) ffnn_sample_kernel(FfnnSampleArgs A)
             for (int k = tid; k < n; k += 256) W1l[k] = src[k];
         }
         for (int k = tid; k < m2p; k += 256) b2s[k] = net.b2p[k];
-        for (int k = tid; k < kRows * NW; k += 256) {
+        for (int k = tid; k < ROWS * NW; k += 256) {
             const int r = k / NW, w = k % NW;
             uint32_t bits = 0;
             if (r < nvalid) {
@@ -230,8 +338,8 @@ __global__ void __launch_bounds__(256) ffnn_sample_kernel(FfnnSampleArgs A)
     }
     __syncthreads();
 
-    // z1 of this wave's 16 rows: lane owns hidden units k = lane + 64 q
-    constexpr int RPW = kRows / 4;
+    // z1 of this wave's RPW rows: lane owns hidden units k = lane + 64 q
+    constexpr int RPW = ROWS / 4;
     float z1[RPW][QK];
     auto refresh_z1 = [&]() {
 #pragma unroll
@@ -272,31 +380,57 @@ __global__ void __launch_bounds__(256) ffnn_sample_kernel(FfnnSampleArgs A)
             dz[q] = g * d;
         }
     };
+    // FP32: the layer-1 changes of this wave's rows, kept for the accepted ones (W1 comes from L2: every row's columns are
+    // read without a branch)
+    float dk[F32 ? RPW : 1][QK];
+    auto row_changes = [&]() {
+#pragma unroll
+        for (int r = 0; r < RPW; ++r) {
+            const int row = wave * RPW + r;
+            const int i = __builtin_amdgcn_readfirstlane(pi[row]), j = __builtin_amdgcn_readfirstlane(pj[row]);
+            const bool eff = __builtin_amdgcn_readfirstlane(peff[row]) != 0;
+            const float g = -2.0f * psgn[row];
+#pragma unroll
+            for (int q = 0; q < QK; ++q) {
+                const int k = min(lane + 64 * q, m1p - 1);
+                const float wi = Mc<T>::to_f32(W1s[i * m1p + k]), wj = Mc<T>::to_f32(W1s[max(j, 0) * m1p + k]);
+                dk[F32 ? r : 0][q] = eff ? g * (j >= 0 ? wi - wj : wi) : 0.0f;
+            }
+        }
+    };
     // stage h1 = ReLU(z1 + dz) of this wave's rows (operand format)
     auto stage = [&](bool with_proposal) {
+        if (F32 && with_proposal) row_changes();
 #pragma unroll
         for (int r = 0; r < RPW; ++r) {
             const int row = wave * RPW + r;
             float dz[QK];
-            if (with_proposal) delta_z1(row, dz);
+            if (!F32 && with_proposal) delta_z1(row, dz);
 #pragma unroll
             for (int q = 0; q < QK; ++q) {
                 const int k = lane + 64 * q;
-                if (k < m1p) {
-                    const float h = fmaxf(z1[r][q] + (with_proposal ? dz[q] : 0.0f), 0.0f);
-                    Hs[row * ldh + k] = Mc<T>::from_f32(h);
+                const float d = with_proposal ? (F32 ? dk[F32 ? r : 0][q] : dz[q]) : 0.0f;
+                const float h = fmaxf(z1[r][q] + d, 0.0f);
+                if constexpr (F32) {
+                    if (k < 8 * KB) Hs[h_index(row, k, KB)] = h;
+                } else {
+                    if (k < m1p) Hs[row * ldh + k] = Mc<T>::from_f32(h);
                 }
             }
         }
     };
-    const T *W2 = reinterpret_cast<const T *>(A.W2);
+    auto layer2 = [&]() {
+        if constexpr (F32)
+            gemm_logcosh_f32<1>(reinterpret_cast<const float4 *>(A.W2), b2s, Hs, KB, m1p / 8, net.widths[2], m2p, part);
+        else gemm_logcosh_rows<T>(reinterpret_cast<const T *>(A.W2), b2s, Hs, ldh, m1p, m2p, part);
+    };
 
     refresh_z1();
     stage(false);
     __syncthreads();
-    gemm_logcosh_rows<T>(W2, b2s, Hs, ldh, m1p, m2p, part);
+    layer2();
     __syncthreads();
-    if (tid < kRows) fcur[tid] = part[tid] + part[kRows + tid] + part[2 * kRows + tid] + part[3 * kRows + tid];
+    if (tid < ROWS) fcur[tid] = part[tid] + part[kRows + tid] + part[2 * kRows + tid] + part[3 * kRows + tid];
 
     const int sw = A.sweep_size;
     const int64_t total = (int64_t)(A.n_burnin + A.n_sweeps) * sw;
@@ -306,7 +440,7 @@ __global__ void __launch_bounds__(256) ffnn_sample_kernel(FfnnSampleArgs A)
     int64_t sweep = 0;
     for (int64_t k = 0; k < total; ++k) {
         // proposals (one thread per row)
-        if (tid < kRows) {
+        if (tid < ROWS) {
             const uint64_t step = A.step_offset + (uint64_t)k;
             const uint32_t gid = A.chain_id_offset + (uint32_t)(c0 + tid);
             const Block4 rb = philox4x32_10((uint32_t)step, (uint32_t)(step >> 32), gid, A.inst << 8, key0, key1);
@@ -330,9 +464,9 @@ __global__ void __launch_bounds__(256) ffnn_sample_kernel(FfnnSampleArgs A)
         __syncthreads();
         stage(true);
         __syncthreads();
-        gemm_logcosh_rows<T>(W2, b2s, Hs, ldh, m1p, m2p, part);
+        layer2();
         __syncthreads();
-        if (tid < kRows) {
+        if (tid < ROWS) {
             const float fnew = part[tid] + part[kRows + tid] + part[2 * kRows + tid] + part[3 * kRows + tid];
             const bool eff = peff[tid] != 0;
             const float d2 = eff ? 2.0f * (fnew - fcur[tid]) / kLn2f : 0.0f;
@@ -364,7 +498,11 @@ __global__ void __launch_bounds__(256) ffnn_sample_kernel(FfnnSampleArgs A)
 #pragma unroll
         for (int r = 0; r < RPW; ++r) {
             const int row = wave * RPW + r;
-            if (pupd[row]) {
+            if constexpr (F32) {
+                const bool u = __builtin_amdgcn_readfirstlane(pupd[row]) != 0;
+#pragma unroll
+                for (int q = 0; q < QK; ++q) z1[r][q] = u ? z1[r][q] + dk[r][q] : z1[r][q];
+            } else if (pupd[row]) {
                 float dz[QK];
                 delta_z1(row, dz);
 #pragma unroll
@@ -427,26 +565,28 @@ __host__ __device__ inline size_t ffnn_eloc_lds_bytes(int N, int m1p, int m2p)
 {
     const size_t ldh = m1p + hs_pad<T>();
     size_t b = 0;
-    if (sizeof(T) == 2) b += sizeof(T) * (size_t)N * m1p;
-    b += sizeof(T) * (size_t)kRows * ldh;
+    if (sizeof(T) == 2) b += sizeof(T) * ((size_t)N * m1p + (size_t)kRows * ldh);
+    else b += sizeof(float) * (size_t)(m1p / 8) * kHBlock;
     b += sizeof(float) * (m2p + 4 * kRows + m1p + N);
     b += (sizeof(int) * 2 + sizeof(float) * 2) * (size_t)(2 * N + 1);
     return b;
 }
 
 template <typename T, int QK>
-__global__ void __launch_bounds__(256) ffnn_eloc_kernel(FfnnElocArgs A)
+__global__ void __launch_bounds__(256, sizeof(T) == 4 ? 2 : 1) ffnn_eloc_kernel(FfnnElocArgs A)
 {
     extern __shared__ __align__(16) unsigned char smem[];
     const FfnnDev &net = A.net;
     const int N = net.widths[0], m1p = net.m1p, m2p = net.m2p;
     const int ldh = m1p + hs_pad<T>();
     const int maxmoves = 2 * N + 1;
-    constexpr bool W1_LDS = sizeof(T) == 2;
+    constexpr bool W1_LDS = sizeof(T) == 2, F32 = !W1_LDS;
+    constexpr int ROWS = F32 ? kRows32 : kRows;
+    const int KB = (net.widths[1] + 7) / 8;            // FP32: fragments of eight units with values
     T *W1l = reinterpret_cast<T *>(smem);
     T *Hs = W1l + (W1_LDS ? (size_t)N * m1p : 0);
     const T *W1s = W1_LDS ? W1l : reinterpret_cast<const T *>(A.W1t);
-    float *b2s = reinterpret_cast<float *>(Hs + (size_t)kRows * ldh);
+    float *b2s = reinterpret_cast<float *>(Hs + (F32 ? (size_t)(m1p / 8) * kHBlock : (size_t)kRows * ldh));
     float *part = b2s + m2p;
     float *zs = part + 4 * kRows;                      // [m1p] z1 of the sample
     float *sp = zs + m1p;                              // [N] spins
@@ -454,7 +594,6 @@ __global__ void __launch_bounds__(256) ffnn_eloc_kernel(FfnnElocArgs A)
     int *mj = mi + maxmoves;
     float *mc = reinterpret_cast<float *>(mj + maxmoves);   // coefficients
     float *fr = mc + maxmoves;                         // f of each row
-    __shared__ int s_nmoves;
     __shared__ int s_wcount[4];
     __shared__ double s_red[4];
 
@@ -466,7 +605,6 @@ __global__ void __launch_bounds__(256) ffnn_eloc_kernel(FfnnElocArgs A)
         }
         for (int k = tid; k < m2p; k += 256) b2s[k] = net.b2p[k];
     }
-    const T *W2 = reinterpret_cast<const T *>(A.W2);
     const int nb = A.dim == 1 ? (A.pbc ? A.L : A.L - 1) : 2 * A.L * A.L;   // candidate bonds (2D: 2 per site)
     for (int64_t smp = blockIdx.x; smp < A.n; smp += gridDim.x) {
         __syncthreads();
@@ -544,11 +682,27 @@ __global__ void __launch_bounds__(256) ffnn_eloc_kernel(FfnnElocArgs A)
             __syncthreads();
         }
         const int nrows = 1 + cnt;
-        // evaluate rows in passes of kRows
-        for (int r0 = 0; r0 < nrows; r0 += kRows) {
+        // evaluate rows in passes of ROWS
+        for (int r0 = 0; r0 < nrows; r0 += ROWS) {
             __syncthreads();
-            for (int r = 0; r < kRows / 4; ++r) {
-                const int row = r0 + wave * (kRows / 4) + r;
+            if constexpr (F32) {
+                // without a branch, so that the rows' columns (from L2) are read together
+#pragma unroll
+                for (int r = 0; r < ROWS / 4; ++r) {
+                    const int lr = wave * (ROWS / 4) + r, row = min(r0 + lr, nrows - 1);
+                    const int i = __builtin_amdgcn_readfirstlane(mi[row]), j = __builtin_amdgcn_readfirstlane(mj[row]);
+                    const float g = i >= 0 ? -2.0f * sp[i] : 0.0f;
+#pragma unroll
+                    for (int q = 0; q < QK; ++q) {
+                        const int k = lane + 64 * q, kc = min(k, m1p - 1);
+                        const float wi = Mc<T>::to_f32(W1s[max(i, 0) * m1p + kc]), wj = Mc<T>::to_f32(W1s[max(j, 0) * m1p + kc]);
+                        const float d = i < 0 ? 0.0f : j >= 0 ? wi - wj : wi;
+                        if (k < 8 * KB) Hs[h_index(lr, k, KB)] = fmaxf(fmaf(g, d, zs[kc]), 0.0f);
+                    }
+                }
+            } else
+            for (int r = 0; r < ROWS / 4; ++r) {
+                const int row = r0 + wave * (ROWS / 4) + r;
                 const int lr = row - r0;
                 int i = -1, j = -1;
                 float g = 0.0f;
@@ -572,9 +726,11 @@ __global__ void __launch_bounds__(256) ffnn_eloc_kernel(FfnnElocArgs A)
                 }
             }
             __syncthreads();
-            gemm_logcosh_rows<T>(W2, b2s, Hs, ldh, m1p, m2p, part);
+            if constexpr (F32)
+                gemm_logcosh_f32<1>(reinterpret_cast<const float4 *>(A.W2), b2s, Hs, KB, m1p / 8, net.widths[2], m2p, part);
+            else gemm_logcosh_rows<T>(reinterpret_cast<const T *>(A.W2), b2s, Hs, ldh, m1p, m2p, part);
             __syncthreads();
-            if (tid < kRows && r0 + tid < nrows)
+            if (tid < ROWS && r0 + tid < nrows)
                 fr[r0 + tid] = part[tid] + part[kRows + tid] + part[2 * kRows + tid] + part[3 * kRows + tid];
         }
         __syncthreads();

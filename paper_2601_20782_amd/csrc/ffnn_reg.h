@@ -678,7 +678,6 @@ __host__ __device__ inline size_t reg_eloc_lds_bytes(int N, int KE, int m2p, int
     b += sizeof(T) * (size_t)(N + 1) * K;               // W1 columns and a column of zeros
     b += sizeof(T) * 2 * (size_t)kElocRows * ldh;       // h1 rows of two passes
     b += sizeof(float) * (size_t)G * K;                 // z1 of the group's samples
-    b += sizeof(float) * K;                             // b1
     b += sizeof(float) * m2p;                           // b2
     b += sizeof(float) * 2 * kRegWaves * kElocRows;     // partial sums of two passes
     b += sizeof(float) * (size_t)G * N;                 // spins
@@ -755,8 +754,7 @@ __global__ void __launch_bounds__(kRegThreads) ffnn_eloc_reg_kernel(FfnnElocArgs
     T *W1l = reinterpret_cast<T *>(smem);              // [N + 1][K]
     T *Hs = W1l + (size_t)(N + 1) * K;                 // [2][kElocRows][ldh]
     float *zs = reinterpret_cast<float *>(Hs + 2 * (size_t)kElocRows * ldh);   // [G][2][K / 8][4]
-    float *b1s = zs + (size_t)G * K;                   // [K]
-    float *b2s = b1s + K;                              // [m2p]
+    float *b2s = zs + (size_t)G * K;                   // [m2p]
     float *part = b2s + m2p;                           // [2][kRegWaves][kElocRows]
     float *sp = part + 2 * kRegWaves * kElocRows;      // [G][N]
     int *ctab = reinterpret_cast<int *>(sp + (size_t)G * N);   // [2N]
@@ -783,7 +781,6 @@ __global__ void __launch_bounds__(kRegThreads) ffnn_eloc_reg_kernel(FfnnElocArgs
         }
     }
     for (int k = tid; k < K; k += NT) W1l[(size_t)N * K + k] = Mc<T>::from_f32(0.0f);
-    for (int k = tid; k < K; k += NT) b1s[k] = net.b1p[k];
     for (int k = tid; k < m2p; k += NT) b2s[k] = net.b2p[k];
     const int nb = A.dim == 1 ? (A.pbc ? A.L : A.L - 1) : 2 * A.L * A.L;   // candidate bonds (2D: 2 per site)
     const int ncand = A.kind == NQS_TFIM ? N : 0;
@@ -899,8 +896,8 @@ __global__ void __launch_bounds__(kRegThreads) ffnn_eloc_reg_kernel(FfnnElocArgs
 #pragma unroll
             for (int e = 0; e < 8; ++e) z[e] += __shfl_xor(z[e], 32, 64);
             if (lh == 0) {
-                const float4 c0 = *reinterpret_cast<const float4 *>(b1s + 8 * c);
-                const float4 c1 = *reinterpret_cast<const float4 *>(b1s + 8 * c + 4);
+                const float4 c0 = *reinterpret_cast<const float4 *>(net.b1p + 8 * c);
+                const float4 c1 = *reinterpret_cast<const float4 *>(net.b1p + 8 * c + 4);
                 *reinterpret_cast<float4 *>(zs + s * K + 4 * c) =
                     make_float4(z[0] + c0.x, z[1] + c0.y, z[2] + c0.z, z[3] + c0.w);
                 *reinterpret_cast<float4 *>(zs + s * K + K / 2 + 4 * c) =

@@ -45,7 +45,7 @@ struct FfnnDev {
     int m1p = 0, m2p = 0;
     uint16_t *W2c = nullptr;               // [m2p][m1p] raw bf16/f16 codes of layer 2
     uint16_t *W1ct = nullptr;              // [N][m1p]   raw codes of layer 1, transposed
-    float *W2p = nullptr;                  // [m2p][m1p] FP32 values of layer 2
+    float *W2p = nullptr;                  // FP32 values of layer 2 [m2p][m1p], in matrix-instruction order (FP32 copy)
     float *W1tp = nullptr;                 // [N][m1p]   FP32 values of layer 1, transposed
     float *b1p = nullptr;                  // [m1p]
     float *b2p = nullptr;                  // [m2p]
