@@ -103,7 +103,7 @@ nqs_status crbm_build_copy(nqs_model *m, int dtype, hipStream_t stream)
 // all but the last FMA of the move's sinh is formed while the decision's sum is
 // under way, and the steps between two refreshes or draws run without tests.
 // 3,000 chains of 16, 64 and 100 sites with as many units: 517, 839 and 755 ns a
-// step before (the second with 128 units), 404, 781 and 690 ns now.
+// step before (the second with 128 units), 378, 757 and 673 ns now.
 
 struct CrbmSampleArgs {
     CrbmDev net;
@@ -193,7 +193,7 @@ __device__ __forceinline__ float crbm_refresh(const CrbmDev &net, uint32_t word,
 }
 
 // Proposal (batch start + g) for lane g of a group: site, u bits, log2 u and
-// the visible-bias term 4 Re(a_i) / ln 2.
+// the negative visible-bias term, -4 Re(a_i) / ln 2.
 struct CrbmProp {
     uint32_t i, ub;
     float l2u, a2;
@@ -207,18 +207,8 @@ __device__ __forceinline__ CrbmProp crbm_prop(const CrbmDev &net, uint64_t step,
     pb.i = (uint32_t)index_from_word(rb.r0, net.N);
     pb.ub = rb.r2 >> 8;
     pb.l2u = __builtin_amdgcn_logf((float)pb.ub * 5.9604644775390625e-8f);   // log2 u, u = ub 2^-24
-    pb.a2 = net.a2[pb.i];
+    pb.a2 = -net.a2[pb.i];
     return pb;
-}
-
-template <int G, int K>
-__device__ __forceinline__ void crbm_column(const float4 *__restrict__ tab, int i, int M, int gl, int last_off,
-                                            bool last_ok, float4 (&cs)[K])
-{
-    const int base = i * M + gl;
-#pragma unroll
-    for (int k = 0; k < K - 1; ++k) cs[k] = tab[base + k * G];
-    cs[K - 1] = tab[last_ok ? base + (K - 1) * G : last_off];
 }
 
 template <int G, int K, bool LDS_TAB>
@@ -239,8 +229,11 @@ __global__ void __launch_bounds__(G == 16 ? 256 : 512) crbm_sample_kernel(CrbmSa
     const uint32_t gid = A.chain_id_offset + (uint32_t)c;
     const uint32_t key0 = (uint32_t)A.seed, key1 = (uint32_t)(A.seed >> 32);
     const int NW = (N + 31) >> 5;
-    const int last_off = N * M;
     const bool last_ok = gl + (K - 1) * G < M;
+    const int base4 = ((int)(threadIdx.x & 63) & ~(G - 1)) << 2;
+    // byte offsets of a column's entries of this lane: its first, and its last or the neutral entry behind the table
+    const int col_step = 16 * M, col_first = 16 * gl;
+    const int last_step = last_ok ? 16 * M : 0, last_first = last_ok ? 16 * (gl + (K - 1) * G) : 16 * N * M;
 
     uint32_t word = 0;
     if (gl < NW) {
@@ -270,11 +263,14 @@ __global__ void __launch_bounds__(G == 16 ? 256 : 512) crbm_sample_kernel(CrbmSa
     float l2u_n = __uint_as_float(group_bcast<G>(__float_as_uint(cur.l2u), 1));
     float a2_c = __uint_as_float(group_bcast<G>(__float_as_uint(cur.a2), 0));
     float a2_n = __uint_as_float(group_bcast<G>(__float_as_uint(cur.a2), 1));
-    bool up = (group_bcast<G>(word, i_c >> 5) >> (i_c & 31)) & 1u;   // spin of site i_c
+    uint32_t smask = (group_bcast<G>(~word, i_c >> 5) >> (i_c & 31)) << 31;   // sign of site i_c's spin: 0 up, 2^31 down
     float4 csA[K], csB[K];
     auto column = [&](int i, float4 (&cs)[K]) {
-        if constexpr (LDS_TAB) crbm_column<G, K>(s_ctab, i, M, gl, last_off, last_ok, cs);
-        else crbm_column<G, K>(A.net.CS, i, M, gl, last_off, last_ok, cs);
+        const unsigned char *t = reinterpret_cast<const unsigned char *>(LDS_TAB ? s_ctab : A.net.CS);
+        const float4 *col = reinterpret_cast<const float4 *>(t + (i * col_step + col_first));
+#pragma unroll
+        for (int q = 0; q < K - 1; ++q) cs[q] = col[q * G];
+        cs[K - 1] = *reinterpret_cast<const float4 *>(t + (i * last_step + last_first));
     };
     column(i_c, csA);
 
@@ -282,15 +278,18 @@ __global__ void __launch_bounds__(G == 16 ? 256 : 512) crbm_sample_kernel(CrbmSa
     auto step = [&](int64_t k, float4 (&cs_c)[K], float4 (&cs_n)[K]) {
         column(i_n, cs_n);
         // the spin of the next proposal's site before this one's decision, and the proposal after the next
-        const uint32_t wbits_n = group_bcast<G>(word, i_n >> 5);
+        const uint32_t smask_b = (~group_bcast4<G>(word, base4, (i_n >> 3) & ~3) >> (i_n & 31)) << 31;
+        // the last lanes' proposals after the next are the next batch's first
         const bool in_cur = p + 2 < G;
-        const int pl = in_cur ? p + 2 : p + 2 - G;
-        const int i_f = (int)group_bcast<G>(in_cur ? cur.i : nxt.i, pl);
-        const float l2u_f = __uint_as_float(group_bcast<G>(__float_as_uint(in_cur ? cur.l2u : nxt.l2u), pl));
-        const float a2_f = __uint_as_float(group_bcast<G>(__float_as_uint(in_cur ? cur.a2 : nxt.a2), pl));
+        const int pl = (in_cur ? p + 2 : p + 2 - G) << 2;
+        const int i_f = (int)group_bcast4<G>(in_cur ? cur.i : nxt.i, base4, pl);
+        const float l2u_f = __uint_as_float(group_bcast4<G>(__float_as_uint(in_cur ? cur.l2u : nxt.l2u), base4, pl));
+        const float a2_f = __uint_as_float(group_bcast4<G>(__float_as_uint(in_cur ? cur.a2 : nxt.a2), base4, pl));
 
         // proposal k: flip site i_c
-        const float si = up ? 1.0f : -1.0f;
+        const float si = __uint_as_float(0x3F800000u | smask);
+        uint32_t flip = gl == (i_c >> 5) ? 1u << (i_c & 31) : 0u, same = i_n == i_c ? 0x80000000u : 0u;
+        asm volatile("" : "+v"(flip), "+v"(same));                         // formed before the decision
         float2 nn[K], ns[K];
         float prod = 1.0f;
         int e2 = 0;
@@ -322,7 +321,7 @@ __global__ void __launch_bounds__(G == 16 ? 256 : 512) crbm_sample_kernel(CrbmSa
             ns[q] = make_float2(fmaf(cc[q].y, spy, sx), fmaf(-cc[q].y, spx, sy));   // - c (s_i S), first half
             asm volatile("" : "+v"(ns[q].x), "+v"(ns[q].y));               // not sunk below the decision
         }
-        d2 = group_sum_uniform<G>(d2) + (up ? -a2_c : a2_c);
+        d2 = group_sum_uniform<G>(d2) + __uint_as_float(__float_as_uint(a2_c) ^ smask);
         const bool accept = l2u_c < d2;                                 // NaN rejects
         if (accept) {
 #pragma unroll
@@ -333,7 +332,7 @@ __global__ void __launch_bounds__(G == 16 ? 256 : 512) crbm_sample_kernel(CrbmSa
                 cc[q] = nn[q];
             }
             lpart = lnew;
-            if (gl == (i_c >> 5)) word ^= 1u << (i_c & 31);
+            word ^= flip;
             ++acc;
         }
         if (traced) {
@@ -347,7 +346,7 @@ __global__ void __launch_bounds__(G == 16 ? 256 : 512) crbm_sample_kernel(CrbmSa
             }
         }
         // advance the pipeline
-        up = (bool)((wbits_n >> (i_n & 31)) & 1u) != (accept && i_n == i_c);
+        smask = smask_b ^ (accept ? same : 0u);
         i_c = i_n;
         l2u_c = l2u_n;
         a2_c = a2_n;
