@@ -181,7 +181,7 @@ __global__ void __launch_bounds__(kRegThreads) ffnn_sample_reg_kernel(FfnnSample
     const FfnnDev &net = A.net;
     const int N = net.widths[0], m1p = net.m1p, m2p = net.m2p, m2 = net.widths[2];
     const int NW = (N + 31) >> 5;
-    const int ldh = K + hs_pad<T>();
+    constexpr int ldh = K + hs_pad<T>();
     const int nwt = (m2 + 31) >> 5;                 // waves that own real outputs
     T *W1l = reinterpret_cast<T *>(smem);           // [N][K]
     T *Hs = W1l + (size_t)N * K;                    // [kRegRows + 1][ldh]
@@ -279,34 +279,44 @@ __global__ void __launch_bounds__(kRegThreads) ffnn_sample_reg_kernel(FfnnSample
         }
     };
     constexpr unsigned kAllRows = (1u << RPW) - 1u;
-    // layer-1 change of flipping i (and j >= 0): W1[:, i] - W1[:, j] of this lane's units, to be weighted by -2 s_i (no
-    // branch: W1[:, max(j, 0)] is read and weighted by 0 for a flip, which leaves W1[:, i] exact)
-    auto delta_z1 = [&](int i, int j, float (&d)[8]) {
-        const frag wi = *reinterpret_cast<const frag *>(W1l + i * K + c8);
-        const frag wj = *reinterpret_cast<const frag *>(W1l + (j >= 0 ? j : 0) * K + c8);
-        const float jm = j >= 0 ? 1.0f : 0.0f;
+    // Layer-1 change of a proposal, this lane's units, to be weighted by -2 s_i: W1[:, i] - W1[:, j] for the chains on their
+    // own, which make exchange moves (a row without a proposal has weight 0), W1[:, i] for the ones together, which flip.
+    // io, jo: byte offsets of the columns in LDS, formed by the proposal's lane, so that no scalar arithmetic is left here.
+    const unsigned char *W1b = reinterpret_cast<const unsigned char *>(W1l) + 2 * c8;
+    auto delta_z1 = [&](int io, int jo, float (&d)[8]) {
+        const frag wi = *reinterpret_cast<const frag *>(W1b + io);
+        if constexpr (PERCHAIN) {
+            const frag wj = *reinterpret_cast<const frag *>(W1b + jo);
+            float minus = -1.0f;
+            if constexpr (std::is_same<T, _Float16>::value) asm("" : "+s"(minus));   // one mixed-precision FMA a unit
 #pragma unroll
-        for (int e = 0; e < 8; ++e) d[e] = fmaf(-jm, Mc<T>::to_f32(wj[e]), Mc<T>::to_f32(wi[e]));
+            for (int e = 0; e < 8; ++e)
+                d[e] = std::is_same<T, _Float16>::value ? fmaf(minus, Mc<T>::to_f32(wj[e]), Mc<T>::to_f32(wi[e]))
+                                                        : Mc<T>::to_f32(wi[e]) - Mc<T>::to_f32(wj[e]);
+        } else {
+#pragma unroll
+            for (int e = 0; e < 8; ++e) d[e] = Mc<T>::to_f32(wi[e]);
+        }
     };
     // h1 = ReLU(z + g d) of one row, this lane's 8 units (g d is exact for g = 0, +-2)
-    auto store_row = [&](int row, const float (&z)[8], float g, const float (&d)[8]) {
+    unsigned char *Hb = reinterpret_cast<unsigned char *>(Hs) + 2 * c8;
+    auto store_row = [&](int row_off, const float (&z)[8], float g, const float (&d)[8]) {
         frag h;
 #pragma unroll
         for (int e = 0; e < 8; ++e) h[e] = Mc<T>::from_f32(fmaxf(fmaf(g, d[e], z[e]), 0.0f));
-        *reinterpret_cast<frag *>(Hs + row * ldh + c8) = h;
+        *reinterpret_cast<frag *>(Hb + row_off) = h;
     };
     // the rows of this wave's chains' proposals: every chain's row is formed, one without a row goes to the spare row
     // kRegRows, so that the code has no branch and later reads overlap earlier stores (but one branch per 1, 2 and 4
     // chains where a wave has fewer)
     auto stage_rows = [&](int slot, int pi, int pj, float si) {
+        const int so = (slot >= 0 ? slot : kRegRows) * (2 * ldh), io = pi * (2 * K), jo = max(pj, 0) * (2 * K);
+        const float g = -2.0f * si;
         auto one = [&](auto r_c) {
             constexpr int r = decltype(r_c)::value;
-            const int sl = __builtin_amdgcn_readlane(slot, r);
-            const int i = __builtin_amdgcn_readlane(pi, r), j = __builtin_amdgcn_readlane(pj, r);
-            const float s_i = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(si), r));
             float d[8];
-            delta_z1(i, j, d);
-            store_row(sl >= 0 ? sl : kRegRows, z1[r], -2.0f * s_i, d);
+            delta_z1(__builtin_amdgcn_readlane(io, r), __builtin_amdgcn_readlane(jo, r), d);
+            store_row(__builtin_amdgcn_readlane(so, r), z1[r], __int_as_float(__builtin_amdgcn_readlane(__float_as_int(g), r)), d);
         };
         one(std::integral_constant<int, 0>{});
         if (rpw > 1) {
@@ -325,15 +335,16 @@ __global__ void __launch_bounds__(kRegThreads) ffnn_sample_reg_kernel(FfnnSample
     };
     // the accepted moves (bit r of um: chain r's) applied to z1
     auto apply_moves = [&](unsigned long long um, int pi, int pj, float si) {
+        const int io = pi * (2 * K), jo = max(pj, 0) * (2 * K);
+        const float g = -2.0f * si;
 #pragma unroll
         for (int r = 0; r < RPW; ++r) {
             if ((um >> r) & 1ull) {
-                const int i = __builtin_amdgcn_readlane(pi, r), j = __builtin_amdgcn_readlane(pj, r);
-                const float s_i = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(si), r));
+                const float gr = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(g), r));
                 float d[8];
-                delta_z1(i, j, d);
+                delta_z1(__builtin_amdgcn_readlane(io, r), __builtin_amdgcn_readlane(jo, r), d);
 #pragma unroll
-                for (int e = 0; e < 8; ++e) z1[r][e] = fmaf(-2.0f * s_i, d[e], z1[r][e]);
+                for (int e = 0; e < 8; ++e) z1[r][e] = fmaf(gr, d[e], z1[r][e]);
             }
         }
     };
@@ -341,7 +352,7 @@ __global__ void __launch_bounds__(kRegThreads) ffnn_sample_reg_kernel(FfnnSample
     auto full_eval = [&]() -> float {
         const float zero[8] = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-        for (int r = 0; r < RPW; ++r) store_row(wave * RPW + r, z1[r], 0.0f, zero);
+        for (int r = 0; r < RPW; ++r) store_row((wave * RPW + r) * (2 * ldh), z1[r], 0.0f, zero);
         __syncthreads();
         if (live)
             for (int t = 0; t < kRegRows / 32; ++t) {
