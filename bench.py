@@ -680,7 +680,7 @@ def run_heis20(a, torch, nqs, workloads):
                       ("gram_T_chunked" if a.gram_chunked else "gram_T_factored"): round(r0["gram_ms"], 3)},
         "eloc_samples_per_s": n_el / (r0["eloc_ms"] * 1e-3),
         "acceptance": r0["acceptance"],
-        "roofline": {"kernel": "deep_gemm_kernel (all layers)", "bound": "mfma", "achieved": round(achieved, 2),
+        "roofline": {"kernel": "deep_frag_gemm_kernel (all layers)", "bound": "mfma", "achieved": round(achieved, 2),
                      "peak": peak, "unit": "TFLOP/s", "frac": round(achieved / peak, 4),
                      "traffic": None, "flops_per_effective_proposal": flops,
                      "note": "about half of the exchange proposals swap equal spins and are not evaluated"},
