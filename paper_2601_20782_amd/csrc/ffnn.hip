@@ -588,8 +588,9 @@ static nqs_status factors_from(const FfnnDev &net, const int8_t *samples, int64_
 }
 
 // O [n][p1 - p0] from the factors: one multiply per value, bound by the writes.  A block writes kExpandSpan
-// consecutive parameters of one sample, so its stores run through memory in order, from the sample's factors in LDS;
-// 16 bytes a store where every layer's rows and O's are multiples of 16 bytes.  4096 samples of the 100-400-200
+// consecutive parameters of one sample, so its stores run through memory in order, from the factors that these meet in
+// LDS (all of a sample's would not fit it for every network that the gradient takes: 165 KB for eight layers of 2,752
+// units); 16 bytes a store where every layer's rows and O's are multiples of 16 bytes.  4096 samples of the 100-400-200
 // network (1.98 GB): 482 us with the factors, 4.5 TB/s for this kernel (a copy reaches 5.2, read and written);
 // 905 us when a block wrote 4 KB of each of 16 samples, 1762 us with one block per sample for everything.
 struct ExpandArgs {
@@ -604,30 +605,51 @@ struct ExpandArgs {
 
 constexpr int kExpandSpan = 16384;
 
+// rows [r0, r0 + result) of layer l's weights that the parameters [b0, b1) meet
+__host__ __device__ inline int expand_rows(const ExpandArgs &E, int l, int64_t b0, int64_t b1, int &r0)
+{
+    const int64_t w0 = E.offW[l], w1 = w0 + (int64_t)E.out[l] * E.in[l];
+    const int64_t s0 = b0 > w0 ? b0 : w0, s1 = b1 < w1 ? b1 : w1;
+    if (s0 >= s1) return 0;
+    const unsigned in = (unsigned)E.in[l];           // a layer has at most 8192^2 weights
+    r0 = (int)((unsigned)(s0 - w0) / in);
+    return (int)((unsigned)(s1 - 1 - w0) / in) - r0 + 1;
+}
+
+// LDS floats of a layer of which `rows` rows are met: its inputs, then the rows' deltas, each a multiple of 16 bytes
+__host__ __device__ inline int expand_words(int in, int rows) { return rows > 0 ? ((in + 3) & ~3) + ((rows + 3) & ~3) : 0; }
+
 // V consecutive parameters per thread and store (1, or 4 where every row is a multiple of 4 floats)
 template <int V>
 __global__ void __launch_bounds__(256) ffnn_expand_kernel(ExpandArgs E, int spans)
 {
-    extern __shared__ __align__(16) float fac[];   // the sample's deltas [sd], then its layer inputs [sa]
+    extern __shared__ __align__(16) float fac[];   // of each layer whose weights the span meets: inputs, rows' deltas
     const int64_t k = blockIdx.x / spans;
     const int tid = threadIdx.x;
     const int64_t b0 = E.p0 + (int64_t)(blockIdx.x - k * spans) * kExpandSpan, b1 = min(E.p1, b0 + kExpandSpan);
-    float *ds = fac, *as = fac + ((E.sd + 3) & ~(int64_t)3);
-    // only the layers that the span meets
+    const float *acts = E.acts + k * E.sa, *dels = E.dels + k * E.sd;
+    float *f = fac;
     for (int l = 0; l < E.L; ++l) {
-        if (E.offW[l + 1] <= b0 || E.offW[l] >= b1) continue;
-        for (int i = tid; i < E.out[l]; i += 256) ds[E.offD[l] + i] = E.dels[k * E.sd + E.offD[l] + i];
-        for (int i = tid; i < E.in[l]; i += 256) as[E.offA[l] + i] = E.acts[k * E.sa + E.offA[l] + i];
+        int r0 = 0;
+        const int in = E.in[l], rows = expand_rows(E, l, b0, b1, r0);
+        if (rows == 0) continue;
+        float *d = f + ((in + 3) & ~3);
+        for (int i = tid; i < in; i += 256) f[i] = acts[E.offA[l] + i];
+        for (int i = tid; i < rows; i += 256) d[i] = dels[E.offD[l] + r0 + i];
+        f += expand_words(in, rows);
     }
     __syncthreads();
     float *O = E.O + k * (E.p1 - E.p0) - E.p0;
+    f = fac;
     for (int l = 0; l < E.L; ++l) {
-        const int in = E.in[l];
+        int r0 = 0;
+        const int in = E.in[l], rows = expand_rows(E, l, b0, b1, r0);
         const int64_t w0 = E.offW[l], w1 = w0 + (int64_t)E.out[l] * in;
-        const float *d = ds + E.offD[l], *a = as + E.offA[l];
         // weights: position q = r in + c, advanced by 256 V with (r, c) carried
-        const int64_t s0 = max(b0, w0), s1 = min(b1, w1);
-        if (s0 < s1) {
+        if (rows > 0) {
+            const float *a = f, *d = f + ((in + 3) & ~3) - r0;
+            f += expand_words(in, rows);
+            const int64_t s0 = max(b0, w0), s1 = min(b1, w1);
             const int64_t q0 = s0 - w0 + tid * V;
             int r = (int)(q0 / in), c = (int)(q0 - (int64_t)r * in);
             const int dr = 256 * V / in, dc = 256 * V - dr * in;
@@ -647,8 +669,28 @@ __global__ void __launch_bounds__(256) ffnn_expand_kernel(ExpandArgs E, int span
                 }
             }
         }
-        for (int64_t p = max(b0, w1) + tid; p < min(b1, E.offW[l + 1]); p += 256) O[p] = d[p - w1];
+        // biases: the deltas themselves
+        for (int64_t p = max(b0, w1) + tid; p < min(b1, E.offW[l + 1]); p += 256) O[p] = dels[E.offD[l] + (p - w1)];
     }
+}
+
+// LDS floats of the span that needs most.  At most kExpandSpan (rows met, and the inputs of layers that lie within the
+// span) and the inputs of the two layers at its ends, 8192 each: 128 KB.
+static int expand_lds_words(const ExpandArgs &E)
+{
+    int words = 0;
+    for (int l = 0; l < E.L; ++l) {
+        if (E.offW[l + 1] <= E.p0 || E.offW[l] >= E.p1) continue;
+        // a span within the layer
+        words = std::max(words, expand_words(E.in[l], std::min(E.out[l], kExpandSpan / E.in[l] + 2)));
+        // the span that the layer ends in
+        if (E.offW[l + 1] >= E.p1) continue;
+        const int64_t b0 = E.p0 + (E.offW[l + 1] - E.p0) / kExpandSpan * kExpandSpan, b1 = std::min(E.p1, b0 + kExpandSpan);
+        int sum = 0, r0;
+        for (int j = 0; j < E.L; ++j) sum += expand_words(E.in[j], expand_rows(E, j, b0, b1, r0));
+        words = std::max(words, sum);
+    }
+    return words;
 }
 
 static ExpandArgs expand_args(const FfnnDev &net)
@@ -678,8 +720,9 @@ static nqs_status expand_columns(ExpandArgs E, int64_t n, int64_t p0, int64_t p1
     E.p1 = p1;
     bool vec = (p1 - p0) % 4 == 0 && p0 % 4 == 0 && (uintptr_t)O % 16 == 0;
     for (int l = 0; l < E.L; ++l) vec = vec && E.in[l] % 4 == 0 && E.out[l] % 4 == 0;
-    const int64_t spans = (p1 - p0 + kExpandSpan - 1) / kExpandSpan, most = INT32_MAX / spans;   // samples per launch
-    const size_t lds = sizeof(float) * (size_t)(((E.sd + 3) & ~(int64_t)3) + E.sa);
+    const int64_t spans = (p1 - p0 + kExpandSpan - 1) / kExpandSpan;
+    const int64_t most = (((int64_t)1 << 24) - 1) / spans;   // samples per launch: fewer than 2^32 threads
+    const size_t lds = sizeof(float) * (size_t)expand_lds_words(E);
     for (int64_t k0 = 0; k0 < n; k0 += most) {
         ExpandArgs C = E;
         C.n = std::min(most, n - k0);
