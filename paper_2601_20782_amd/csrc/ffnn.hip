@@ -431,6 +431,7 @@ __global__ void __launch_bounds__(256) ffnn_grad_kernel(GradArgs A)
 // launches; the products take half of it) against 175 us with one block per sample, whose sums wait for L2.
 // ---------------------------------------------------------------------------
 constexpr int kGmTile = 64, kGmStep = 32, kGmLdx = 36, kGmLdb = 80;
+constexpr int64_t kFactorSamples = 65535 * (int64_t)kGmTile;   // of one launch (tiles of samples along the grid's y)
 typedef float gm_f32x4 __attribute__((ext_vector_type(4)));
 
 struct FactorGemmArgs {
@@ -567,7 +568,7 @@ static nqs_status factors_from(const FfnnDev &net, const int8_t *samples, int64_
         sd += net.widths[l + 1];
     }
     const int64_t sb = (n * N + 255) / 256, my = (n + kGmTile - 1) / kGmTile;
-    if (sb > INT32_MAX || my > 65535) return set_error(NQS_EINVAL, "too many samples");
+    if (n > kFactorSamples) return set_error(NQS_EINVAL, "too many samples");
     hipLaunchKernelGGL(ffnn_factor_spins_kernel, dim3((unsigned)sb), dim3(256), 0, stream, samples, n, N, sa, acts);
     auto gemm = [&](const FactorGemmArgs &G) {
         hipLaunchKernelGGL(ffnn_factor_gemm_kernel, dim3((unsigned)((G.N + kGmTile - 1) / kGmTile), (unsigned)my),
@@ -773,8 +774,7 @@ nqs_status ffnn_logpsi_grad(nqs_model *m, const int8_t *samples, int64_t n, floa
     } else if (logpsi || O) {
         ExpandArgs E = expand_args(net);
         const int64_t per = E.sa + E.sd;
-        const int64_t chunk = std::max<int64_t>(1, std::min<int64_t>({n, (int64_t)(kLeaseBytes / sizeof(float)) / per,
-                                                                           (int64_t)4 << 20}));
+        const int64_t chunk = std::max<int64_t>(1, std::min({n, (int64_t)(kLeaseBytes / sizeof(float)) / per, kFactorSamples}));
         const ScratchLease lease(sizeof(float) * (size_t)(chunk * per), stream);
         if (!lease.ptr()) return set_error(NQS_ENOMEM, "scratch allocation failed");
         float *acts = (float *)lease.ptr(), *dels = acts + chunk * E.sa;
@@ -793,7 +793,7 @@ nqs_status ffnn_logpsi_grad(nqs_model *m, const int8_t *samples, int64_t n, floa
         // at a time (100-400-200, 6000 samples: 0.18 ms, half of it the products, against 6.7 ms through blocks of O)
         ExpandArgs E = expand_args(net);
         const int64_t per = E.sa + E.sd;
-        const int64_t chunk = std::max<int64_t>(1, std::min<int64_t>({n, ((int64_t)64 << 20) / per, (int64_t)4 << 20}));
+        const int64_t chunk = std::max<int64_t>(1, std::min({n, ((int64_t)64 << 20) / per, kFactorSamples}));
         FacLayerDesc lay[NQS_MAX_LAYERS];
         for (int l = 0; l < E.L; ++l) lay[l] = FacLayerDesc{nullptr, nullptr, E.sd, E.sa, E.out[l], E.in[l], 0, nullptr};
         const size_t fb = (sizeof(float) * (size_t)(chunk * per) + 255) & ~(size_t)255;
