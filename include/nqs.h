@@ -31,8 +31,13 @@
  * Conventions (every entry point):
  *   - All array arguments are DEVICE pointers unless marked "host".  The
  *     caller allocates and owns every buffer; the library owns only the model
- *     handle (its reduced-precision weight copies and lookup tables) and a
- *     per-device workspace it grows on demand.
+ *     handle (its reduced-precision weight copies and lookup tables), a
+ *     per-device workspace it grows on demand, and per device up to eight
+ *     scratch buffers of 64 MB, given back with the last model, that log psi
+ *     and log-derivatives of dense networks and local energies of
+ *     convolutional ones hold while they run.  Calls of these on up to eight
+ *     streams do not wait for one another; where a buffer cannot be had they
+ *     run without, slower.
  *   - Calls are stream ordered and asynchronous: `stream` is a hipStream_t
  *     (NULL = the default stream).  Argument validation happens on the host
  *     before any launch; a rejected call launches nothing.

@@ -2,7 +2,9 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <atomic>
 #include <cmath>
+#include <condition_variable>
 #include <cstring>
 #include <mutex>
 #include <string>
@@ -91,53 +93,107 @@ void *workspace_slot(int slot, size_t bytes, hipStream_t stream)
 void *workspace(size_t bytes, hipStream_t stream) { return workspace_slot(0, bytes, stream); }
 
 // ---- scratch of one call (ScratchLease) ----
-struct LeaseSlot {
-    std::mutex mu;
+struct ScratchBuffer {
     void *ptr = nullptr;
-    size_t bytes = 0;
-    hipEvent_t done = nullptr;
-    bool used = false;
+    hipEvent_t done = nullptr;     // behind the last holder's kernels
+    hipStream_t last = nullptr;    // the last holder's stream (a preference only: the event orders the calls)
+    uint64_t turn = 0;             // when it was handed back
+    bool held = false, used = false;
 };
-constexpr int kLeaseDevices = 64;
-static LeaseSlot g_lease[kLeaseDevices];
+struct ScratchPool {
+    std::mutex mu;
+    std::condition_variable back;
+    ScratchBuffer buf[kScratchBuffers];
+    int n = 0;
+    uint64_t turns = 0;
+};
+constexpr int kScratchDevices = 64;
+static ScratchPool g_scratch[kScratchDevices];
+static std::atomic<int64_t> g_models{0};
 
-ScratchLease::ScratchLease(size_t bytes, hipStream_t stream) : stream_(stream)
+// Another thread's capture in global mode would refuse the allocation.
+struct RelaxedCapture {
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    bool ok;
+    RelaxedCapture() : ok(hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess) {}
+    ~RelaxedCapture()
+    {
+        if (ok) (void)hipThreadExchangeStreamCaptureMode(&mode);
+    }
+};
+
+static bool scratch_new(ScratchBuffer &b)
+{
+    const RelaxedCapture relaxed;
+    if (hipMalloc(&b.ptr, kScratchBytes) == hipSuccess) {
+        if (hipEventCreateWithFlags(&b.done, hipEventDisableTiming) == hipSuccess) return true;
+        (void)hipFree(b.ptr);
+    }
+    (void)hipGetLastError();   // the caller does without
+    b = ScratchBuffer();
+    return false;
+}
+
+ScratchLease::ScratchLease(hipStream_t stream) : stream_(stream)
 {
     int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kLeaseDevices) return;
-    LeaseSlot &l = g_lease[dev];
-    l.mu.lock();
-    dev_ = dev;
-    if (!l.done && hipEventCreateWithFlags(&l.done, hipEventDisableTiming) != hipSuccess) {
-        l.done = nullptr;
-        return;
-    }
-    if (l.bytes < bytes) {
-        if (l.used && hipEventSynchronize(l.done) != hipSuccess) return;
-        l.used = false;
-        if (l.ptr) (void)hipFree(l.ptr);
-        l.ptr = nullptr;
-        l.bytes = 0;
-        const size_t want = std::max<size_t>(bytes, (size_t)1 << 20);
-        if (hipMalloc(&l.ptr, want) != hipSuccess) {
-            l.ptr = nullptr;
-            return;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kScratchDevices) return;
+    ScratchPool &p = g_scratch[dev];
+    {
+        std::unique_lock<std::mutex> lock(p.mu);
+        ScratchBuffer *b = nullptr;
+        while (!b) {
+            ScratchBuffer *oldest = nullptr;
+            for (int i = 0; i < p.n; ++i) {
+                ScratchBuffer &c = p.buf[i];
+                if (c.held) continue;
+                if (c.last == stream) b = &c;
+                if (!oldest || c.turn < oldest->turn) oldest = &c;
+            }
+            if (!b && p.n < kScratchBuffers && scratch_new(p.buf[p.n])) b = &p.buf[p.n++];
+            if (!b) b = oldest;
+            if (!b && p.n == 0) return;
+            if (!b) p.back.wait(lock);
         }
-        l.bytes = want;
+        b->held = true;
+        buf_ = b;
     }
-    if (l.used && hipStreamWaitEvent(stream, l.done, 0) != hipSuccess) return;
-    ptr_ = l.ptr;
+    dev_ = dev;
+    if (!buf_->used || hipStreamWaitEvent(stream, buf_->done, 0) == hipSuccess) ptr_ = buf_->ptr;
+    else (void)hipGetLastError();
 }
 
 ScratchLease::~ScratchLease()
 {
-    if (dev_ < 0) return;
-    LeaseSlot &l = g_lease[dev_];
+    if (!buf_) return;
     if (ptr_) {
-        l.used = hipEventRecord(l.done, stream_) == hipSuccess;
-        if (!l.used) (void)hipStreamSynchronize(stream_);
+        buf_->last = stream_;
+        buf_->used = hipEventRecord(buf_->done, stream_) == hipSuccess;
+        if (!buf_->used) (void)hipStreamSynchronize(stream_);
     }
-    l.mu.unlock();
+    ScratchPool &p = g_scratch[dev_];
+    {
+        const std::lock_guard<std::mutex> lock(p.mu);
+        buf_->held = false;
+        buf_->turn = ++p.turns;
+    }
+    p.back.notify_one();
+}
+
+// the last model is gone (and with it every call): the buffers go back
+static void scratch_release()
+{
+    const RelaxedCapture relaxed;
+    for (ScratchPool &p : g_scratch) {
+        const std::lock_guard<std::mutex> lock(p.mu);
+        for (int i = 0; i < p.n; ++i) {
+            if (p.buf[i].used) (void)hipEventSynchronize(p.buf[i].done);
+            (void)hipEventDestroy(p.buf[i].done);
+            (void)hipFree(p.buf[i].ptr);
+            p.buf[i] = ScratchBuffer();
+        }
+        p.n = 0;
+    }
 }
 
 bool stream_capturing(hipStream_t stream)
@@ -256,6 +312,7 @@ nqs_status nqs_model_create(const nqs_model_desc *desc, const double *host_param
     if (e != hipSuccess) { (void)hipFree(m->master); delete m; return hip_error(e, "hipMalloc(scratch)"); }
     e = hipMemcpy(m->master, host_params, sizeof(double) * P, hipMemcpyHostToDevice);
     if (e != hipSuccess) { (void)hipFree(m->master); (void)hipFree(m->wb_f32); delete m; return hip_error(e, "hipMemcpy(master)"); }
+    ++g_models;
     *out = m;
     return NQS_OK;
 }
@@ -292,6 +349,7 @@ nqs_status nqs_model_destroy(nqs_model *m)
     (void)hipFree(m->master);
     (void)hipFree(m->wb_f32);
     delete m;
+    if (--g_models == 0) scratch_release();
     return NQS_OK;
 }
 

@@ -1058,35 +1058,33 @@ nqs_status cnn_local_energy(nqs_model *m, const nqs_ham_desc &ham, const int8_t 
     const int L = net.L, S = L * L, F = net.F;
     // 16 and 32 channels on up to 256 sites whose batch fits LDS: the batched forward pass, whose log psi are the
     // one-configuration kernel's bit for bit (beyond 256 sites a thread of that kernel sums two sites' channels as one
-    // chain).  A captured call takes the one-configuration kernel, which needs no scratch.
+    // chain).  A captured call and one that gets no scratch take the one-configuration kernel, which needs none.
     if ((F == 16 || F == 32) && S <= kCnnThreads && cnn_mc_lds_bytes(1, S, F, 4) <= 160 * 1024 &&
         !stream_capturing(stream)) {
-        // log psi values kept at a time: 64 MB of scratch
-        const int64_t chunk = std::max<int64_t>(1, std::min<int64_t>(n, ((int64_t)16 << 20) / (S + 1)));
-        const ScratchLease lease(sizeof(float) * (size_t)chunk * (S + 1), stream);
-        float *f = (float *)lease.ptr();
-        if (!f) return set_error(NQS_ENOMEM, "scratch allocation failed");
-        for (int64_t k0 = 0; k0 < n; k0 += chunk) {
-            const int64_t kn = std::min(chunk, n - k0), count = kn * (S + 1);
-            const int B = cnn_mc_batch(S, F, 4, count);
-            const size_t lds = cnn_mc_lds_bytes(B, S, F, 4);
-            const int64_t per_cu = lds <= 80 * 1024 ? 2 : 1;
-            const int64_t blocks = std::min<int64_t>((count + B - 1) / B, per_cu * device_cus());
-            if (F == 16) {
-                allow_lds(cnn_eloc_logpsi_kernel<16>, lds);
-                hipLaunchKernelGGL((cnn_eloc_logpsi_kernel<16>), dim3((unsigned)blocks), dim3(kMcThreads), lds, stream,
-                                   net, samples + k0 * S, kn, B, f);
-            } else {
-                allow_lds(cnn_eloc_logpsi_kernel<32>, lds);
-                hipLaunchKernelGGL((cnn_eloc_logpsi_kernel<32>), dim3((unsigned)blocks), dim3(kMcThreads), lds, stream,
-                                   net, samples + k0 * S, kn, B, f);
+        const ScratchLease lease(stream);
+        if (float *f = (float *)lease.ptr()) {
+            // the samples whose log psi values the scratch holds
+            const int64_t chunk = std::min<int64_t>(n, (int64_t)(kScratchBytes / sizeof(float)) / (S + 1));
+            for (int64_t k0 = 0; k0 < n; k0 += chunk) {
+                const int64_t kn = std::min(chunk, n - k0), count = kn * (S + 1);
+                const int B = cnn_mc_batch(S, F, 4, count);
+                const size_t lds = cnn_mc_lds_bytes(B, S, F, 4);
+                const int64_t per_cu = lds <= 80 * 1024 ? 2 : 1;
+                const int64_t blocks = std::min<int64_t>((count + B - 1) / B, per_cu * device_cus());
+                auto launch = [&](auto kernel) {
+                    allow_lds(kernel, lds);
+                    hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(kMcThreads), lds, stream, net,
+                                       samples + k0 * S, kn, B, f);
+                };
+                if (F == 16) launch(cnn_eloc_logpsi_kernel<16>);
+                else launch(cnn_eloc_logpsi_kernel<32>);
+                NQS_HIP_TRY(hipGetLastError());
+                hipLaunchKernelGGL(cnn_eloc_reduce_kernel, dim3((unsigned)((kn + 3) / 4)), dim3(256), 0, stream,
+                                   samples + k0 * S, f, kn, L, ham.J, ham.h, eloc + k0);
+                NQS_HIP_TRY(hipGetLastError());
             }
-            NQS_HIP_TRY(hipGetLastError());
-            hipLaunchKernelGGL(cnn_eloc_reduce_kernel, dim3((unsigned)((kn + 3) / 4)), dim3(256), 0, stream,
-                               samples + k0 * S, f, kn, L, ham.J, ham.h, eloc + k0);
-            NQS_HIP_TRY(hipGetLastError());
+            return NQS_OK;
         }
-        return NQS_OK;
     }
     const size_t lds = cnn_lds_bytes(S, F);
     allow_lds(cnn_eloc_tfim_kernel, lds);

@@ -758,35 +758,39 @@ nqs_status ffnn_logpsi_grad(nqs_model *m, const int8_t *samples, int64_t n, floa
     const size_t lds = sizeof(float) * (size_t)A.lds_stride * (1 + net.n_layers + 2);
     if (lds > 160 * 1024) return set_error(NQS_EUNSUPPORTED, "network too wide for the gradient kernel");
     allow_lds(ffnn_grad_kernel, lds);
-    // Small calls, and calls under capture (no scratch), take one block per sample; the others form the factors
+    // Small calls, and calls under capture or without scratch, take one block per sample; the others form the factors
     // and expand them, chunk by chunk.  The values are the same bit for bit.  The line: 16-64-32, 512 samples 36 us as one
     // block per sample (its chains' latency; 126 us at 4096 samples against 43), 36-144-72, 64 samples 68 against 39;
     // log psi alone 36-144-72, 1024 samples 21 against 28 (five launches), 64-256-128 34 against 29.
     const double P = (double)m->P, nP = (double)n * P;
     const bool small = O ? P < 1.2e4 && nP < 2.5e6 : P < 3.0e4 && nP < 3.0e7;
-    if ((logpsi || O) && (small || stream_capturing(stream))) {
+    bool todo = logpsi || O;
+    if (todo && !small && !stream_capturing(stream)) {
+        const ScratchLease lease(stream);
+        if (float *acts = (float *)lease.ptr()) {
+            ExpandArgs E = expand_args(net);
+            const int64_t per = E.sa + E.sd;
+            const int64_t chunk = std::min({n, (int64_t)(kScratchBytes / sizeof(float)) / per, kFactorSamples});
+            float *dels = acts + chunk * E.sa;
+            E.acts = acts;
+            E.dels = dels;
+            for (int64_t k0 = 0; k0 < n; k0 += chunk) {
+                const int64_t kn = std::min(chunk, n - k0);
+                st = factors_from(net, samples + k0 * net.widths[0], kn, acts, dels, logpsi ? logpsi + k0 : nullptr,
+                                  O != nullptr, stream);
+                if (st == NQS_OK && O) st = expand_columns(E, kn, p0, p1, O + k0 * (p1 - p0), stream);
+                if (st != NQS_OK) return st;
+            }
+            todo = false;
+        }
+    }
+    if (todo) {
         A.samples = samples;
         A.n = n;
         A.logpsi = logpsi;
         A.O = O;
         hipLaunchKernelGGL(ffnn_grad_kernel, dim3((unsigned)std::min<int64_t>(n, 4096)), dim3(256), lds, stream, A);
         NQS_HIP_TRY(hipGetLastError());
-    } else if (logpsi || O) {
-        ExpandArgs E = expand_args(net);
-        const int64_t per = E.sa + E.sd;
-        const int64_t chunk = std::max<int64_t>(1, std::min({n, (int64_t)(kLeaseBytes / sizeof(float)) / per, kFactorSamples}));
-        const ScratchLease lease(sizeof(float) * (size_t)(chunk * per), stream);
-        if (!lease.ptr()) return set_error(NQS_ENOMEM, "scratch allocation failed");
-        float *acts = (float *)lease.ptr(), *dels = acts + chunk * E.sa;
-        E.acts = acts;
-        E.dels = dels;
-        for (int64_t k0 = 0; k0 < n; k0 += chunk) {
-            const int64_t kn = std::min(chunk, n - k0);
-            st = factors_from(net, samples + k0 * net.widths[0], kn, acts, dels, logpsi ? logpsi + k0 : nullptr,
-                              O != nullptr, stream);
-            if (st == NQS_OK && O) st = expand_columns(E, kn, p0, p1, O + k0 * (p1 - p0), stream);
-            if (st != NQS_OK) return st;
-        }
     }
     if (vjp_in) {
         // sum_k g_k delta_k (x) a_k per layer on the FP64 matrix cores, from the factors of up to 256 MiB of samples

@@ -145,21 +145,26 @@ void *workspace(size_t bytes, hipStream_t stream);
 constexpr int kWorkspaceSlots = 3;
 void *workspace_slot(int slot, size_t bytes, hipStream_t stream);
 
-// Scratch of one call, for entry points that any thread and stream may use at the same time: one buffer per
-// device, grown on demand, that a call holds while it enqueues its kernels.  The holder's stream first waits for
-// the event that the previous holder recorded behind its last kernel, so calls on different streams take turns
-// on the device; a mutex keeps the launches of two threads from interleaving.  Callers ask for at most
-// kLeaseBytes (larger problems are cut into chunks) and not from a stream that is being captured (a captured
-// graph would keep the address of a buffer that may grow, hence move, before a replay).
-constexpr size_t kLeaseBytes = (size_t)256 << 20;
+// Scratch of one call, for entry points that any thread and stream may use at the same time: up to kScratchBuffers
+// buffers of kScratchBytes per device, made when they are first needed and given back when the last model is destroyed.
+// A call holds one while it enqueues its kernels (no other thread's call gets it meanwhile), and its stream first waits
+// for the event behind the previous holder's kernels.  A stream is handed the buffer that it used last, else a new one,
+// so calls on up to kScratchBuffers streams wait for none of each other's; beyond, on the one handed back longest ago.
+// No call waits on the host for the device.  Callers cut larger problems into chunks, do without scratch where there is
+// none to be had (ptr() is NULL), and do not ask from a stream that is being captured (a captured graph would keep the
+// address of a buffer that other calls use at its replays).
+constexpr size_t kScratchBytes = (size_t)64 << 20;
+constexpr int kScratchBuffers = 8;
+struct ScratchBuffer;
 class ScratchLease {
 public:
-    ScratchLease(size_t bytes, hipStream_t stream);
+    explicit ScratchLease(hipStream_t stream);
     ~ScratchLease();
     ScratchLease(const ScratchLease &) = delete;
     ScratchLease &operator=(const ScratchLease &) = delete;
-    void *ptr() const { return ptr_; }   // nullptr: the allocation failed
+    void *ptr() const { return ptr_; }
 private:
+    ScratchBuffer *buf_ = nullptr;
     void *ptr_ = nullptr;
     int dev_ = -1;
     hipStream_t stream_;
