@@ -959,8 +959,10 @@ struct DeepBuffers {
     int *counter, *row_chain, *row_i, *row_j;
     void *H[2];
     float *part;
-    int npart;
+    int64_t npart;
 };
+// (its bytes are part of the sweep graph's signature: no padding, which would differ from call to call)
+static_assert(std::has_unique_object_representations_v<DeepBuffers>, "no padding");
 
 static size_t al256(size_t x) { return (x + 255) & ~(size_t)255; }
 
