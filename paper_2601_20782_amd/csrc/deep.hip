@@ -1195,10 +1195,13 @@ nqs_status deep_sample(nqs_model *m, const nqs_sample_cfg &cfg, int8_t *chain_st
     // Two or more sweeps: capture one sweep's launches (proposal, forward pass, decision for each
     // of its proposals, then the sample emit) once into a graph and replay it per sweep; the proposal index and
     // the sweep come from a device counter that the graph's last node advances, so every replay is the same graph.
+    // (The FP32 copy's steps are long, so with odd sweep sizes, mostly flips on small lattices, capturing costs more than
+    // it saves: 1,000 chains, two sweeps of 9, 49, 81 and 225 flips take 0.84, 6.06, 13.3 and 72.4 ms with a graph and
+    // 0.77, 5.84, 12.9 and 70.8 ms without.)
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
     NQS_HIP_TRY(hipStreamIsCapturing(stream, &cap));
     const int n_sw = cfg.n_burnin + cfg.n_sweeps;
-    if (n_sw >= 2 && cap == hipStreamCaptureStatusNone) {
+    if (n_sw >= 2 && (sw % 2 == 0 || cfg.dtype != NQS_F32) && cap == hipStreamCaptureStatusNone) {
         a.kbase = kbase;
         hipLaunchKernelGGL(deep_set_i64_kernel, dim3(1), dim3(1), 0, stream, kbase, (int64_t)0, (int64_t)0);
         std::string sig;
