@@ -81,15 +81,32 @@ __device__ inline double fac_aug(const float *F, int64_t ld, int d, int64_t n, i
     return j == d ? 1.0 : (double)F[k * ld + j];
 }
 
+// The vector-Jacobian product's parameter order: with c = 1 (RBM) [row du, column dv, inner block], else [inner block,
+// column dv] of each layer in turn.  The first parameter of layer l, and the place in it of entry (r, c) of its sums
+// (-1: no parameter).
+__device__ __forceinline__ int64_t fac_vjp_first(const FacArgs &A, int l)
+{
+    int64_t off = 0;
+    for (int i = 0; i < l; ++i) off += (int64_t)A.lay[i].du * (A.lay[i].dv + 1) + (A.lay[i].c ? A.lay[i].dv : 0);
+    return off;
+}
+__device__ __forceinline__ int64_t fac_vjp_place(const FacLayer &y, int r, int c)
+{
+    if (r < y.du) return c < y.dv ? (y.c ? y.dv + y.du : 0) + (int64_t)r * y.dv + c : (y.c ? y.dv : (int64_t)y.du * y.dv) + r;
+    return c < y.dv && y.c ? c : -1;
+}
+
 // Sums of g_k [U_k,1] (x) [V_k,1] (g = 1 without `g`) over the samples of one split (blockIdx.y), one 64 x 64 tile
-// of one layer per block (blockIdx.x), to mpart, or added to it (`add`).  The products of two FP32 factors and of
-// g with one are exact in FP64.  Both operands are read along the samples, 32 of them per barrier with the next 32
-// already in registers (the row stride of 80 floats spreads a fragment read over all banks): a block's four waves
-// then wait for the matrix cores, 2048 cycles per 32 samples, and not for memory.  Mean matrices of the 100-400-200
-// network, 6000 samples: 118 us on the vector units, 90 us (1.45 GFLOP; 64-bit vector and matrix rates are alike,
-// the vector form waited for its LDS reads).
+// of one layer per block (blockIdx.x), to mpart, or added to it (`add`), or, where one split holds all samples, straight
+// to the gradient `vjp` (400 x 1600 RBM, 100 samples: 252 us with the sums written, read and reduced, 196 us without).
+// The products of two FP32 factors and of g with one are exact in FP64.  Both operands are read along the samples, 32 of
+// them per barrier with the next 32 already in registers (the row stride of 80 floats spreads a fragment read over all
+// banks): a block's four waves then wait for the matrix cores, 2048 cycles per 32 samples, and not for memory.  Mean
+// matrices of the 100-400-200 network, 6000 samples: 118 us on the vector units, 90 us (1.45 GFLOP; 64-bit vector and
+// matrix rates are alike, the vector form waited for its LDS reads).
 constexpr int kOutLd = 80;
-__global__ void __launch_bounds__(256) fac_outer_kernel(FacArgs A, const float *__restrict__ g, int add)
+__global__ void __launch_bounds__(256) fac_outer_kernel(FacArgs A, const float *__restrict__ g, int add,
+                                                        float *__restrict__ vjp)
 {
     __shared__ float Us[2][kFK * kOutLd], Vs[2][kFK * kOutLd], gs[2][kFK];
     const int l = fac_layer_of(A, blockIdx.x, false);
@@ -155,6 +172,7 @@ __global__ void __launch_bounds__(256) fac_outer_kernel(FacArgs A, const float *
     }
     // D[i][j] of a 16 x 16 FP64 block: j = lane % 16, i = lane / 16 + 4 * register
     double *out = A.mpart + (int64_t)blockIdx.y * A.mtot + y.moff;
+    if (vjp) vjp += fac_vjp_first(A, l);
 #pragma unroll
     for (int a = 0; a < 2; ++a)
 #pragma unroll
@@ -163,6 +181,11 @@ __global__ void __launch_bounds__(256) fac_outer_kernel(FacArgs A, const float *
             for (int q = 0; q < 4; ++q) {
                 const int r = r0 + wm + 16 * a + lk + 4 * q, c = c0 + wn + 16 * b + la;
                 if (r > y.du || c > y.dv) continue;
+                if (vjp) {
+                    const int64_t p = fac_vjp_place(y, r, c);
+                    if (p >= 0) vjp[p] = (float)(0.0 + acc[a][b][q]);
+                    continue;
+                }
                 double *o = out + (int64_t)r * (y.dv + 1) + c;
                 *o = add ? *o + acc[a][b][q] : acc[a][b][q];
             }
@@ -177,26 +200,18 @@ __device__ __forceinline__ double fac_split_sum(const FacArgs &A, int64_t e)
     return s;
 }
 
-// The sums of fac_outer_kernel as the gradient in parameter order: with c = 1 (RBM) [row du, column dv, inner
-// block], else [inner block, column dv] of each layer in turn.
+// The sums of fac_outer_kernel as the gradient in parameter order
 __global__ void __launch_bounds__(256) fac_vjp_reduce_kernel(FacArgs A, float *__restrict__ out)
 {
     const int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
     if (e >= A.mtot) return;
     int l = 0;
-    int64_t off = 0;
-    while (l + 1 < A.L && e >= A.lay[l + 1].moff) {
-        off += (int64_t)A.lay[l].du * (A.lay[l].dv + 1) + (A.lay[l].c ? A.lay[l].dv : 0);
-        ++l;
-    }
+    while (l + 1 < A.L && e >= A.lay[l + 1].moff) ++l;
     const FacLayer &y = A.lay[l];
-    const int64_t q = e - y.moff, nw = (int64_t)y.du * y.dv;
+    const int64_t q = e - y.moff;
     const int r = (int)(q / (y.dv + 1)), c = (int)(q - (int64_t)r * (y.dv + 1));
-    int64_t p;
-    if (r < y.du) p = c < y.dv ? (y.c ? y.dv + y.du : 0) + (int64_t)r * y.dv + c : (y.c ? y.dv : nw) + r;
-    else if (c < y.dv && y.c) p = c;
-    else return;
-    out[off + p] = (float)fac_split_sum(A, e);
+    const int64_t p = fac_vjp_place(y, r, c);
+    if (p >= 0) out[fac_vjp_first(A, l) + p] = (float)fac_split_sum(A, e);
 }
 
 // M_l = (1/n) (sum of the splits in order), masked: the (du, dv) corner is 0 and
@@ -537,8 +552,10 @@ nqs_status launch_fac_vjp(const FacLayerDesc *lay, int L, int64_t n, int64_t n_f
     FacArgs A = fac_args(lay, L, n, p, nullptr);
     A.mpart = (double *)wsp;
     if (p.mt > INT32_MAX || (p.mtot + 255) / 256 > INT32_MAX) return set_error(NQS_EINVAL, "network too large");
-    hipLaunchKernelGGL(fac_outer_kernel, dim3((unsigned)p.mt, (unsigned)p.splits), dim3(256), 0, stream, A, g, add ? 1 : 0);
-    if (vjp_out)
+    const bool whole = vjp_out && !add && p.splits == 1;
+    hipLaunchKernelGGL(fac_outer_kernel, dim3((unsigned)p.mt, (unsigned)p.splits), dim3(256), 0, stream, A, g, add ? 1 : 0,
+                       whole ? vjp_out : nullptr);
+    if (vjp_out && !whole)
         hipLaunchKernelGGL(fac_vjp_reduce_kernel, dim3((unsigned)((p.mtot + 255) / 256)), dim3(256), 0, stream, A,
                            vjp_out);
     NQS_HIP_TRY(hipGetLastError());
@@ -569,7 +586,7 @@ nqs_status launch_fac_gram(const FacLayerDesc *lay, int L, int64_t n, float *T, 
         return set_error(NQS_EINVAL, "sample-space Gram matrix too large");
 
     hipLaunchKernelGGL(fac_outer_kernel, dim3((unsigned)p.mt, (unsigned)p.splits), dim3(256), 0, stream, A,
-                       (const float *)nullptr, 0);
+                       (const float *)nullptr, 0, (float *)nullptr);
     hipLaunchKernelGGL(fac_mean_reduce_kernel, dim3((unsigned)p.m2blocks), dim3(256), 0, stream, A);
     hipLaunchKernelGGL(fac_v_kernel, dim3((unsigned)ktiles, (unsigned)p.vs), dim3(256), 0, stream, A);
     hipLaunchKernelGGL(fac_vsum_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, stream, A);
