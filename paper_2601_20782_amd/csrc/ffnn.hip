@@ -761,9 +761,13 @@ nqs_status ffnn_logpsi_grad(nqs_model *m, const int8_t *samples, int64_t n, floa
     // Small calls, and calls under capture or without scratch, take one block per sample; the others form the factors
     // and expand them, chunk by chunk.  The values are the same bit for bit.  The line: 16-64-32, 512 samples 36 us as one
     // block per sample (its chains' latency; 126 us at 4096 samples against 43), 36-144-72, 64 samples 68 against 39;
-    // log psi alone 36-144-72, 1024 samples 21 against 28 (five launches), 64-256-128 34 against 29.
-    const double P = (double)m->P, nP = (double)n * P;
-    const bool small = O ? P < 1.2e4 && nP < 2.5e6 : P < 3.0e4 && nP < 3.0e7;
+    // log psi alone 36-144-72, 1024 samples 21 against 28 (five launches), 64-256-128 34 against 29.  Some columns: while
+    // the samples' blocks run all at once and write little, 513 samples of 36-144-72, 317 columns 45 against 51, of
+    // 25-100-50, 1,912 columns 41 against 47 (4,096 samples: 94 against 61).
+    const double P = (double)m->P, nP = (double)n * P, w = (double)(p1 - p0);
+    const bool small = !O                ? P < 3.0e4 && nP < 3.0e7
+                       : p1 - p0 == m->P ? P < 1.2e4 && nP < 2.5e6
+                                         : n <= 2048 && n * w < 2.5e6 && (P < 1.2e4 || (P < 2.0e4 && 16 * w <= P));
     bool todo = logpsi || O;
     if (todo && !small && !stream_capturing(stream)) {
         const ScratchLease lease(stream);

@@ -83,3 +83,20 @@ def test_factors_beyond_the_lds(nqs, W):
     nqs.nqs_sample_gram(model, xd, T, P)
     assert torch.equal(T, G)
     model.close()
+
+
+@pytest.mark.parametrize("N,widths,n", [(25, (100, 50), 2048), (25, (100, 50), 2049), (36, (144, 72), 513), (5, (3,), 70)])
+def test_columns_equal_the_whole(nqs, N, widths, n):
+    """Few samples and columns take one block per sample, others the factors: the values do not depend on it."""
+    rng = np.random.default_rng(n)
+    sizes = [N, *widths]
+    P = sum(o * (i + 1) for i, o in zip(sizes, sizes[1:]))
+    model = nqs.Model("ffnn", N, widths, rng.normal(scale=0.1, size=P))
+    x = torch.from_numpy((2 * rng.integers(0, 2, (n, N)) - 1).astype(np.int8)).to(DEV)
+    O = torch.empty(n, P, dtype=torch.float32, device=DEV)
+    nqs.nqs_logpsi_grad(model, x, O=O)
+    for p0, p1 in ((0, P), (0, P - 1), (P // 3, P // 3 + 1), (1, P // 16 + 1), (2, 2 + P // 4), (P // 2, P)):
+        cut = torch.full((n, p1 - p0), float("nan"), dtype=torch.float32, device=DEV)
+        nqs.nqs_logpsi_grad_cols(model, x, p0, p1, cut)
+        assert torch.equal(cut, O[:, p0:p1])
+    model.close()
