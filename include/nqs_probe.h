@@ -1,7 +1,9 @@
 /*
  * nqs_probe.h -- microbenchmarks of the rates this device achieves, used to
- * put the roofline figures of the method's kernels next to measured ceilings.
- * Measurement support only: no step of the method goes through these calls.
+ * put the roofline figures of the method's kernels next to measured ceilings,
+ * and the path that a solve took, for tests of its fallback.
+ * Measurement and test support only: no step of the method goes through these
+ * calls.
  */
 #ifndef NQS_PROBE_H
 #define NQS_PROBE_H
@@ -55,6 +57,15 @@ typedef enum {
  * bytes moved (read, or read + written).  *work is a host pointer.  NQS_EINVAL on a
  * bad kind, size or pointer. */
 nqs_status nqs_probe_rate(int32_t kind, int64_t size, const void *src, void *dst, double *work, void *stream);
+
+/* Whether the calling thread's last nqs_sr_solve (nqs_sr_solve_complex) ran as
+ * one launch (1) or as separate launches (0); -1 before its first. */
+int32_t nqs_probe_solve_one_launch(void);
+
+/* How often a block of the one-launch solve looks for the other blocks' values
+ * before it gives up and the solve falls back to separate launches, for later
+ * solves of the calling thread; 0: the default, some seconds. */
+void nqs_probe_solve_polls(int32_t polls);
 
 #ifdef __cplusplus
 }

@@ -25,7 +25,7 @@ EXPORTS = [
     "nqs_sr_solve", "nqs_sr_solve_mixed", "nqs_sr_solve_complex", "nqs_sr_update", "nqs_sample_noisy", "nqs_local_energy_complex",
     "nqs_last_error",
     "nqs_version",
-    "nqs_probe_rate",
+    "nqs_probe_rate", "nqs_probe_solve_one_launch", "nqs_probe_solve_polls",
 ]
 
 PROBE_KINDS = {"fma_f32": 0, "log_f32": 1, "exp_f32": 2, "mfma_bf16_k16": 3, "mfma_bf16_k32": 4, "mfma_f32": 5,
@@ -124,6 +124,8 @@ def load() -> ctypes.CDLL:
         "nqs_sr_solve": ([P, P, i64, ctypes.c_double, ctypes.c_double, i32, P, P, P, P], st),
         "nqs_sr_solve_complex": ([P, P, P, i64, ctypes.c_double, ctypes.c_double, i32, P, P, P, P], st),
         "nqs_probe_rate": ([i32, i64, P, P, P, P], st),
+        "nqs_probe_solve_one_launch": ([], i32),
+        "nqs_probe_solve_polls": ([i32], None),
         "nqs_sr_solve_mixed": ([P, P, i64, ctypes.c_double, i32, ctypes.c_double, i32, P, P, P, P, P, P], st),
         "nqs_sr_update": ([P, P, i64, P, ctypes.c_double, P, P], st),
         "nqs_sample_noisy": ([P, P, ctypes.c_double, ctypes.c_uint64, P, P, P, P, P], st),

@@ -28,6 +28,7 @@
 #include "common.h"
 #include "internal.h"
 #include "nqs.h"
+#include "nqs_probe.h"
 
 namespace nqs {
 
@@ -38,12 +39,16 @@ constexpr unsigned long long kCgEmpty = 0x7FF8A5C3D2E1F00Full;
 // Beyond 5120 unknowns more than two fifths of T would be read again each iteration, and two launches are as good
 // (n = 8192: 82 us an iteration this way, 87 us as two launches).
 constexpr int64_t kCgMax = 5120;
-constexpr int kCgSpins = 1 << 21;            // polls before a block gives up (seconds)
+constexpr int kCgPolls = 1 << 21;            // before a block gives up (seconds)
+
+// of the calling thread: polls of its later solves (0: kCgPolls), and whether its last one was one launch (-1: none yet)
+static thread_local int g_cg_polls = 0;
+static thread_local int g_cg_one_launch = -1;
 
 struct CgArgs {
     const float *T;
     const double *eps;
-    int n, max_iter, check;
+    int n, max_iter, check, polls;
     double shift, tol;
     double *y;
     unsigned long long *slots;   // [3][n]
@@ -225,7 +230,7 @@ __global__ void __launch_bounds__(kCgThreads) sr_cg_kernel(CgArgs A)
                         waiting = waiting || v[e] == kCgEmpty;
                         ap[e] = __builtin_bit_cast(double, v[e]);
                     }
-                    if (waiting && ++spins > kCgSpins) {
+                    if (waiting && ++spins >= A.polls) {
                         gave_up = 1;
                         waiting = false;
                     }
@@ -285,14 +290,16 @@ __global__ void __launch_bounds__(kCgThreads) sr_cg_kernel(CgArgs A)
 
 size_t cg_resident_bytes(int64_t n) { return 3 * sizeof(double) * (size_t)n + 64; }
 
-// Solves in one launch and waits for it; *done = false when the launch does not apply (size, device, capture) or gave
-// up, with nothing that the caller's own solve would not overwrite.  ws: cg_resident_bytes(n).
+// Solves in one launch and waits for it; *done = false when the launch does not apply (size, device, y in the energies'
+// buffer) or gave up, with nothing that the caller's own solve would not overwrite.  ws: cg_resident_bytes(n).
 nqs_status cg_resident(const float *T, const double *eloc, int64_t n, double shift, double tol, int max_iter, int check,
                        double *y, void *ws, int *iters, double *rel, bool *done, hipStream_t stream)
 {
     *done = false;
-    // y is written while other blocks may still read eloc only if the two overlap
-    if (n > kCgMax || (y < eloc + n && eloc < y + n)) return NQS_OK;
+    g_cg_one_launch = 0;
+    // (one sample's centred energy is zero: nothing to solve)  y is written while other blocks may still read eloc only
+    // if the two overlap
+    if (n < 2 || n > kCgMax || (y < eloc + n && eloc < y + n)) return NQS_OK;
     // rows per wave: as many as let at most one block per CU hold all rows
     const int cus = device_cus();
     const void *kernel = nullptr;
@@ -309,13 +316,18 @@ nqs_status cg_resident(const float *T, const double *eloc, int64_t n, double shi
         hipDeviceGetAttribute(&coop, hipDeviceAttributeCooperativeLaunch, dev) != hipSuccess || !coop ||
         blocks > cus)
         return NQS_OK;
-    if (lds > 60 * 1024) (void)hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (lds > 60 * 1024 &&
+        hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess) {
+        (void)hipGetLastError();
+        return NQS_OK;
+    }
     CgArgs A;
     A.T = T;
     A.eps = eloc;
     A.n = (int)n;
     A.max_iter = max_iter;
     A.check = check;
+    A.polls = g_cg_polls > 0 ? g_cg_polls : kCgPolls;
     A.shift = shift;
     A.tol = tol;
     A.y = y;
@@ -336,7 +348,12 @@ nqs_status cg_resident(const float *T, const double *eloc, int64_t n, double shi
     *iters = (int)out[0];
     *rel = out[1];
     *done = true;
+    g_cg_one_launch = 1;
     return NQS_OK;
 }
 
 }  // namespace nqs
+
+extern "C" int32_t nqs_probe_solve_one_launch(void) { return nqs::g_cg_one_launch; }
+
+extern "C" void nqs_probe_solve_polls(int32_t polls) { nqs::g_cg_polls = polls > 0 ? polls : 0; }
