@@ -410,7 +410,7 @@ __global__ void __launch_bounds__(kCnnThreads) cnn_eloc_tfim_kernel(CnnDev net, 
                 const int right = ((x + 1) % L) * L + y, down = x * L + (y + 1) % L;
                 diag += (double)(l.x[s] * l.x[right]) + (double)(l.x[s] * l.x[down]);
             }
-            eloc[k] = J * diag + h * off;
+            eloc[k] = fma(h, off, J * diag);
         }
         __syncthreads();
     }
@@ -919,7 +919,7 @@ __global__ void __launch_bounds__(256) cnn_eloc_reduce_kernel(const int8_t *__re
         diag += group_sum<64>(d);            // whole numbers: exact in any order
         for (int i = 0; i < 64; ++i) off += __shfl(e, i, 64);   // site order (zeros past the last site)
     }
-    if (lane == 0) eloc[k] = J * diag + h * off;
+    if (lane == 0) eloc[k] = fma(h, off, J * diag);   // as the one-configuration kernel, to the last bit
 }
 
 // Whether the batched sampler serves this network (its log psi differs from the one-chain kernel's in the order
