@@ -9,6 +9,7 @@
 #include <vector>
 
 #include "common.h"
+#include "expand.h"
 #include "ffnn_reg.h"
 #include "internal.h"
 
@@ -593,74 +594,50 @@ static nqs_status factors_from(const FfnnDev &net, const int8_t *samples, int64_
 // LDS (all of a sample's would not fit it for every network that the gradient takes: 165 KB for eight layers of 2,752
 // units); 16 bytes a store where every layer's rows and O's are multiples of 16 bytes.  4096 samples of the 100-400-200
 // network (1.98 GB): 482 us with the factors, 4.5 TB/s for this kernel (a copy reaches 5.2, read and written);
-// 905 us when a block wrote 4 KB of each of 16 samples, 1762 us with one block per sample for everything.
-struct ExpandArgs {
-    const float *acts, *dels;
-    float *O;                     // [n][p1 - p0]
-    int64_t n, p0, p1, sa, sd;    // sa, sd: row lengths of acts and dels
-    int L;
-    int64_t offW[NQS_MAX_LAYERS + 1];   // first parameter of layer l; offW[L] = P
-    int in[NQS_MAX_LAYERS], out[NQS_MAX_LAYERS];
-    int64_t offA[NQS_MAX_LAYERS], offD[NQS_MAX_LAYERS];
-};
-
-constexpr int kExpandSpan = 16384;
-
-// rows [r0, r0 + result) of layer l's weights that the parameters [b0, b1) meet
-__host__ __device__ inline int expand_rows(const ExpandArgs &E, int l, int64_t b0, int64_t b1, int &r0)
-{
-    const int64_t w0 = E.offW[l], w1 = w0 + (int64_t)E.out[l] * E.in[l];
-    const int64_t s0 = b0 > w0 ? b0 : w0, s1 = b1 < w1 ? b1 : w1;
-    if (s0 >= s1) return 0;
-    const unsigned in = (unsigned)E.in[l];           // a layer has at most 8192^2 weights
-    r0 = (int)((unsigned)(s0 - w0) / in);
-    return (int)((unsigned)(s1 - 1 - w0) / in) - r0 + 1;
-}
-
-// LDS floats of a layer of which `rows` rows are met: its inputs, then the rows' deltas, each a multiple of 16 bytes
-__host__ __device__ inline int expand_words(int in, int rows) { return rows > 0 ? ((in + 3) & ~3) + ((rows + 3) & ~3) : 0; }
-
+// 905 us when a block wrote 4 KB of each of 16 samples, 1762 us with one block per sample for everything.  (All of a
+// sample's factors in LDS, where they fit: 858 instead of 861 us for 4001 samples with the forces.)
 // V consecutive parameters per thread and store (1, or 4 where every row is a multiple of 4 floats)
 template <int V>
 __global__ void __launch_bounds__(256) ffnn_expand_kernel(ExpandArgs E, int spans)
 {
-    extern __shared__ __align__(16) float fac[];   // of each layer whose weights the span meets: inputs, rows' deltas
+    extern __shared__ __align__(16) float fac[];   // of each layer that the span meets: inputs, rows' deltas, biases' deltas
     const int64_t k = blockIdx.x / spans;
     const int tid = threadIdx.x;
     const int64_t b0 = E.p0 + (int64_t)(blockIdx.x - k * spans) * kExpandSpan, b1 = min(E.p1, b0 + kExpandSpan);
-    const float *acts = E.acts + k * E.sa, *dels = E.dels + k * E.sd;
     float *f = fac;
     for (int l = 0; l < E.L; ++l) {
-        int r0 = 0;
-        const int in = E.in[l], rows = expand_rows(E, l, b0, b1, r0);
-        if (rows == 0) continue;
-        float *d = f + ((in + 3) & ~3);
-        for (int i = tid; i < in; i += 256) f[i] = acts[E.offA[l] + i];
-        for (int i = tid; i < rows; i += 256) d[i] = dels[E.offD[l] + r0 + i];
-        f += expand_words(in, rows);
+        const ExpandPart x = expand_part(E, l, b0, b1);
+        const float *d = E.dels + k * E.sd + E.offD[l];
+        if (x.rows > 0) {
+            const int in = E.in[l];
+            for (int i = tid; i < in; i += 256) f[i] = E.acts[k * E.sa + E.offA[l] + i];
+            f += (in + 3) & ~3;
+            for (int i = tid; i < x.rows; i += 256) f[i] = d[x.r0 + i];
+            f += (x.rows + 3) & ~3;
+        }
+        for (int i = tid; i < x.nd; i += 256) f[i] = d[x.d0 + i];
+        f += (x.nd + 3) & ~3;
     }
     __syncthreads();
-    float *O = E.O + k * (E.p1 - E.p0) - E.p0;
+    float *O = E.O + k * (E.p1 - E.p0) + (b0 - E.p0);
     f = fac;
     for (int l = 0; l < E.L; ++l) {
-        int r0 = 0;
-        const int in = E.in[l], rows = expand_rows(E, l, b0, b1, r0);
-        const int64_t w0 = E.offW[l], w1 = w0 + (int64_t)E.out[l] * in;
-        // weights: position q = r in + c, advanced by 256 V with (r, c) carried
-        if (rows > 0) {
-            const float *a = f, *d = f + ((in + 3) & ~3) - r0;
-            f += expand_words(in, rows);
-            const int64_t s0 = max(b0, w0), s1 = min(b1, w1);
-            const int64_t q0 = s0 - w0 + tid * V;
-            int r = (int)(q0 / in), c = (int)(q0 - (int64_t)r * in);
-            const int dr = 256 * V / in, dc = 256 * V - dr * in;
-            for (int64_t p = s0 + tid * V; p < s1; p += 256 * V) {
+        const ExpandPart x = expand_part(E, l, b0, b1);
+        if (x.rows > 0) {
+            const unsigned in = (unsigned)E.in[l], inv = E.inv[l];
+            const float *a = f, *d = f + ((in + 3) & ~3u);
+            f += expand_words((int)in, x.rows, 0);
+            // position q0 + t is row r0 + r, column c; t advanced by 256 V with (r, c) carried
+            const unsigned c0 = x.q0 - x.r0 * in + tid * V;
+            unsigned r = expand_div(c0, in, inv), c = c0 - r * in;
+            const unsigned dr = expand_div(256 * V, in, inv), dc = 256 * V - dr * in;
+            for (unsigned t = tid * V; t < x.count; t += 256 * V) {
                 const float dv = d[r];
                 if constexpr (V == 4) {
                     const float4 av = *reinterpret_cast<const float4 *>(a + c);
-                    *reinterpret_cast<float4 *>(O + p) = make_float4(dv * av.x, dv * av.y, dv * av.z, dv * av.w);
+                    *reinterpret_cast<float4 *>(O + t) = make_float4(dv * av.x, dv * av.y, dv * av.z, dv * av.w);
                 } else {
-                    O[p] = dv * a[c];
+                    O[t] = dv * a[c];
                 }
                 r += dr;
                 c += dc;
@@ -669,29 +646,12 @@ __global__ void __launch_bounds__(256) ffnn_expand_kernel(ExpandArgs E, int span
                     ++r;
                 }
             }
+            O += x.count;
         }
-        // biases: the deltas themselves
-        for (int64_t p = max(b0, w1) + tid; p < min(b1, E.offW[l + 1]); p += 256) O[p] = dels[E.offD[l] + (p - w1)];
+        for (int i = tid; i < x.nd; i += 256) O[i] = f[i];
+        f += (x.nd + 3) & ~3;
+        O += x.nd;
     }
-}
-
-// LDS floats of the span that needs most.  At most kExpandSpan (rows met, and the inputs of layers that lie within the
-// span) and the inputs of the two layers at its ends, 8192 each: 128 KB.
-static int expand_lds_words(const ExpandArgs &E)
-{
-    int words = 0;
-    for (int l = 0; l < E.L; ++l) {
-        if (E.offW[l + 1] <= E.p0 || E.offW[l] >= E.p1) continue;
-        // a span within the layer
-        words = std::max(words, expand_words(E.in[l], std::min(E.out[l], kExpandSpan / E.in[l] + 2)));
-        // the span that the layer ends in
-        if (E.offW[l + 1] >= E.p1) continue;
-        const int64_t b0 = E.p0 + (E.offW[l + 1] - E.p0) / kExpandSpan * kExpandSpan, b1 = std::min(E.p1, b0 + kExpandSpan);
-        int sum = 0, r0;
-        for (int j = 0; j < E.L; ++j) sum += expand_words(E.in[j], expand_rows(E, j, b0, b1, r0));
-        words = std::max(words, sum);
-    }
-    return words;
 }
 
 static ExpandArgs expand_args(const FfnnDev &net)
@@ -702,6 +662,7 @@ static ExpandArgs expand_args(const FfnnDev &net)
     for (int l = 0; l < E.L; ++l) {
         E.in[l] = net.widths[l];
         E.out[l] = net.widths[l + 1];
+        E.inv[l] = 0xFFFFFFFFu / (unsigned)net.widths[l];
         E.offW[l] = off;
         E.offA[l] = E.sa;
         E.offD[l] = E.sd;
