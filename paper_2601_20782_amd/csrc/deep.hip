@@ -1045,7 +1045,10 @@ static void deep_frag_forward(const FfnnDev &f, const DeepBuffers &b, const int8
         // alone takes 0.7 of that; 128 x 64 tiles, four side by side, 0.94 of the unit each, fewer 1.06 + 0.58 t.  With
         // 1600 x 800 weights the choice is 128 x 64 below 5,500 rows (4,000: 21.4 us, 256 x 64 24.6), 256 x 64 at 8,200
         // (29.6; 128 x 64 33.4, 256 x 128 34.7), 256 x 96 at 12,000 (36.6; 256 x 128 43.7), 256 x 128 at 16,400
-        // (46.3; 256 x 64 51.7, 256 x 160 51.5) and 256 x 160 at 32,800 (84.7; 256 x 128 89.8).
+        // (46.3; 256 x 64 51.7, 256 x 160 51.5) and 256 x 160 at 32,800 (84.7; 256 x 128 89.8).  The constants are those of
+        // 1600 x 800 weights in BF16.  Elsewhere, steps of 500 to 65,536 rows of the networks 64-250-130-70, 100-400-200-100,
+        // 256-1024-512-256, 400-1600-800-400 and 144-2000-300-1500 take from 0.93 to 1.04 times the best step with one tile
+        // for all layers in 16 bits, to 1.07 times in E4M3 (worst: 6,000 rows of the last, 51.5 us, 128 x 64 48.0).
         const int64_t cus = device_cus();
         auto tiles = [&](int RB, int NT) {   // of the busiest CU
             return (double)(((expect + 128 * RB - 1) / (128 * RB) * ((g.nblk + NT - 1) / NT) + cus - 1) / cus);

@@ -708,11 +708,13 @@ __device__ __forceinline__ uint32_t eloc_row_code(int KE, int i, int j, int s, b
 // h1 = ReLU(z1 + g (W1[:, i] - W1[:, j])) of a row (g = -2 s_i), the 16 bytes c16 / 16 of it (lanes past the row's
 // chunks repeat the last one).  W1l: [N + 1][K] in LDS; zs: [G][2][K / 8][4] (units 8c .. 8c + 3 of every
 // chunk, then units 8c + 4 .. 8c + 7, so that the 16-byte reads of consecutive lanes are consecutive).
-// A pass is bound by the instructions its waves issue: with two waves on a SIMD each issues a vector one about every 5
-// cycles (8.3 where it needs the one before) and a scalar one every 8.4.  So the code holds places, not sites, needs no
-// select for flips, and is decoded in vector registers: 47 vector and no scalar instructions a row instead of 53 and 16 (BF16).
-// 400-200, 65,001 samples of 100 sites: 2,090 -> 1,950 to 1,980 us.  (Waves of their own for staging and for the next group's
-// preparation, four or twelve waves in all, took 2,380 to 2,810 us.)
+// A wave issues a vector instruction at best every 5 cycles (8.3 where it needs the one before) and a scalar one every 8.4.
+// So the code holds places, not sites, needs no select for flips, and is decoded in vector registers: 47 vector and no
+// scalar instructions a row instead of 53 and 16 (BF16).  400-200, 65,001 samples of 100 sites: 2,092 -> 2,002 us; at
+// 8,192,000 samples it is as fast as before, 262 ms: the instructions a 32-row pass no longer issues (853 vector ones per SIMD,
+// 103 scalar; 904 and 131 before) became waiting.  Its counters there: a wave waits for LDS or a barrier in 40 % of its
+// cycles, for its turn to issue in 18 %, issues vector instructions in 31 %; matrix cores busy 24 %.  (Waves of their own
+// for staging and for the next group's preparation, four or twelve waves in all, took 2,380 to 2,810 us.)
 template <typename T, int K>
 struct ElocRow {
     typedef typename Mc<T>::frag frag;

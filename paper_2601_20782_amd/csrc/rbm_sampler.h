@@ -15,8 +15,9 @@
 // The (C,S) table (plus one neutral entry (1,0) used by lanes past the last
 // hidden unit) lives in LDS when it fits, else it is read through L2; the
 // table column of the next proposal is loaded while the current one is
-// decided.  Group sums use DPP and end in one lane, read back with
-// v_readlane, so every lane of a chain takes the same decision.
+// decided.  Group sums use DPP and give every lane of a chain the same total,
+// hence the same decision (16 and 32 lanes: moved between lanes within the
+// vector registers; 64 lanes: read back from one with v_readlane).
 //
 // With up to two waves per SIMD a step is its wave's chain of instructions (8.3
 // cycles where one needs the one before, 5 otherwise): broadcasts run two

@@ -3,8 +3,9 @@
 //
 // As two launches per iteration the solve spent 31 us of an n = 4096 iteration on reading T (67 MB) at 256
 // wavefronts' worth of loads in flight, on one block's vector updates, and on the gaps between launches.  But 67 MB
-// are half of the chip's 128 MB of vector registers: a block of 1024 threads per CU keeps its 16 rows of T (64
-// registers a thread) from the first iteration to the last.  What an iteration then has to move is T p: every block
+// are half of the chip's 128 MB of vector registers: a block of 1024 threads per CU keeps its 16 rows of T (64 of the
+// 128 registers that a thread may have; the form for n up to 4096 spills 12 others, the one above it 11) from the first
+// iteration to the last.  What an iteration then has to move is T p: every block
 // publishes its 16 values, reads all n of them, and repeats the scalar sums and the updates of r, z and p for all n
 // elements in the same order, so that every block holds the same bits and takes the same decisions.  One exchange an
 // iteration, no other communication.

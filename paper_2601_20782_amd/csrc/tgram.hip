@@ -65,7 +65,7 @@ struct FacArgs {
 };
 
 constexpr int kFT = 64;    // tile side
-constexpr int kFK = 32;    // staged contraction chunk of the VALU kernels
+constexpr int kFK = 32;    // contraction steps staged per barrier by fac_outer and fac_v
 
 __device__ inline int fac_layer_of(const FacArgs &A, int64_t t, bool vslots)
 {
