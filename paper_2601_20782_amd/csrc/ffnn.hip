@@ -594,10 +594,13 @@ static nqs_status factors_from(const FfnnDev &net, const int8_t *samples, int64_
 // LDS (all of a sample's would not fit it for every network that the gradient takes: 165 KB for eight layers of 2,752
 // units); 16 bytes a store where every layer's rows and O's are multiples of 16 bytes.  4096 samples of the 100-400-200
 // network (1.98 GB): 482 us with the factors, 4.5 TB/s for this kernel (a copy reaches 5.2, read and written);
-// 905 us when a block wrote 4 KB of each of 16 samples, 1762 us with one block per sample for everything.  (All of a
-// sample's factors in LDS, where they fit: 858 instead of 861 us for 4001 samples with the forces.)
+// 905 us when a block wrote 4 KB of each of 16 samples, 1762 us with one block per sample for everything.
+// Small networks of several blocks a sample keep all deltas and inputs of the layers met (WHOLE): 4001 samples of
+// 100-400-200 take 451 us wherever O lies, 452 to 473 with only the needed ones; beyond 10 KB of factors these are as
+// fast or faster (64-2048-2048-2048, 100 samples: 1,063 us against 1,365).
 // V consecutive parameters per thread and store (1, or 4 where every row is a multiple of 4 floats)
-template <int V>
+// WHOLE: all deltas and inputs of the layers that the span meets, else only those that it needs
+template <int V, bool WHOLE>
 __global__ void __launch_bounds__(256) ffnn_expand_kernel(ExpandArgs E, int spans)
 {
     extern __shared__ __align__(16) float fac[];   // of each layer that the span meets: inputs, rows' deltas, biases' deltas
@@ -608,13 +611,13 @@ __global__ void __launch_bounds__(256) ffnn_expand_kernel(ExpandArgs E, int span
     for (int l = 0; l < E.L; ++l) {
         const ExpandPart x = expand_part(E, l, b0, b1);
         const float *d = E.dels + k * E.sd + E.offD[l];
-        if (x.rows > 0) {
-            const int in = E.in[l];
+        if (WHOLE ? x.rows + x.nd > 0 : x.rows > 0) {
+            const int in = E.in[l], r0 = WHOLE ? 0 : (int)x.r0, rows = WHOLE ? E.out[l] : x.rows;
+            for (int i = tid; i < rows; i += 256) f[((in + 3) & ~3) + i] = d[r0 + i];
             for (int i = tid; i < in; i += 256) f[i] = E.acts[k * E.sa + E.offA[l] + i];
-            f += (in + 3) & ~3;
-            for (int i = tid; i < x.rows; i += 256) f[i] = d[x.r0 + i];
-            f += (x.rows + 3) & ~3;
+            f += expand_words(in, rows, 0);
         }
+        if (WHOLE) continue;
         for (int i = tid; i < x.nd; i += 256) f[i] = d[x.d0 + i];
         f += (x.nd + 3) & ~3;
     }
@@ -623,10 +626,15 @@ __global__ void __launch_bounds__(256) ffnn_expand_kernel(ExpandArgs E, int span
     f = fac;
     for (int l = 0; l < E.L; ++l) {
         const ExpandPart x = expand_part(E, l, b0, b1);
-        if (x.rows > 0) {
-            const unsigned in = (unsigned)E.in[l], inv = E.inv[l];
-            const float *a = f, *d = f + ((in + 3) & ~3u);
+        const unsigned in = (unsigned)E.in[l], inv = E.inv[l];
+        const float *a = f, *d = f + ((in + 3) & ~3u);   // the deltas from the first row met on
+        if (WHOLE) {
+            if (x.rows + x.nd > 0) f += expand_words((int)in, E.out[l], 0);
+        } else {
             f += expand_words((int)in, x.rows, 0);
+        }
+        if (x.rows > 0) {
+            if (WHOLE) d += x.r0;
             // position q0 + t is row r0 + r, column c; t advanced by 256 V with (r, c) carried
             const unsigned c0 = x.q0 - x.r0 * in + tid * V;
             unsigned r = expand_div(c0, in, inv), c = c0 - r * in;
@@ -648,8 +656,9 @@ __global__ void __launch_bounds__(256) ffnn_expand_kernel(ExpandArgs E, int span
             }
             O += x.count;
         }
-        for (int i = tid; i < x.nd; i += 256) O[i] = f[i];
-        f += (x.nd + 3) & ~3;
+        const float *b = WHOLE ? a + ((in + 3) & ~3u) + x.d0 : f;
+        for (int i = tid; i < x.nd; i += 256) O[i] = b[i];
+        if (!WHOLE) f += (x.nd + 3) & ~3;
         O += x.nd;
     }
 }
@@ -684,7 +693,10 @@ static nqs_status expand_columns(ExpandArgs E, int64_t n, int64_t p0, int64_t p1
     for (int l = 0; l < E.L; ++l) vec = vec && E.in[l] % 4 == 0 && E.out[l] % 4 == 0;
     const int64_t spans = (p1 - p0 + kExpandSpan - 1) / kExpandSpan;
     const int64_t most = (((int64_t)1 << 24) - 1) / spans;   // samples per launch: fewer than 2^32 threads
-    const size_t lds = sizeof(float) * (size_t)expand_lds_words(E);
+    int all = 0;
+    for (int l = 0; l < E.L; ++l) all += expand_words(E.in[l], E.out[l], 0);
+    const bool whole = vec && spans > 1 && all <= 2560;
+    const size_t lds = sizeof(float) * (size_t)(whole ? all : expand_lds_words(E));
     for (int64_t k0 = 0; k0 < n; k0 += most) {
         ExpandArgs C = E;
         C.n = std::min(most, n - k0);
@@ -695,8 +707,9 @@ static nqs_status expand_columns(ExpandArgs E, int64_t n, int64_t p0, int64_t p1
             allow_lds(kernel, lds);
             hipLaunchKernelGGL(kernel, dim3((unsigned)(C.n * spans)), dim3(256), lds, stream, C, (int)spans);
         };
-        if (vec) launch(ffnn_expand_kernel<4>);
-        else launch(ffnn_expand_kernel<1>);
+        if (whole) launch(ffnn_expand_kernel<4, true>);
+        else if (vec) launch(ffnn_expand_kernel<4, false>);
+        else launch(ffnn_expand_kernel<1, false>);
     }
     NQS_HIP_TRY(hipGetLastError());
     return NQS_OK;

@@ -85,7 +85,8 @@ def test_factors_beyond_the_lds(nqs, W):
     model.close()
 
 
-@pytest.mark.parametrize("N,widths,n", [(25, (100, 50), 2048), (25, (100, 50), 2049), (36, (144, 72), 513), (5, (3,), 70)])
+@pytest.mark.parametrize("N,widths,n", [(25, (100, 50), 2048), (25, (100, 50), 2049), (36, (144, 72), 513), (5, (3,), 70),
+                                            (64, (256, 128), 300), (40, (64, 404, 32), 70)])
 def test_columns_equal_the_whole(nqs, N, widths, n):
     """Few samples and columns take one block per sample, others the factors: the values do not depend on it."""
     rng = np.random.default_rng(n)
